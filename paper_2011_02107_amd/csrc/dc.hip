@@ -1,392 +1,662 @@
-// Divide-and-conquer eigen-decomposition of a symmetric tridiagonal matrix
-// (Cuppen's tear, deflation and the secular equation; eigenvectors of each
-// rank-one update from the Gu-Eisenstat recomputed z so they stay orthogonal
-// to working precision).  The host keeps the O(n) bookkeeping; the secular
-// roots, the eigenvector matrices of the rank-one problems and their products
-// with the child eigenvectors (FP64 MFMA GEMMs) run on the GPU.
+// Divide-and-conquer eigen-decomposition of symmetric tridiagonal matrices (Cuppen's tear,
+// deflation and the secular equation; eigenvectors of each rank-one update from the Gu-Eisenstat
+// recomputed z so they stay orthogonal to working precision), for any number of matrices at once.
 //
-// Eigenvectors are kept as rows: Zc[lo + j][lo + i] = component i of
-// eigenvector j of the block [lo, hi).
+// What bounds it: a merge of a few hundred rows is microseconds of arithmetic, so the tree is walked
+// one depth at a time with every merge of that depth, of every matrix, in the same launches.  A
+// depth costs one copy to the host (the update vectors and eigenvalues), the O(n) deflation
+// bookkeeping there, one copy back and seven launches; the leaves are solved on the GPU.
+// Measured on one matrix of n = 1237 (and its 866-row H~): the merges took 75 ms as one host-driven
+// merge after another with a thread per secular root.
+//
+// Eigenvectors are kept as rows: row lo + j of a block [lo, hi) holds component lo + i at column
+// lo + i.  A node of depth t writes buffer t mod 2 (the root, depth 0, the caller's Z), so its
+// children, all at depth t + 1, sit in the other one.  Entries outside a node's own columns are
+// never read: each merge knows which half every row is supported on.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <numeric>
 #include <vector>
 
 #include "host_rules.h"
 #include "internal.h"
+#include "secular.h"
 
 namespace dacp {
 
 namespace {
 
 constexpr int kLeaf = 32;
+constexpr int kDcThreads = 256;  // four waves, one secular root (or row) each
 
-// Root j of f(lam) = 1 + rho sum_i z_i^2 / (d_i - lam) in (d_j, d_{j+1}) (or
-// (d_{k-1}, d_{k-1} + rho |z|^2] for the last one), stored as origin index
-// org[j] and offset tau[j] from d[org[j]] so that d_i - lam = (d_i - d_org) - tau
-// keeps full relative accuracy near the pole.
-__global__ void k_secular(const double *d, const double *z, int k, double rho, int *org, double *tau) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= k) return;
-  double zz = 0.0;
-  for (int i = 0; i < k; ++i) zz += z[i] * z[i];
-  const double hi_gap = (j + 1 < k) ? d[j + 1] - d[j] : rho * zz;
-  // f at the middle of the interval decides the nearer pole
-  int o = j;
-  {
-    const double mid = 0.5 * hi_gap;
-    double f = 1.0;
-    for (int i = 0; i < k; ++i) f += rho * z[i] * z[i] / ((d[i] - d[j]) - mid);
-    if (j + 1 < k && f <= 0.0) o = j + 1;
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// One leaf: rows [lo, hi) of the matrix with diagonal d and off-diagonal e, Z its eigenvector buffer.
+struct DcLeaf {
+  const double *d, *e;
+  double *Z, *w;
+  int n, lo, hi;
+};
+
+// One rank-one merge of the halves [lo, m) and [m, hi).
+struct DcMerge {
+  double *Zin, *Zout;  // children's rows, result rows (ld n each)
+  double *U, *G;       // eigenvectors of the update and the gathered children's rows (ld n each)
+  double *w;           // the matrix's eigenvalues, block row t at w[lo + t]
+  double rho;
+  int n, lo, m, hi;
+  int off;             // offset of this merge in the depth's packed per-row arrays
+  int k;               // size of the secular problem
+  int k1, k12;         // its rows supported on the first half only / on both (the rest: second half)
+  int nrot, rot;       // deflating rotations and their offset
+};
+
+// Rotation of rows p and q (absolute); bit 0 / 1 of pf, qf: the row is supported on the first /
+// second half when the rotation reads it.
+struct DcRot {
+  double c, s;
+  int p, q, pf, qf;
+};
+
+// Packed per-row device arrays of one depth (one slot per block row of every merge).
+struct DcRows {
+  const double *pole, *z;  // secular problem, ascending poles (k entries)
+  const double *dval;      // deflated eigenvalues ascending (n - k entries)
+  const int *ucol;         // column of U / row of G of pole i
+  const int *src;          // G row q: absolute source row
+  const int *dsrc;         // deflated entry t: absolute source row
+  const int *dflag;        // deflated entry t: halves its row is supported on (bits 0, 1)
+  int *org;
+  double *tau, *zh;
+  int *rank;               // root j: block row of its eigenvector
+};
+
+struct WaveLanes {
+  __device__ __forceinline__ int first() const { return threadIdx.x & 63; }
+  __device__ __forceinline__ int stride() const { return 64; }
+  __device__ __forceinline__ double sum(double v) const {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
   }
-  const double base = d[o] - d[j];  // 0 or hi_gap
-  // bracket for tau relative to d[o]
-  double lo, hi;
-  if (o == j) {
-    lo = 0.0;
-    hi = (j + 1 < k) ? 0.5 * hi_gap : hi_gap;
-  } else {
-    lo = -0.5 * hi_gap;
-    hi = 0.0;
+};
+
+// Leaf eigenproblem, one wave each: implicit QR with a Wilkinson shift on the torn diagonal (every
+// lane runs the same scalar chain and keeps its own copy of what it writes; lane i also holds
+// component i of every eigenvector), then the eigenvalues sorted by counting.  bad is set when the
+// iteration does not end.
+__global__ __launch_bounds__(64) void k_dc_leaf(const DcLeaf *leaves, int *bad) {
+  __shared__ double Zs[kLeaf][kLeaf + 1];
+  const DcLeaf L = leaves[blockIdx.x];
+  const int n = L.hi - L.lo, lane = threadIdx.x;
+  const int col = lane & (kLeaf - 1);  // lanes 32.. shadow lanes 0..
+  __shared__ double d[kLeaf], e[kLeaf];
+  for (int i = 0; i < n; ++i) {
+    double v = L.d[L.lo + i];
+    // the tears at the block's two ends (|e| taken off both neighbours)
+    if (i == 0 && L.lo > 0) v -= fabs(L.e[L.lo - 1]);
+    if (i == n - 1 && L.hi < L.n) v -= fabs(L.e[L.hi - 1]);
+    d[i] = v;
+    e[i] = (i + 1 < n) ? L.e[L.lo + i] : 0.0;
+    Zs[i][col] = (i == col) ? 1.0 : 0.0;
   }
-  auto feval = [&](double t, double &fp) {
-    double f = 1.0;
-    fp = 0.0;
-    for (int i = 0; i < k; ++i) {
-      const double del = (d[i] - d[o]) - t;
-      const double q = z[i] / del;
-      f += rho * z[i] * q;
-      fp += rho * q * q;
+  const double eps = 2.220446049250313e-16;
+  int q = n - 1, iters = 0;
+  bool ok = true;
+  while (q > 0) {
+    if (e[q - 1] == 0.0 || fabs(e[q - 1]) <= eps * (fabs(d[q - 1]) + fabs(d[q]))) {
+      e[q - 1] = 0.0;
+      --q;
+      continue;
     }
-    return f;
-  };
-  double t = 0.5 * (lo + hi);
-  for (int it = 0; it < 70; ++it) {
-    double fp;
-    const double f = feval(t, fp);
-    if (f > 0.0) hi = t;
-    else lo = t;
-    const double tn = 0.5 * (lo + hi);
-    if (tn == t) break;
-    t = tn;
+    int p = q - 1;
+    while (p > 0 && !(fabs(e[p - 1]) <= eps * (fabs(d[p - 1]) + fabs(d[p])))) --p;
+    if (p > 0) e[p - 1] = 0.0;
+    if (++iters > 40 * n + 100) {
+      ok = false;
+      break;
+    }
+    const double a = d[q - 1], bb = e[q - 1], cc = d[q];
+    const double delta = 0.5 * (a - cc);
+    const double den = delta + (delta >= 0.0 ? 1.0 : -1.0) * hypot(delta, bb);
+    const double mu = (den != 0.0) ? cc - bb * bb / den : cc;
+    double x = d[p] - mu, z = e[p], dk = d[p], ek = e[p];
+    double carry = Zs[p][col];
+    for (int k = p; k < q; ++k) {
+      double c = 1.0, s = 0.0;
+      if (z != 0.0) {
+        const bool big = fabs(z) > fabs(x);
+        const double tau = big ? -x / z : -z / x;
+        const double r = 1.0 / sqrt(1.0 + tau * tau);
+        s = big ? r : r * tau;
+        c = big ? r * tau : r;
+      }
+      if (k > p) e[k - 1] = c * x - s * z;
+      const double dk1 = d[k + 1], en = e[k + 1];
+      d[k] = c * c * dk - 2.0 * c * s * ek + s * s * dk1;
+      const double dn = s * s * dk + 2.0 * c * s * ek + c * c * dk1;
+      const double off = c * s * (dk - dk1) + (c * c - s * s) * ek;
+      e[k] = off;
+      d[k + 1] = dn;
+      dk = dn;
+      if (k < q - 1) {
+        x = off;
+        z = -s * en;
+        ek = c * en;
+        e[k + 1] = ek;
+      }
+      const double zn = Zs[k + 1][col];
+      Zs[k][col] = c * carry - s * zn;
+      carry = s * carry + c * zn;
+    }
+    Zs[q][col] = carry;
   }
-  for (int it = 0; it < 4; ++it) {  // Newton polish inside the bracket
-    double fp;
-    const double f = feval(t, fp);
-    if (!(fp > 0.0)) break;
-    double tn = t - f / fp;
-    if (!(tn > lo && tn < hi)) break;
-    t = tn;
-  }
-  (void)base;
-  org[j] = o;
-  tau[j] = t;
-}
-
-// zhat_i = sign(z_i) sqrt(prod_j (lam_j - d_i) / (rho prod_{j != i} (d_j - d_i)))  (Gu-Eisenstat)
-__global__ void k_zhat(const double *d, const double *z, int k, double rho, const int *org, const double *tau,
-                       double *zh) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= k) return;
-  // (lam_i - d_i) first, then the ratios (lam_j - d_i)/(d_j - d_i), each of moderate size
-  double p = -((d[i] - d[org[i]]) - tau[i]);
-  for (int j = 0; j < k; ++j) {
-    if (j == i) continue;
-    const double lmd = -((d[i] - d[org[j]]) - tau[j]);  // lam_j - d_i
-    p *= lmd / (d[j] - d[i]);
-  }
-  p /= rho;
-  const double v = sqrt(fabs(p));
-  zh[i] = (z[i] >= 0.0) ? v : -v;
-}
-
-// U[j][i] = zhat_i / (d_i - lam_j), rows normalised afterwards.
-__global__ void k_form_u(const double *d, const double *zh, int k, const int *org, const double *tau, double *U) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= static_cast<int64_t>(k) * k) return;
-  const int j = static_cast<int>(e / k), i = static_cast<int>(e - static_cast<int64_t>(j) * k);
-  U[e] = zh[i] / ((d[i] - d[org[j]]) - tau[j]);
-}
-
-__global__ void k_normalise_rows(double *U, int k, int64_t ld, int ncols) {
-  __shared__ double red[256];
-  const int j = blockIdx.x;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < ncols; i += blockDim.x) s += U[j * ld + i] * U[j * ld + i];
-  red[threadIdx.x] = s;
+  if (!ok && lane == 0) *bad = 1;
   __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+  for (int r = 0; r < n; ++r) {
+    const double v = d[r];
+    int rank = 0;
+    for (int i = 0; i < n; ++i) rank += (d[i] < v || (d[i] == v && i < r)) ? 1 : 0;
+    if (lane == 0) L.w[L.lo + rank] = v;
+    if (lane < n) L.Z[static_cast<int64_t>(L.lo + rank) * L.n + L.lo + lane] = Zs[r][lane];
+  }
+}
+
+// z = [last component of the first half's rows; first component of the second half's].
+__global__ void k_dc_z(const DcMerge *merges, double *z) {
+  const DcMerge M = merges[blockIdx.y];
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= M.hi - M.lo) return;
+  const int c = (M.lo + i < M.m) ? M.m - 1 : M.m;
+  z[M.off + i] = M.Zin[static_cast<int64_t>(M.lo + i) * M.n + c];
+}
+
+// The deflating rotations in order, one column per thread: row_p <- c row_p - s row_q,
+// row_q <- s row_p + c row_q.  Consecutive rotations mostly chain (p is the previous q), so the
+// running row stays in a register and the q rows are loaded ahead, 8 rotations at a time.
+__global__ __launch_bounds__(64) void k_dc_rot(const DcMerge *merges, const DcRot *rots) {
+  const DcMerge M = merges[blockIdx.y];
+  const int col = M.lo + blockIdx.x * 64 + threadIdx.x;
+  if (M.nrot == 0 || col >= M.hi) return;
+  const int half = col < M.m ? 1 : 2;
+  double *zc = M.Zin + col;
+  const int64_t ld = M.n;
+  const DcRot *rt = rots + M.rot;
+  int held = -1;  // row whose value `carry` is, not yet stored
+  double carry = 0.0;
+  constexpr int B = 8;
+  for (int r0 = 0; r0 < M.nrot; r0 += B) {
+    double qv[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      qv[b] = 0.0;
+      // a row is q of at most one rotation, and p only after that: no store in between changes it
+      if (r0 + b < M.nrot && (rt[r0 + b].qf & half)) qv[b] = zc[rt[r0 + b].q * ld];
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      if (r0 + b >= M.nrot) break;
+      const DcRot R = rt[r0 + b];
+      double a;
+      if (R.p == held) {
+        a = carry;
+      } else {
+        if (held >= 0) zc[held * ld] = carry;
+        a = (R.pf & half) ? zc[R.p * ld] : 0.0;
+      }
+      zc[R.p * ld] = R.c * a - R.s * qv[b];
+      carry = R.s * a + R.c * qv[b];
+      held = R.q;
+    }
+  }
+  if (held >= 0) zc[held * ld] = carry;
+}
+
+__global__ __launch_bounds__(kDcThreads) void k_dc_secular(const DcMerge *merges, DcRows rw) {
+  const DcMerge M = merges[blockIdx.y];
+  const int j = blockIdx.x * (kDcThreads / 64) + (threadIdx.x >> 6);
+  if (j >= M.k) return;
+  int org;
+  double tau;
+  secular_root(rw.pole + M.off, rw.z + M.off, M.k, M.rho, j, WaveLanes(), org, tau);
+  if ((threadIdx.x & 63) == 0) {
+    rw.org[M.off + j] = org;
+    rw.tau[M.off + j] = tau;
+  }
+}
+
+// zhat_i = sign(z_i) sqrt(prod_j (lam_j - d_i) / (rho prod_{j != i} (d_j - d_i)))  (Gu-Eisenstat),
+// a wave per i; the ratios (lam_j - d_i) / (d_j - d_i) are of moderate size in any order.
+__global__ __launch_bounds__(kDcThreads) void k_dc_zhat(const DcMerge *merges, DcRows rw) {
+  const DcMerge M = merges[blockIdx.y];
+  const int i = blockIdx.x * (kDcThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (i >= M.k) return;
+  const double *d = rw.pole + M.off, *tau = rw.tau + M.off;
+  const int *org = rw.org + M.off;
+  const double di = d[i];
+  double p = 1.0;
+  for (int j = lane; j < M.k; j += 64) {
+    const double lmd = -((di - d[org[j]]) - tau[j]);  // lam_j - d_i
+    p *= (j == i) ? lmd : lmd / (d[j] - di);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) p *= __shfl_xor(p, off, 64);
+  if (lane == 0) {
+    const double v = sqrt(fabs(p / M.rho));
+    rw.zh[M.off + i] = (rw.z[M.off + i] >= 0.0) ? v : -v;
+  }
+}
+
+// A wave per block row.  Row j < k: eigenvector j of the update, U[j][ucol(i)] = zhat_i / (d_i - lam_j)
+// normalised, its eigenvalue and its place among the block's values (the roots and the deflated
+// values are both ascending, so a binary search of the other list gives it).  Row k + t: deflated
+// entry t, copied to its place, zero on the half its row is not supported on.
+__global__ __launch_bounds__(kDcThreads) void k_dc_rows(const DcMerge *merges, DcRows rw) {
+  const DcMerge M = merges[blockIdx.y];
+  const int row = blockIdx.x * (kDcThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nb = M.hi - M.lo, k = M.k;
+  if (row >= nb) return;
+  const double *d = rw.pole + M.off, *tau = rw.tau + M.off, *zh = rw.zh + M.off, *dval = rw.dval + M.off;
+  const int *org = rw.org + M.off;
+  if (row < k) {
+    const double dorg = d[org[row]], t = tau[row];
+    double s = 0.0;
+    for (int i = lane; i < k; i += 64) {
+      const double u = zh[i] / ((d[i] - dorg) - t);
+      s += u * u;
+    }
+    s = WaveLanes().sum(s);
+    const double inv = 1.0 / sqrt(s);
+    double *U = M.U + static_cast<int64_t>(M.lo + row) * M.n + M.lo;
+    for (int i = lane; i < k; i += 64) U[rw.ucol[M.off + i]] = zh[i] / ((d[i] - dorg) - t) * inv;
+    if (lane == 0) {
+      const double lam = dorg + t;
+      int a = 0, b = nb - k;  // deflated values <= lam
+      while (a < b) {
+        const int c = (a + b) >> 1;
+        if (dval[c] <= lam) a = c + 1;
+        else b = c;
+      }
+      rw.rank[M.off + row] = row + a;
+      M.w[M.lo + row + a] = lam;
+    }
+    return;
+  }
+  const int t = row - k;
+  const double v = dval[t];
+  int a = 0, b = k;  // roots < v
+  while (a < b) {
+    const int c = (a + b) >> 1;
+    if (d[org[c]] + tau[c] < v) a = c + 1;
+    else b = c;
+  }
+  const int flag = rw.dflag[M.off + t];
+  const double *src = M.Zin + static_cast<int64_t>(rw.dsrc[M.off + t]) * M.n;
+  double *dst = M.Zout + static_cast<int64_t>(M.lo + t + a) * M.n;
+  for (int c = M.lo + lane; c < M.hi; c += 64) dst[c] = (flag & (c < M.m ? 1 : 2)) ? src[c] : 0.0;
+  if (lane == 0) M.w[M.lo + t + a] = v;
+}
+
+// G row q: the child row of U's column q, on the columns of the half or halves it is supported on.
+__global__ __launch_bounds__(kDcThreads) void k_dc_gather(const DcMerge *merges, DcRows rw) {
+  const DcMerge M = merges[blockIdx.y];
+  const int q = blockIdx.x * (kDcThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (q >= M.k) return;
+  const int c0 = q < M.k12 ? M.lo : M.m, c1 = q >= M.k1 ? M.hi : M.m;
+  const double *src = M.Zin + static_cast<int64_t>(rw.src[M.off + q]) * M.n;
+  double *dst = M.G + static_cast<int64_t>(M.lo + q) * M.n;
+  for (int c = c0 + lane; c < c1; c += 64) dst[c] = src[c];
+}
+
+// New rows = U G on each half's columns: the first half's need U's columns [0, k12) only, the second
+// half's [k1, k).  blockIdx.y = 2 merge + half, blockIdx.x a 64 x 64 tile; a root's row goes to its
+// place in the block (rank).  FP64 MFMA as in k_dgemm (same permuted-k LDS rows), but with 64 x 64
+// tiles: a depth's products are a few hundred rows wide, and 128 x 128 tiles leave most of the
+// compute units idle.
+constexpr int kTB = 64, kTK = 16, kTS = 18;
+__global__ __launch_bounds__(256) void k_dc_gemm(const DcMerge *merges, const int *rank) {
+  __shared__ __attribute__((aligned(16))) double As[2][kTB][kTS];
+  __shared__ __attribute__((aligned(16))) double Bs[2][kTB][kTS];
+  const DcMerge M = merges[blockIdx.y >> 1];
+  const int half = blockIdx.y & 1;
+  const int cbeg = half ? M.m : M.lo, cend = half ? M.hi : M.m;
+  const int kbeg = half ? M.k1 : 0, kend = half ? M.k : M.k12;
+  const int nt = (cend - cbeg + kTB - 1) / kTB, mt = (M.k + kTB - 1) / kTB;
+  if (static_cast<int>(blockIdx.x) >= nt * mt) return;
+  const int tm = blockIdx.x / nt, tn = blockIdx.x - tm * nt;
+  const int r0 = tm * kTB, c0 = cbeg + tn * kTB;
+  const int64_t ld = M.n;
+  const double *U = M.U + static_cast<int64_t>(M.lo) * ld + M.lo;
+  const double *G = M.G + static_cast<int64_t>(M.lo) * ld;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  // U slab: k = tid % 16 of rows tid / 16 + 16 q;  G slab: column tid % 64, k = (tid / 64) * 4 + q
+  double ua[4], gb[4];
+  const int uk = tid & 15, ur = tid >> 4, ukp = 4 * (uk & 3) + (uk >> 2);
+  const int gc = tid & 63, gk = (tid >> 6) * 4;
+  auto load = [&](int kb) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      ua[q] = (kb + uk < kend && r0 + ur + 16 * q < M.k) ? U[(r0 + ur + 16 * q) * ld + kb + uk] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      gb[q] = (kb + gk + q < kend && c0 + gc < cend) ? G[(kb + gk + q) * ld + c0 + gc] : 0.0;
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) As[buf][ur + 16 * q][ukp] = ua[q];
+    // k = gk + q, permuted 4 (k % 4) + k / 4 = 4 q + gk / 4
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Bs[buf][gc][4 * q + (gk >> 2)] = gb[q];
+  };
+  v4d acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int nk = kend > kbeg ? (kend - kbeg + kTK - 1) / kTK : 0;
+  if (nk > 0) {
+    load(kbeg);
+    store(0);
+  }
+  __syncthreads();
+  const int r = lane & 15, q4 = (lane >> 4) * 4;
+  for (int kt = 0; kt < nk; ++kt) {
+    const int buf = kt & 1;
+    if (kt + 1 < nk) load(kbeg + (kt + 1) * kTK);
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      v2d av[2], bv[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        av[i] = *reinterpret_cast<const v2d *>(&As[buf][wm + i * 16 + r][q4 + 2 * hf]);
+        bv[i] = *reinterpret_cast<const v2d *>(&Bs[buf][wn + i * 16 + r][q4 + 2 * hf]);
+      }
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][s2], bv[j][s2], acc[i][j], 0, 0, 0);
+    }
+    if (kt + 1 < nk) store(buf ^ 1);
     __syncthreads();
   }
-  const double inv = 1.0 / sqrt(red[0]);
-  for (int i = threadIdx.x; i < ncols; i += blockDim.x) U[j * ld + i] *= inv;
-  (void)k;
-}
-
-// Sequential list of plane rotations on row pairs (p, q): row_p <- c row_p - s row_q,
-// row_q <- s row_p + c row_q; every lane owns one column.
-__global__ void k_row_rotations(double *Z, int64_t ld, int col0, int ncols, const int *pq, const double *cs, int nrot) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= ncols) return;
-  double *zc = Z + col0 + col;
-  for (int r = 0; r < nrot; ++r) {
-    const int p = pq[2 * r], q = pq[2 * r + 1];
-    const double c = cs[2 * r], s = cs[2 * r + 1];
-    const double a = zc[static_cast<int64_t>(p) * ld], b = zc[static_cast<int64_t>(q) * ld];
-    zc[static_cast<int64_t>(p) * ld] = c * a - s * b;
-    zc[static_cast<int64_t>(q) * ld] = s * a + c * b;
-  }
-}
-
-// dst[r][c] = src[rows[r]][col0 + c]
-__global__ void k_gather_block(const double *src, int64_t lds, const int *rows, int col0, int nrows, int ncols,
-                               double *dst, int64_t ldd) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= static_cast<int64_t>(nrows) * ncols) return;
-  const int r = static_cast<int>(e / ncols), c = static_cast<int>(e - static_cast<int64_t>(r) * ncols);
-  dst[r * ldd + c] = src[static_cast<int64_t>(rows[r]) * lds + col0 + c];
-}
-
-// dst[rows[r]][col0 + c] = src[r][c]
-__global__ void k_scatter_block(const double *src, int64_t lds, const int *rows, int col0, int nrows, int ncols,
-                                double *dst, int64_t ldd) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= static_cast<int64_t>(nrows) * ncols) return;
-  const int r = static_cast<int>(e / ncols), c = static_cast<int>(e - static_cast<int64_t>(r) * ncols);
-  dst[static_cast<int64_t>(rows[r]) * ldd + col0 + c] = src[r * lds + c];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = r0 + wm + i * 16 + (lane >> 4) + 4 * e;
+      if (row >= M.k) continue;
+      double *out = M.Zout + static_cast<int64_t>(M.lo + rank[M.off + row]) * ld;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int c = c0 + wn + j * 16 + (lane & 15);
+        if (c < cend) out[c] = acc[i][j][e];
+      }
+    }
 }
 
 inline unsigned nblk(int64_t n, int t) { return static_cast<unsigned>((n + t - 1) / t); }
 
-struct DcWork {
-  dacp_ctx ctx;
-  int n;
-  double *Z;  // n x n device, rows = eigenvectors
-  std::vector<double> w;  // eigenvalues of solved blocks (ascending within each block)
-  // device scratch, grown on demand
-  DevBuf dd, dz, dtau, dzh, dU, dA, dB, dcs;
-  DevBuf dorg, drows, dpq;
+// A node of the tree: the block [lo, hi) of one matrix at a depth.
+struct Node {
+  int job, lo, hi;
 };
 
-dacp_status ensure(dacp_ctx ctx, DevBuf &b, size_t bytes) {
-  if (b.bytes >= bytes) return DACP_OK;
-  DACP_HIP(ctx, b.alloc(bytes));
-  return DACP_OK;
+// Appends the nodes of [lo, hi) to the lists of their depths (halves of n / 2 and n - n / 2 rows
+// until a block has at most kLeaf).
+void plan_nodes(std::vector<std::vector<Node>> &inner, std::vector<std::vector<Node>> &leaf, int job, int lo, int hi,
+                size_t depth) {
+  if (inner.size() <= depth) {
+    inner.resize(depth + 1);
+    leaf.resize(depth + 1);
+  }
+  if (hi - lo <= kLeaf) {
+    leaf[depth].push_back({job, lo, hi});
+    return;
+  }
+  inner[depth].push_back({job, lo, hi});
+  const int m = lo + (hi - lo) / 2;
+  plan_nodes(inner, leaf, job, lo, m, depth + 1);
+  plan_nodes(inner, leaf, job, m, hi, depth + 1);
 }
 
-dacp_status solve(DcWork &W, std::vector<double> &d, std::vector<double> &e, int lo, int hi);
-
-// Merge the solved halves [lo, m) and [m, hi), torn with rho = |beta|.
-dacp_status merge(DcWork &W, int lo, int m, int hi, double beta) {
-  dacp_ctx ctx = W.ctx;
-  hipStream_t st = ctx->stream;
-  const int n = hi - lo;
-  const int n1 = m - lo;
-  {
-    // every scratch buffer of this merge sized for the whole block before any kernel uses it
-    const size_t nn = static_cast<size_t>(n) * n;
-    dacp_status s0 = DACP_OK;
-    if ((s0 = ensure(ctx, W.dA, nn * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dB, nn * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dU, nn * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dd, n * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dz, n * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dtau, n * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dzh, n * sizeof(double)))) return s0;
-    if ((s0 = ensure(ctx, W.dorg, n * sizeof(int)))) return s0;
-    if ((s0 = ensure(ctx, W.drows, n * sizeof(int)))) return s0;
-    if ((s0 = ensure(ctx, W.dpq, 2 * n * sizeof(int)))) return s0;
-    if ((s0 = ensure(ctx, W.dcs, 2 * n * sizeof(double)))) return s0;
-  }
-  const double sgn = beta >= 0.0 ? 1.0 : -1.0;
-  double rho = std::fabs(beta);
-  // z = [sgn * last row of Q1; first row of Q2]: component m-1 of the first half's
-  // eigenvectors, component m of the second half's.
-  std::vector<double> z(n);
-  {
-    // both strided columns gathered into the merge's own z buffer, then one copy to the host
-    std::vector<double> col(n);
-    DACP_HIP(ctx, launch_copy_cols(W.Z + static_cast<int64_t>(lo) * W.n + (m - 1), W.n, W.dz.as<double>(), 1, n1, 1,
-                                   st));
-    DACP_HIP(ctx, launch_copy_cols(W.Z + static_cast<int64_t>(m) * W.n + m, W.n, W.dz.as<double>() + n1, 1, n - n1, 1,
-                                   st));
-    DACP_TRY(to_host(ctx, col.data(), W.dz.p, static_cast<size_t>(n) * sizeof(double)));
-    for (int i = 0; i < n1; ++i) z[i] = sgn * col[i];
-    for (int i = n1; i < n; ++i) z[i] = col[i];
-  }
-  std::vector<double> dv(W.w.begin() + lo, W.w.begin() + hi);
-  // normalise z (rho absorbs |z|^2)
-  double zn = 0.0;
-  for (double v : z) zn += v * v;
-  zn = std::sqrt(zn);
-  for (double &v : z) v /= zn;
-  rho *= zn * zn;
-  // sort, deflate and list the secular problem (host bookkeeping, host_rules.cpp)
-  rules::DcDeflation df = rules::dc_deflate(dv, z, rho, lo);
-  const std::vector<double> &ds = df.ds, &zs = df.zs;
-  const std::vector<int> &rowid = df.rowid, &rot_pq = df.rot_pq, &nd = df.nd;
-  const std::vector<double> &rot_cs = df.rot_cs;
-  const std::vector<char> &defl = df.defl;
-  if (!rot_pq.empty()) {
-    const int nr = static_cast<int>(rot_cs.size() / 2);
-    DACP_TRY(to_device(ctx, W.dpq.p, rot_pq.data(), rot_pq.size() * sizeof(int)));
-    DACP_TRY(to_device(ctx, W.dcs.p, rot_cs.data(), rot_cs.size() * sizeof(double)));
-    hipLaunchKernelGGL(k_row_rotations, dim3(nblk(n, 64)), dim3(64), 0, st, W.Z, (int64_t)W.n, lo, n,
-                       W.dpq.as<int>(), W.dcs.as<double>(), nr);
-    DACP_HIP(ctx, hipGetLastError());
-  }
-  // non-deflated problem
-  const int k = static_cast<int>(nd.size());
-  // final eigenvalue list: (value, kind, index) kind 0 = deflated (rowid), 1 = secular root (nd index)
-  std::vector<rules::DcEntry> ents;
-  for (int j = 0; j < n; ++j)
-    if (defl[j]) ents.push_back({ds[j], 0, rowid[j]});
-  if (k > 0) {
-    std::vector<double> dk(k), zk(k);
-    std::vector<int> rk(k);
-    for (int q = 0; q < k; ++q) {
-      dk[q] = ds[nd[q]];
-      zk[q] = zs[nd[q]];
-      rk[q] = rowid[nd[q]];
-    }
-    const size_t kk = static_cast<size_t>(k) * k;
-    DACP_TRY(to_device(ctx, W.dd.p, dk.data(), k * sizeof(double)));
-    DACP_TRY(to_device(ctx, W.dz.p, zk.data(), k * sizeof(double)));
-    hipLaunchKernelGGL(k_secular, dim3(nblk(k, 64)), dim3(64), 0, st, W.dd.as<double>(), W.dz.as<double>(), k, rho,
-                       W.dorg.as<int>(), W.dtau.as<double>());
-    hipLaunchKernelGGL(k_zhat, dim3(nblk(k, 64)), dim3(64), 0, st, W.dd.as<double>(), W.dz.as<double>(), k, rho,
-                       W.dorg.as<int>(), W.dtau.as<double>(), W.dzh.as<double>());
-    hipLaunchKernelGGL(k_form_u, dim3(nblk(static_cast<int64_t>(kk), 256)), dim3(256), 0, st, W.dd.as<double>(),
-                       W.dzh.as<double>(), k, W.dorg.as<int>(), W.dtau.as<double>(), W.dU.as<double>());
-    hipLaunchKernelGGL(k_normalise_rows, dim3(k), dim3(256), 0, st, W.dU.as<double>(), k, (int64_t)k, k);
-    // old rows of the non-deflated entries (block columns [lo, hi))
-    DACP_TRY(to_device(ctx, W.drows.p, rk.data(), k * sizeof(int)));
-    hipLaunchKernelGGL(k_gather_block, dim3(nblk(static_cast<int64_t>(k) * n, 256)), dim3(256), 0, st, W.Z,
-                       (int64_t)W.n, W.drows.as<int>(), lo, k, n, W.dA.as<double>(), (int64_t)n);
-    // new rows = U * old rows
-    DACP_HIP(ctx, launch_dgemm(0, 0, k, n, k, 1.0, W.dU.as<double>(), k, W.dA.as<double>(), n, 0.0, W.dB.as<double>(),
-                               n, 0, st));
-    DACP_HIP(ctx, hipGetLastError());
-    std::vector<int> org(k);
-    std::vector<double> tau(k);
-    DACP_TRY(to_host(ctx, org.data(), W.dorg.p, k * sizeof(int)));
-    DACP_TRY(to_host(ctx, tau.data(), W.dtau.p, k * sizeof(double)));
-    DACP_HIP(ctx, hipStreamSynchronize(st));
-    for (int q = 0; q < k; ++q) {
-      const double v = dk[org[q]] + tau[q];
-      if (!std::isfinite(v)) return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite root");
-      ents.push_back({v, 1, q});
-    }
-  }
-  // place rows: deflated rows are copied (they may currently sit anywhere in the block), roots
-  // come from dB; stage everything through dA (n x n of the block) then copy to rows lo..hi
-  const rules::DcPlacement pl = rules::dc_place(std::move(ents), k);
-  const std::vector<int> &src_defl = pl.src_defl, &dst_defl = pl.dst_defl;
-  for (int t = 0; t < n; ++t) W.w[lo + t] = pl.w[t];
-  // deflated: gather Z rows -> dA rows dst
-  DevBuf tmp_idx;
-  if (!src_defl.empty()) {
-    std::vector<int> idx(src_defl);
-    idx.insert(idx.end(), dst_defl.begin(), dst_defl.end());
-    DACP_HIP(ctx, tmp_idx.alloc(idx.size() * sizeof(int)));
-    DACP_TRY(to_device(ctx, tmp_idx.p, idx.data(), idx.size() * sizeof(int)));
-    const int nd2 = static_cast<int>(src_defl.size());
-    // stage: gather into contiguous rows, then scatter into dA at dst rows
-    DevBuf stage;
-    DACP_HIP(ctx, stage.alloc(static_cast<size_t>(nd2) * n * sizeof(double)));
-    hipLaunchKernelGGL(k_gather_block, dim3(nblk(static_cast<int64_t>(nd2) * n, 256)), dim3(256), 0, st, W.Z,
-                       (int64_t)W.n, tmp_idx.as<int>(), lo, nd2, n, stage.as<double>(), (int64_t)n);
-    hipLaunchKernelGGL(k_scatter_block, dim3(nblk(static_cast<int64_t>(nd2) * n, 256)), dim3(256), 0, st,
-                       stage.as<double>(), (int64_t)n, tmp_idx.as<int>() + nd2, 0, nd2, n, W.dA.as<double>(),
-                       (int64_t)n);
-    DACP_HIP(ctx, hipGetLastError());
-    DACP_HIP(ctx, hipStreamSynchronize(st));
-  }
-  if (k > 0) {
-    // dB row q (root q) -> dA row dst_of_root[q]
-    DACP_TRY(to_device(ctx, W.drows.p, pl.dst_of_root.data(), k * sizeof(int)));
-    hipLaunchKernelGGL(k_scatter_block, dim3(nblk(static_cast<int64_t>(k) * n, 256)), dim3(256), 0, st,
-                       W.dB.as<double>(), (int64_t)n, W.drows.as<int>(), 0, k, n, W.dA.as<double>(), (int64_t)n);
-    DACP_HIP(ctx, hipGetLastError());
-  }
-  // dA (n x n) -> Z rows lo..hi, columns lo..hi
-  DACP_HIP(ctx, launch_copy_cols(W.dA.as<double>(), n, W.Z + static_cast<int64_t>(lo) * W.n + lo, W.n, n, n, st));
-  DACP_HIP(ctx, hipStreamSynchronize(st));
-  return DACP_OK;
-}
-
-dacp_status solve(DcWork &W, std::vector<double> &d, std::vector<double> &e, int lo, int hi) {
-  const int n = hi - lo;
-  if (n <= kLeaf) {
-    std::vector<double> w(n), Zh(static_cast<size_t>(n) * n);
-    if (!host_tridiag_eig(d.data() + lo, e.data() + lo, n, w.data(), Zh.data()))
-      return set_err(W.ctx, DACP_E_CONVERGENCE, "divide and conquer: leaf QR did not converge");
-    std::vector<double> rows(static_cast<size_t>(n) * n);
-    for (int j = 0; j < n; ++j)
-      for (int i = 0; i < n; ++i) rows[static_cast<size_t>(j) * n + i] = Zh[static_cast<size_t>(i) * n + j];
-    for (int j = 0; j < n; ++j) W.w[lo + j] = w[j];
-    DACP_TRY(to_device_2d(W.ctx, W.Z + static_cast<int64_t>(lo) * W.n + lo, W.n, rows.data(), n, n));
-    DACP_HIP(W.ctx, hipStreamSynchronize(W.ctx->stream));  // `rows` goes out of scope
-    return DACP_OK;
-  }
-  const int m = lo + n / 2;
-  const double beta = e[m - 1];
-  // tear: T = diag(T1 - |beta| e e^T, T2 - |beta| e e^T) + |beta| v v^T, v = (sign(beta) e_last; e_first)
-  d[m - 1] -= std::fabs(beta);
-  d[m] -= std::fabs(beta);
-  dacp_status st = solve(W, d, e, lo, m);
-  if (st) return st;
-  st = solve(W, d, e, m, hi);
-  if (st) return st;
-  if (beta == 0.0) {
-    // already split: merge the two sorted halves without a rank-one update
-    std::vector<int> order(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::vector<double> wv(W.w.begin() + lo, W.w.begin() + hi);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return wv[a] < wv[b]; });
-    DevBuf idx, stage;
-    std::vector<int> src(n);
-    for (int t = 0; t < n; ++t) {
-      src[t] = lo + order[t];
-      W.w[lo + t] = wv[order[t]];
-    }
-    DACP_HIP(W.ctx, idx.alloc(n * sizeof(int)));
-    DACP_HIP(W.ctx, stage.alloc(static_cast<size_t>(n) * n * sizeof(double)));
-    DACP_TRY(to_device(W.ctx, idx.p, src.data(), n * sizeof(int)));
-    hipLaunchKernelGGL(k_gather_block, dim3(nblk(static_cast<int64_t>(n) * n, 256)), dim3(256), 0, W.ctx->stream,
-                       W.Z, (int64_t)W.n, idx.as<int>(), lo, n, n, stage.as<double>(), (int64_t)n);
-    DACP_HIP(W.ctx, launch_copy_cols(stage.as<double>(), n, W.Z + static_cast<int64_t>(lo) * W.n + lo, W.n, n, n,
-                                     W.ctx->stream));
-    DACP_HIP(W.ctx, hipStreamSynchronize(W.ctx->stream));
-    return DACP_OK;
-  }
-  return merge(W, lo, m, hi, beta);
-}
+size_t align8(size_t x) { return (x + 7) / 8 * 8; }
 
 }  // namespace
 
-// Eigen-decomposition of the symmetric tridiagonal (d, e) (e[i] couples i and i+1).
-// w (host) ascending; Z (device n x n, ld n): row j = eigenvector j.  Z is zero-filled
-// here (off-block entries of the merged halves must read as zero).
-dacp_status dc_tridiag(dacp_ctx ctx, int n, const double *d_in, const double *e_in, double *w, double *Z) {
-  for (int i = 0; i < n; ++i)
-    if (!std::isfinite(d_in[i]) || (i + 1 < n && !std::isfinite(e_in[i])))
-      return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite tridiagonal entry");
-  DACP_HIP(ctx, hipMemsetAsync(Z, 0, static_cast<size_t>(n) * n * sizeof(double), ctx->stream));
-  DcWork W;
-  W.ctx = ctx;
-  W.n = n;
-  W.Z = Z;
-  W.w.assign(n, 0.0);
-  std::vector<double> d(d_in, d_in + n), e(n, 0.0);
-  for (int i = 0; i + 1 < n; ++i) e[i] = e_in[i];
-  dacp_status st = solve(W, d, e, 0, n);
-  if (st) return st;
-  DACP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  std::copy(W.w.begin(), W.w.end(), w);
+size_t dc_work_doubles(int n) { return 3 * static_cast<size_t>(n) * n; }
+
+dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
+  hipStream_t st = ctx->stream;
+  std::vector<std::vector<Node>> inner, leaf;
+  std::vector<size_t> woff(jobs.size() + 1, 0);
+  for (size_t i = 0; i < jobs.size(); ++i) {
+    woff[i + 1] = woff[i] + static_cast<size_t>(jobs[i].n);
+    if (jobs[i].n > 0) plan_nodes(inner, leaf, static_cast<int>(i), 0, jobs[i].n, 0);
+  }
+  const size_t wtot = woff.back();
+  if (wtot == 0) return DACP_OK;
+  auto buffer = [&](int job, size_t depth) { return (depth & 1) ? jobs[job].work : jobs[job].Z; };
+
+  size_t max_merges = 0, n_leaves = 0;
+  for (const auto &v : inner) max_merges = std::max(max_merges, v.size());
+  for (const auto &v : leaf) n_leaves += v.size();
+  // device: eigenvalues and update vectors (copied to the host together, with the leaves' flag),
+  // the depth's packed tables (one upload), and the kernels' own per-row arrays
+  DevBuf wz, table, rows, dleaf;
+  DACP_HIP(ctx, wz.alloc((2 * wtot + 1) * sizeof(double)));
+  double *wdev = wz.as<double>(), *zdev = wdev + wtot;
+  int *bad = reinterpret_cast<int *>(zdev + wtot);
+  const size_t table_bytes = align8(max_merges * sizeof(DcMerge)) + align8(wtot * sizeof(DcRot)) +
+                             3 * wtot * sizeof(double) + 4 * align8(wtot * sizeof(int));
+  DACP_HIP(ctx, table.alloc(table_bytes));
+  DACP_HIP(ctx, rows.alloc(2 * wtot * sizeof(double) + 2 * align8(wtot * sizeof(int))));
+  DACP_HIP(ctx, dleaf.alloc(n_leaves * sizeof(DcLeaf)));
+
+  // the diagonals come to the host once: the tears' weights and a check that they are finite
+  std::vector<double> eh(wtot, 0.0), dh(wtot, 0.0);
+  for (size_t i = 0; i < jobs.size(); ++i) {
+    if (jobs[i].n <= 0) continue;
+    DACP_HIP(ctx, hipMemcpyAsync(dh.data() + woff[i], jobs[i].d, jobs[i].n * sizeof(double), hipMemcpyDeviceToHost, st));
+    if (jobs[i].n > 1)
+      DACP_HIP(ctx, hipMemcpyAsync(eh.data() + woff[i], jobs[i].e, (jobs[i].n - 1) * sizeof(double),
+                                   hipMemcpyDeviceToHost, st));
+  }
+  {
+    std::vector<DcLeaf> ls;
+    for (size_t t = 0; t < leaf.size(); ++t)
+      for (const Node &nd : leaf[t])
+        ls.push_back({jobs[nd.job].d, jobs[nd.job].e, buffer(nd.job, t), wdev + woff[nd.job], jobs[nd.job].n, nd.lo, nd.hi});
+    const int zero = 0;
+    DACP_HIP(ctx, hipMemcpyAsync(bad, &zero, sizeof(int), hipMemcpyHostToDevice, st));
+    DACP_TRY(to_device(ctx, dleaf.p, ls.data(), ls.size() * sizeof(DcLeaf)));
+    for (size_t i = 0; i < wtot; ++i)
+      if (!std::isfinite(dh[i]) || !std::isfinite(eh[i]))
+        return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite tridiagonal entry");
+    hipLaunchKernelGGL(k_dc_leaf, dim3(static_cast<unsigned>(ls.size())), dim3(64), 0, st, dleaf.as<DcLeaf>(), bad);
+    DACP_HIP(ctx, hipGetLastError());
+  }
+
+  // the merges' blocks and buffers, every depth in one upload (the update vectors' kernel reads them)
+  std::vector<DcMerge> geo;
+  std::vector<size_t> geo_at(inner.size());
+  for (size_t depth = 0; depth < inner.size(); ++depth) {
+    geo_at[depth] = geo.size();
+    int off = 0;
+    for (const Node &nd : inner[depth]) {
+      const DcJob &jb = jobs[nd.job];
+      const size_t nn = static_cast<size_t>(jb.n) * jb.n;
+      DcMerge M;
+      std::memset(&M, 0, sizeof(M));
+      M.Zin = buffer(nd.job, depth + 1);
+      M.Zout = buffer(nd.job, depth);
+      M.U = jb.work + nn;
+      M.G = jb.work + 2 * nn;
+      M.w = wdev + woff[nd.job];
+      M.n = jb.n;
+      M.lo = nd.lo;
+      M.hi = nd.hi;
+      M.m = nd.lo + (nd.hi - nd.lo) / 2;
+      M.off = off;
+      off += nd.hi - nd.lo;
+      geo.push_back(M);
+    }
+  }
+  DevBuf dgeo;
+  DACP_HIP(ctx, dgeo.alloc(geo.size() * sizeof(DcMerge)));
+  DACP_TRY(to_device(ctx, dgeo.p, geo.data(), geo.size() * sizeof(DcMerge)));
+
+  std::vector<double> host_wz(2 * wtot + 1);
+  std::vector<unsigned char> blob(table_bytes);
+  std::vector<DcMerge> ms;
+  for (size_t depth = inner.size(); depth-- > 0;) {
+    const std::vector<Node> &nodes = inner[depth];
+    if (nodes.empty()) continue;
+    ms.assign(geo.begin() + geo_at[depth], geo.begin() + geo_at[depth] + nodes.size());
+    int off = 0, max_n = 0;
+    for (const DcMerge &M : ms) {
+      off += M.hi - M.lo;
+      max_n = std::max(max_n, M.hi - M.lo);
+    }
+    const unsigned nm = static_cast<unsigned>(ms.size());
+    hipLaunchKernelGGL(k_dc_z, dim3(nblk(max_n, 256), nm), dim3(256), 0, st, dgeo.as<DcMerge>() + geo_at[depth], zdev);
+    DACP_HIP(ctx, hipGetLastError());
+    DACP_TRY(to_host(ctx, host_wz.data(), wdev, (2 * wtot + 1) * sizeof(double)));
+    int failed = 0;
+    std::memcpy(&failed, host_wz.data() + 2 * wtot, sizeof(int));
+    if (failed) return set_err(ctx, DACP_E_CONVERGENCE, "divide and conquer: leaf QR did not converge");
+
+    // deflation of every merge (host_rules.cpp), packed for one upload
+    size_t at = align8(nm * sizeof(DcMerge));
+    const size_t arr = static_cast<size_t>(off);
+    auto carve = [&](size_t bytes) {
+      const size_t p = at;
+      at += align8(bytes);
+      return p;
+    };
+    const size_t o_pole = carve(arr * sizeof(double)), o_z = carve(arr * sizeof(double)),
+                 o_dval = carve(arr * sizeof(double)), o_ucol = carve(arr * sizeof(int)),
+                 o_src = carve(arr * sizeof(int)), o_dsrc = carve(arr * sizeof(int)), o_dflag = carve(arr * sizeof(int)),
+                 o_rot = at;
+    double *pole = reinterpret_cast<double *>(blob.data() + o_pole), *zv = reinterpret_cast<double *>(blob.data() + o_z),
+           *dval = reinterpret_cast<double *>(blob.data() + o_dval);
+    int *ucol = reinterpret_cast<int *>(blob.data() + o_ucol), *src = reinterpret_cast<int *>(blob.data() + o_src),
+        *dsrc = reinterpret_cast<int *>(blob.data() + o_dsrc), *dflag = reinterpret_cast<int *>(blob.data() + o_dflag);
+    DcRot *rots = reinterpret_cast<DcRot *>(blob.data() + o_rot);
+    int nrot = 0, max_k = 0;
+    std::vector<int> flag, dorder;
+    for (size_t i = 0; i < nodes.size(); ++i) {
+      DcMerge &M = ms[i];
+      const int n = M.hi - M.lo, n1 = M.m - M.lo;
+      const double beta = eh[woff[nodes[i].job] + M.m - 1];
+      std::vector<double> z(host_wz.begin() + wtot + M.off, host_wz.begin() + wtot + M.off + n);
+      const double *wv = host_wz.data() + woff[nodes[i].job] + M.lo;
+      std::vector<double> dv(wv, wv + n);
+      // T = diag(T1, T2) torn + |beta| v v^T, v = (sign(beta) e_last; e_first); z normalised, rho
+      // absorbs |z|^2
+      double zn = 0.0;
+      for (int q = 0; q < n; ++q) {
+        if (q < n1 && beta < 0.0) z[q] = -z[q];
+        zn += z[q] * z[q];
+      }
+      if (!std::isfinite(zn) || !(zn > 0.0))
+        return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite update vector");
+      zn = std::sqrt(zn);
+      for (double &x : z) x /= zn;
+      M.rho = std::fabs(beta) * zn * zn;
+      const rules::DcDeflation df = rules::dc_deflate(dv, z, M.rho, M.lo);
+      // halves each row is supported on: its own, both once a rotation has mixed it
+      flag.assign(n, 0);
+      for (int q = 0; q < n; ++q) flag[q] = q < n1 ? 1 : 2;
+      M.rot = nrot;
+      M.nrot = static_cast<int>(df.rot_cs.size() / 2);
+      for (int q = 0; q < M.nrot; ++q) {
+        DcRot &R = rots[nrot++];
+        R.c = df.rot_cs[2 * q];
+        R.s = df.rot_cs[2 * q + 1];
+        R.p = df.rot_pq[2 * q];
+        R.q = df.rot_pq[2 * q + 1];
+        int &fp = flag[R.p - M.lo], &fq = flag[R.q - M.lo];
+        R.pf = fp;
+        R.qf = fq;
+        fp = fq = fp | fq;
+      }
+      M.k = static_cast<int>(df.nd.size());
+      max_k = std::max(max_k, M.k);
+      int cnt[4] = {0, 0, 0, 0};
+      for (int j : df.nd) ++cnt[flag[df.rowid[j] - M.lo]];
+      M.k1 = cnt[1];
+      M.k12 = cnt[1] + cnt[3];
+      int next[4] = {0, 0, cnt[1] + cnt[3], cnt[1]};  // next column of the rows on half 1 / half 2 / both
+      for (int q = 0; q < M.k; ++q) {
+        const int j = df.nd[q], row = df.rowid[j];
+        const int c = next[flag[row - M.lo]]++;
+        pole[M.off + q] = df.ds[j];
+        zv[M.off + q] = df.zs[j];
+        ucol[M.off + q] = c;
+        src[M.off + c] = row;
+      }
+      dorder.clear();
+      for (int j = 0; j < n; ++j)
+        if (df.defl[j]) dorder.push_back(j);
+      std::stable_sort(dorder.begin(), dorder.end(), [&](int a, int b) { return df.ds[a] < df.ds[b]; });
+      for (size_t t = 0; t < dorder.size(); ++t) {
+        dval[M.off + t] = df.ds[dorder[t]];
+        dsrc[M.off + t] = df.rowid[dorder[t]];
+        dflag[M.off + t] = flag[df.rowid[dorder[t]] - M.lo];
+      }
+    }
+    std::memcpy(blob.data(), ms.data(), nm * sizeof(DcMerge));
+    DACP_TRY(to_device(ctx, table.p, blob.data(), o_rot + nrot * sizeof(DcRot)));
+    const unsigned char *tb = table.as<unsigned char>();
+    const DcMerge *dm = table.as<DcMerge>();
+    DcRows rw;
+    rw.pole = reinterpret_cast<const double *>(tb + o_pole);
+    rw.z = reinterpret_cast<const double *>(tb + o_z);
+    rw.dval = reinterpret_cast<const double *>(tb + o_dval);
+    rw.ucol = reinterpret_cast<const int *>(tb + o_ucol);
+    rw.src = reinterpret_cast<const int *>(tb + o_src);
+    rw.dsrc = reinterpret_cast<const int *>(tb + o_dsrc);
+    rw.dflag = reinterpret_cast<const int *>(tb + o_dflag);
+    rw.tau = rows.as<double>();
+    rw.zh = rw.tau + wtot;
+    rw.org = reinterpret_cast<int *>(rw.zh + wtot);
+    rw.rank = rw.org + align8(wtot * sizeof(int)) / sizeof(int);
+    if (nrot > 0) {
+      hipLaunchKernelGGL(k_dc_rot, dim3(nblk(max_n, 64), nm), dim3(64), 0, st, dm,
+                         reinterpret_cast<const DcRot *>(tb + o_rot));
+      DACP_HIP(ctx, hipGetLastError());
+    }
+    const int per = kDcThreads / 64;
+    if (max_k > 0) {
+      hipLaunchKernelGGL(k_dc_secular, dim3(nblk(max_k, per), nm), dim3(kDcThreads), 0, st, dm, rw);
+      hipLaunchKernelGGL(k_dc_zhat, dim3(nblk(max_k, per), nm), dim3(kDcThreads), 0, st, dm, rw);
+      hipLaunchKernelGGL(k_dc_gather, dim3(nblk(max_k, per), nm), dim3(kDcThreads), 0, st, dm, rw);
+      DACP_HIP(ctx, hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_dc_rows, dim3(nblk(max_n, per), nm), dim3(kDcThreads), 0, st, dm, rw);
+    DACP_HIP(ctx, hipGetLastError());
+    if (max_k > 0) {
+      const unsigned tiles = nblk(max_k, kTB) * nblk((max_n + 1) / 2, kTB);
+      hipLaunchKernelGGL(k_dc_gemm, dim3(tiles, 2 * nm), dim3(256), 0, st, dm, rw.rank);
+      DACP_HIP(ctx, hipGetLastError());
+    }
+  }
+  DACP_TRY(to_host(ctx, host_wz.data(), wdev, (2 * wtot + 1) * sizeof(double)));
+  int failed = 0;
+  std::memcpy(&failed, host_wz.data() + 2 * wtot, sizeof(int));
+  if (failed) return set_err(ctx, DACP_E_CONVERGENCE, "divide and conquer: leaf QR did not converge");
+  for (size_t i = 0; i < wtot; ++i)
+    if (!std::isfinite(host_wz[i])) return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite root");
+  for (size_t i = 0; i < jobs.size(); ++i)
+    if (jobs[i].n > 0) std::copy_n(host_wz.begin() + woff[i], jobs[i].n, jobs[i].w);
   return DACP_OK;
 }
 

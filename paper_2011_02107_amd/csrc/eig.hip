@@ -542,17 +542,19 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
 
   if (Zrows && ctx->dc_min_n > 0 && n >= ctx->dc_min_n) {
     // Eigenvectors of T by divide and conquer, then rows of (Q Y)^T = Y^T Q^T = Zt * Qc.
-    DevBuf zt, qc;
+    DevBuf zt, qc, work;
     DACP_HIP(ctx, zt.alloc(static_cast<size_t>(n) * n * sizeof(double)));
     DACP_HIP(ctx, qc.alloc(static_cast<size_t>(n) * n * sizeof(double)));
+    DACP_HIP(ctx, work.alloc(dc_work_doubles(n) * sizeof(double)));
     DACP_HIP(ctx, hipMemcpyAsync(qc.p, Zrows, static_cast<size_t>(n) * n * sizeof(double), hipMemcpyDeviceToDevice, st));
-    DACP_HIP(ctx, hipStreamSynchronize(st));  // the Q-formation kernels read db and A
-    (void)hipFree(dv);
+    DACP_TRY(to_device(ctx, dd, d.data(), sizeof(double) * n));  // with the last 2 x 2 block's entries
+    DACP_TRY(to_device(ctx, de, e.data(), sizeof(double) * n));
+    const dacp_status drc = dc_tridiag_jobs(ctx, {{n, dd, de, zt.as<double>(), work.as<double>(), w}});
+    (void)hipFree(dv);  // the Q-formation kernels, which read db and A, are done
     (void)hipFree(dp);
     (void)hipFree(dd);
     (void)hipFree(de);
     (void)hipFree(db);
-    dacp_status drc = dc_tridiag(ctx, n, d.data(), e.data(), w, zt.as<double>());
     if (drc) return drc;
     const double t_dc = wall_ms();
     DACP_HIP(ctx, launch_dgemm(0, 0, n, n, n, 1.0, zt.as<double>(), n, qc.as<double>(), n, 0.0, Zrows, n, 0, st));

@@ -411,7 +411,16 @@ size_t batch_syev_noalloc_bytes(int count, const int *n);
 dacp_status batch_syev_noalloc(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
                                double *const *Zrows);
 bool host_tridiag_eig(const double *diag, const double *off, int n, double *w, double *Z);
-dacp_status dc_tridiag(dacp_ctx ctx, int n, const double *d, const double *e, double *w, double *Z);
+// Divide and conquer (dc.hip) of several symmetric tridiagonal matrices at once: d, e device (e[i]
+// couples i and i + 1), w host ascending, Z device n x n with row j = eigenvector j, work device
+// dc_work_doubles(n) doubles.  Waits for the context's stream.
+struct DcJob {
+  int n;
+  const double *d, *e;
+  double *Z, *work, *w;
+};
+size_t dc_work_doubles(int n);
+dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs);
 }  // namespace dacp
 
 #define DACP_HIP(ctx, call)                                  \
