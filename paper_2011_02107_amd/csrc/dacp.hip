@@ -953,11 +953,11 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
 // ------------------------------------------------------------- projection
 // K splits of the projection's small form (1: the shape does not take it): when the upper
 // triangle of the m x m output has fewer 128 x 128 tiles than the GPU has compute units, K = D is
-// split over up to 64 workgroup layers of at least 1024 rows each.
+// split over up to 64 ranges of at least 1024 rows each.
 int64_t project_small_splits(dacp_ctx ctx, int64_t D, int m) {
   const int64_t t = (m + 127) / 128, tu = t * (t + 1) / 2;
   if (!ctx->project_splitk || tu >= ctx->num_cus) return 1;
-  return std::min<int64_t>({64, (2 * ctx->num_cus + tu - 1) / tu, std::max<int64_t>(1, D / 1024)});
+  return dacp::gemm_splits(m, m, D, 1, ctx->num_cus, 1024, 64);
 }
 
 // One product of the small form, queued on the context's stream without waiting: part 1 is
@@ -1230,9 +1230,7 @@ dacp_status anchor_projection(dacp_ctx ctx, dacp_ham h, const std::vector<int64_
   DACP_HIP(ctx, gd.alloc(static_cast<size_t>(mg) * m * sizeof(double)));
   {
     DevBuf work;
-    const int64_t tiles = static_cast<int64_t>((mg + 127) / 128) * ((m + 127) / 128);
-    const int sp = static_cast<int>(std::min<int64_t>(
-        {16, std::max<int64_t>(1, (4 * ctx->num_cus + tiles - 1) / tiles), std::max<int64_t>(1, D / 4096)}));
+    const int sp = dacp::gemm_splits(mg, m, D, 0, ctx->num_cus, 1024, 64);
     if (sp > 1) {
       DACP_HIP(ctx, work.alloc(static_cast<size_t>(sp) * mg * m * sizeof(double)));
       DACP_HIP(ctx, dacp::launch_dgemm_splitk(1, 0, mg, m, D, 1.0, abuf, mg, V, ldv, 0.0, gd.as<double>(), m, 0, sp,
@@ -1375,13 +1373,13 @@ dacp_status run_project(dacp_ctx ctx, dacp_ham h, int m, const double *V, int64_
     DACP_HIP(ctx, hipStreamSynchronize(s));
     return DACP_OK;
   }
-  // The large form: upper-triangle tiles, K split in two when the scratch fits (twice the work
-  // units: the last round of 8 x 8 tile blocks over the 8 XCDs is then half as long).
+  // The large form: upper-triangle tiles, K split a few ways where that fills the last round of
+  // workgroups better and the scratch fits.
   DevBuf split_work;
-  const int big_splits = (ctx->project_splitk && D >= (int64_t(1) << 18) &&
-                          split_work.alloc(2 * static_cast<size_t>(m) * m * sizeof(double)) == hipSuccess)
-                             ? 2
-                             : 1;
+  int big_splits = ctx->project_splitk ? dacp::gemm_splits(m, m, D, 1, ctx->num_cus, 4096, 4) : 1;
+  if (big_splits > 1 &&
+      split_work.alloc(static_cast<size_t>(big_splits) * m * m * sizeof(double)) != hipSuccess)
+    big_splits = 1;
   (void)hipGetLastError();
   auto gram_upper = [&](const double *B, int64_t ldb, double *C) -> hipError_t {
     return big_splits > 1 ? dacp::launch_dgemm_splitk(1, 0, m, m, D, 1.0, V, ldv, B, ldb, 0.0, C, ld, 1, big_splits,
@@ -1422,13 +1420,9 @@ dacp_status run_project(dacp_ctx ctx, dacp_ham h, int m, const double *V, int64_
   DevBuf wbuf;
   DACP_HIP(ctx, wbuf.alloc(static_cast<size_t>(D) * cw * sizeof(double)));
   double *W = wbuf.as<double>();
-  // The early chunks have few output tiles against a K of 2^L: split K so that every chunk
-  // launches at least ~2 workgroups per compute unit.
+  // The early chunks have few output tiles against a K of 2^L: split K to fill the GPU.
   auto splits_for = [&](int rows, int cols) {
-    const int64_t tiles = ((rows + 127) / 128) * static_cast<int64_t>((cols + 127) / 128);
-    int sp = static_cast<int>(std::min<int64_t>(64, (2 * ctx->num_cus + tiles - 1) / tiles));
-    if (D < 64 * 1024) sp = 1;
-    return std::max(1, sp);
+    return dacp::gemm_splits(rows, cols, D, 0, ctx->num_cus, 1024, 64);
   };
   size_t work_elems = 0;
   for (int c0 = 0; c0 < m; c0 += cw) {

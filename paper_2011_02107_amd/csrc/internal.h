@@ -219,7 +219,9 @@ hipError_t launch_gather_cols(const double *src, int64_t lds, const int *cols, c
 hipError_t launch_dgemm(int transA, int transB, int64_t M, int64_t N, int64_t K, double alpha, const double *A,
                         int64_t lda, const double *B, int64_t ldb, double beta, double *C, int64_t ldc, int upper,
                         hipStream_t s);
-// Same with K split over `splits` workgroup layers; work holds splits * M * N doubles (not upper).
+// Same with K split over `splits` ranges; work holds splits * M * N doubles.  gemm_splits picks their
+// number for a device of `cus` compute units (at least min_rows of K in each).
+int gemm_splits(int64_t M, int64_t N, int64_t K, int upper, int cus, int64_t min_rows, int max_splits);
 hipError_t launch_dgemm_splitk(int transA, int transB, int64_t M, int64_t N, int64_t K, double alpha, const double *A,
                                int64_t lda, const double *B, int64_t ldb, double beta, double *C, int64_t ldc,
                                int upper, int splits, double *work, hipStream_t s);
