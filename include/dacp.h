@@ -365,7 +365,7 @@ typedef struct {
   double t_bound_ms, t_filter_ms, t_evol_ms, t_project_ms, t_gep_ms, t_accept_ms, t_total_ms;
   double evol_kernel_ms;    /* HIP-event time of the evolution launches only        */
   double max_err_est;       /* largest accepted error estimate                      */
-  int evol_group;           /* column-group width the evolution ran with            */
+  int evol_group;           /* columns one evolution launch advances                */
   int n_ghost;              /* candidates whose residual reaches the window edge   */
   int model_used;           /* dacp_central_eigs_learned: 1 = bound and window from the network */
   int model_fallback;       /* 1 = the network's window failed and Lanczos / KPM redid the call */
@@ -471,7 +471,7 @@ dacp_status dacp_accept_rule(int r, const double *theta, int n_sel, const double
 dacp_status dacp_spacing_ratios(const double *eigs, int n, double *r_out, double *mean_out);
 
 /* Autotuner of the evolution recurrence for this Hamiltonian and block width b: times `steps`
- * evolution steps of one column group for every group width (powers of two up to min(b, 16)),
+ * evolution steps of the columns one launch advances for every group width (powers of two up to min(b, 16)),
  * workgroup size (512, 1024), fused tile (4096, 8192 elements; also 1024 and 2048 below 2^19
  * rows) and high-tile row count
  * (automatic, 1, 2), at the real state length, and keeps the fastest in ctx (the "group",

@@ -344,6 +344,40 @@ bool fused_plan(dacp_ctx ctx, dacp_ham h, int g, int &lo_bits, int &W, int esize
   return false;
 }
 
+// Column groups of a recurrence over b columns, `g` columns wanted per group and `blocks` live
+// [D][g] blocks of up to `esize` bytes an element: the fused kernels take power-of-two widths, so a
+// ragged width is rounded up and the columns past b are zero (they cost no launch, where the
+// general kernels take twice as long per step), and `per` groups advance in one launch.  One group
+// of 8 columns is 2 to 32 MB a block below 2^19 rows, whose launches are bound by their own start
+// and end (6-8 us each at 2^16 rows, the streams' rate would take 2.5); together they stream at the
+// rate of a large copy.  A launch's groups stay within the Infinity Cache: past kRecCacheBytes
+// every step would go to HBM (two groups at once at 2^20 rows: 50-60 us a group, alone 44).
+// A shape without a fused plan keeps its width and runs one group at a time.
+constexpr int64_t kRecCacheBytes = int64_t(200) << 20;
+struct ColGroups {
+  int g, per;
+  bool fused;
+  // columns of the launch that starts at column c0 of b, its group width and group count
+  int cols(int c0, int b) const { return std::min(g * per, b - c0); }
+  int width(int nc) const { return fused ? g : nc; }
+  int groups(int nc) const { return fused ? (nc + g - 1) / g : 1; }
+  size_t elems(int64_t D) const { return static_cast<size_t>(D) * g * per; }
+};
+ColGroups column_groups(dacp_ctx ctx, dacp_ham h, int b, int g, int blocks, std::initializer_list<int> esizes) {
+  int w = 1;
+  while (w < g) w *= 2;
+  int emax = 0;
+  for (int e : esizes) {
+    int lo_bits = 0, hw = 1;
+    if (!fused_plan(ctx, h, w, lo_bits, hw, e)) return {g, 1, false};
+    emax = std::max(emax, e);
+  }
+  const int64_t all = (b + w - 1) / w;
+  const int64_t fit = std::max<int64_t>(1, kRecCacheBytes / (h->D * w * emax * blocks));
+  const int64_t launches = (all + fit - 1) / fit;  // of about equal size
+  return {w, static_cast<int>((all + launches - 1) / launches), true};
+}
+
 // y = alpha H x + beta u + gamma z (+ FP64 copy into st), columns split in chunks of <= 2048.
 template <typename T>
 dacp_status step(dacp_ctx ctx, dacp_ham h, int b, const T *x, int64_t ldx, T *y, int64_t ldy, T alpha,
@@ -493,11 +527,11 @@ dacp_status filter_steps(dacp_ctx ctx, dacp_ham h, int b, const FilterCoefs &fc,
 // kernel completes w = H T^_k and starts the partial of T^_{k+1} = alpha H w + beta T^_k +
 // gamma T^_{k-1}; the high coset kernel completes T^_{k+1} and starts the partial of the next w.
 // Same recurrence as filter_steps, with 9 block streams per order instead of two full applies
-// with global gathers.  W and Pp are [D][b] scratch blocks.  `done` stays false, and nothing is
+// with global gathers.  A, B, W and Pp hold `groups` [D][b] blocks each.  `done` stays false, and nothing is
 // launched, when the shape has no fused plan.
 template <typename T>
-dacp_status filter_steps_fused(dacp_ctx ctx, dacp_ham h, int b, const FilterCoefs &fc, T *&A, T *&B, T *W, T *Pp,
-                               int nsteps, bool &done) {
+dacp_status filter_steps_fused(dacp_ctx ctx, dacp_ham h, int b, int groups, const FilterCoefs &fc, T *&A, T *&B, T *W,
+                               T *Pp, int nsteps, bool &done) {
   done = false;
   int lo_bits = 0, hw = 1;
   if (nsteps < 1 || !fused_plan(ctx, h, b, lo_bits, hw, static_cast<int>(sizeof(T)))) return DACP_OK;
@@ -507,13 +541,13 @@ dacp_status filter_steps_fused(dacp_ctx ctx, dacp_ham h, int b, const FilterCoef
   const int64_t D = h->D;
   hipStream_t s = ctx->stream;
   // partial of w_1 = H B: the high half, Pp = Hi B
-  DACP_HIP(ctx, hipMemsetAsync(Pp, 0, static_cast<size_t>(D) * b * sizeof(T), s));
-  {
+  DACP_HIP(ctx, hipMemsetAsync(Pp, 0, static_cast<size_t>(D) * b * groups * sizeof(T), s));
+  for (int y = 0; y < groups; ++y) {
     dacp::HiArgs<T> hb;
     std::memset(&hb, 0, sizeof(hb));
-    hb.x = B;
+    hb.x = B + y * D * b;
     hb.ldx = b;
-    hb.y = Pp;
+    hb.y = Pp + y * D * b;
     hb.ldy = b;
     hb.alpha = T(1);
     hb.flips = so.hi;
@@ -531,7 +565,8 @@ dacp_status filter_steps_fused(dacp_ctx ctx, dacp_ham h, int b, const FilterCoef
   const T gamma = T(-1.0 / (fc.rho * fc.rho));
   dacp::RecArgs<T> ra;
   std::memset(&ra, 0, sizeof(ra));
-  ra.ld = b;
+  ra.groups = groups;
+  ra.gstride = D * b;
   ra.diag = std::is_same<T, double>::value ? reinterpret_cast<const T *>(h->d64) : reinterpret_cast<const T *>(h->d32);
   ra.b = b;
   ra.lo_bits = lo_bits;
@@ -588,14 +623,15 @@ dacp_status normalise_cols(dacp_ctx ctx, double *x, int64_t D, int b) {
   return DACP_OK;
 }
 
-// Filter one contiguous [D][g] group of start columns (FP32 part, then FP64 steps); the
-// newest recurrence term ends in `out` (D x g, FP64, not normalised).
-dacp_status filter_group(dacp_ctx ctx, dacp_ham h, int g, const FilterCoefs &fc, int K, int tail_in, int precision,
-                         const double *psi, double *out) {
-  const int64_t D = h->D;
-  const size_t blk = static_cast<size_t>(D) * g;
+// Filter `groups` contiguous [D][g] groups of start columns (FP32 part, then FP64 steps); the
+// newest recurrence term ends in `out` (same layout, FP64, not normalised).  More than one group
+// only for a shape with fused plans.
+dacp_status filter_group(dacp_ctx ctx, dacp_ham h, int g, int groups, const FilterCoefs &fc, int K, int tail_in,
+                         int precision, const double *psi, double *out) {
+  const int64_t D = h->D, DG = D * groups;
+  const size_t blk = static_cast<size_t>(DG) * g;
   if (K == 0) {
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi, g, out, g, D, g, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_copy_cols(psi, g, out, g, DG, g, ctx->stream));
     return DACP_OK;
   }
   DevBuf a64, w64, b64;
@@ -612,44 +648,48 @@ dacp_status filter_group(dacp_ctx ctx, dacp_ham h, int g, const FilterCoefs &fc,
     DACP_HIP(ctx, b32.alloc(blk * sizeof(float)));
     DACP_HIP(ctx, w32.alloc(blk * sizeof(float)));
     DACP_HIP(ctx, p32.alloc(blk * sizeof(float)));
-    DACP_HIP(ctx, dacp::launch_convert_f64_to_f32(psi, g, p32.as<float>(), g, D, g, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_convert_f64_to_f32(psi, g, p32.as<float>(), g, DG, g, ctx->stream));
     float *A32 = a32.as<float>(), *B32 = b32.as<float>();
-    DACP_HIP(ctx, dacp::launch_convert_f64_to_f32(psi, g, A32, g, D, g, ctx->stream));
-    st = filter_first<float>(ctx, h, g, fc, p32.as<float>(), B32, w32.as<float>());
-    if (st) return st;
+    DACP_HIP(ctx, dacp::launch_convert_f64_to_f32(psi, g, A32, g, DG, g, ctx->stream));
+    for (int y = 0; y < groups; ++y) {
+      st = filter_first<float>(ctx, h, g, fc, p32.as<float>() + y * D * g, B32 + y * D * g, w32.as<float>() + y * D * g);
+      if (st) return st;
+    }
     bool fused = false;
     if (n32 - 1 >= 1) {
       DevBuf q32;
       DACP_HIP(ctx, q32.alloc(blk * sizeof(float)));
-      st = filter_steps_fused<float>(ctx, h, g, fc, A32, B32, w32.as<float>(), q32.as<float>(), n32 - 1, fused);
+      st = filter_steps_fused<float>(ctx, h, g, groups, fc, A32, B32, w32.as<float>(), q32.as<float>(), n32 - 1, fused);
       if (st) return st;
       if (fused) DACP_HIP(ctx, hipStreamSynchronize(ctx->stream));  // q32 is released at scope end
     }
-    if (!fused) {
+    if (!fused && n32 - 1 >= 1) {  // one group
       st = filter_steps<float>(ctx, h, g, fc, A32, B32, w32.as<float>(), n32 - 1);
       if (st) return st;
     }
-    DACP_HIP(ctx, dacp::launch_convert_f32_to_f64(A32, g, A, g, D, g, ctx->stream));
-    DACP_HIP(ctx, dacp::launch_convert_f32_to_f64(B32, g, B, g, D, g, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_convert_f32_to_f64(A32, g, A, g, DG, g, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_convert_f32_to_f64(B32, g, B, g, DG, g, ctx->stream));
     DACP_HIP(ctx, hipStreamSynchronize(ctx->stream));  // FP32 buffers are released at scope end
   } else {
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi, g, A, g, D, g, ctx->stream));
-    st = filter_first<double>(ctx, h, g, fc, psi, B, w64.as<double>());
-    if (st) return st;
+    DACP_HIP(ctx, dacp::launch_copy_cols(psi, g, A, g, DG, g, ctx->stream));
+    for (int y = 0; y < groups; ++y) {
+      st = filter_first<double>(ctx, h, g, fc, psi + y * D * g, B + y * D * g, w64.as<double>() + y * D * g);
+      if (st) return st;
+    }
     tail = K - 1;
   }
   bool fused = false;
   DevBuf q64;
   if (tail >= 1) {
     DACP_HIP(ctx, q64.alloc(blk * sizeof(double)));
-    st = filter_steps_fused<double>(ctx, h, g, fc, A, B, w64.as<double>(), q64.as<double>(), tail, fused);
+    st = filter_steps_fused<double>(ctx, h, g, groups, fc, A, B, w64.as<double>(), q64.as<double>(), tail, fused);
     if (st) return st;
   }
-  if (!fused) {
+  if (!fused && tail >= 1) {  // one group
     st = filter_steps<double>(ctx, h, g, fc, A, B, w64.as<double>(), tail);
     if (st) return st;
   }
-  DACP_HIP(ctx, dacp::launch_copy_cols(B, g, out, g, D, g, ctx->stream));
+  DACP_HIP(ctx, dacp::launch_copy_cols(B, g, out, g, DG, g, ctx->stream));
   DACP_HIP(ctx, hipStreamSynchronize(ctx->stream));
   return DACP_OK;
 }
@@ -679,21 +719,22 @@ dacp_status run_filter(dacp_ctx ctx, dacp_ham h, const dacp_filter_params *p, co
     DACP_HIP(ctx, dacp::launch_philox_gauss(s0.as<double>(), D, b, p->seed, ctx->stream));
     psi = s0.as<double>();
   }
-  // the filter moves 5 blocks per order (apply, apply + combine): a wider group than the
-  // evolution's keeps its launches long enough to stream at full rate
   const int gf = p->precision == DACP_F32 ? ctx->filter_group_f32 : ctx->filter_group_f64;
-  const int g = (h->L >= 15 && b > gf) ? gf : b;
+  // four live blocks: T_(k-1), T_k, w and the partial
+  const int gt = (h->L >= 15 && b > gf) ? gf : b;
+  const ColGroups cg = p->precision == DACP_F32 ? column_groups(ctx, h, b, gt, 4, {4, 8})
+                                                : column_groups(ctx, h, b, gt, 4, {8});
   DevBuf gin, gout;
-  DACP_HIP(ctx, gin.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, gout.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  for (int g0 = 0; g0 < b; g0 += g) {
-    const int gw = std::min(g, b - g0);
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi + g0, b, gin.as<double>(), gw, D, gw, ctx->stream));
-    dacp_status st = filter_group(ctx, h, gw, fc, p->K, p->fp64_tail, p->precision, gin.as<double>(),
+  DACP_HIP(ctx, gin.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, gout.alloc(cg.elems(D) * sizeof(double)));
+  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
+    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
+    DACP_HIP(ctx, dacp::launch_split_cols(psi + g0, b, nc, gin.as<double>(), D, gw, groups, ctx->stream));
+    dacp_status st = filter_group(ctx, h, gw, groups, fc, p->K, p->fp64_tail, p->precision, gin.as<double>(),
                                   gout.as<double>());
     if (st) return st;
-    DACP_HIP(ctx, dacp::launch_copy_cols(gout.as<double>(), gw, psi_out + g0, b, D, gw, ctx->stream));
-    vlog("filter group %d/%d done", g0 / g + 1, (b + g - 1) / g);
+    DACP_HIP(ctx, dacp::launch_join_cols(gout.as<double>(), D, gw, groups, psi_out + g0, b, nc, ctx->stream));
+    vlog("filter columns %d..%d of %d done", g0, g0 + nc, b);
   }
   dacp_status st = normalise_cols(ctx, psi_out, D, b);
   if (st) return st;
@@ -742,17 +783,18 @@ struct GraphRun {
   }
 };
 
-// Chebyshev evolution T_{k+1}(G) = 2 G T_k - T_{k-1} (Sec. II.B) of one column group from T_0 (in
-// A, D x gw, row stride gw) up to T_kmax, G = H inv_e.  A, B and P are D x gw buffers.
+// Chebyshev evolution T_{k+1}(G) = 2 G T_k - T_{k-1} (Sec. II.B) of ncols columns from T_0 (in A) up
+// to T_kmax, G = H inv_e.  A, B and P hold `groups` [D][gw] blocks, block after block (more than one,
+// or columns past ncols, only for a shape with a fused plan).
 //   store_of(k)       device pointer (row stride ldst) that the kernel writing T_k also fills with an
-//                     FP64 copy of it, or null
-//   visit(k, T_k)     called once T_k is complete (D x gw, stride gw) for every k with want(k); it may
-//                     queue work on the context stream that reads T_k (queued before T_k's buffer is
-//                     reused)
+//                     FP64 copy of its ncols columns, or null
+//   visit(k, T_k)     called once T_k is complete (the blocks of A's layout) for every k with want(k);
+//                     it may queue work on the context stream that reads T_k (queued before T_k's
+//                     buffer is reused)
 //   events(k1, k2)    whether a store or a visit falls on k1..k2 (such steps are not replayed from a
 //                     captured graph)
-dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, int gw, double *A, double *B,
-                         double *Pp, const std::function<double *(int64_t)> &store_of, int64_t ldst,
+dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, int gw, int groups, int ncols,
+                         double *A, double *B, double *Pp, const std::function<double *(int64_t)> &store_of, int64_t ldst,
                          const std::function<bool(int64_t)> &want,
                          const std::function<dacp_status(int64_t, const double *)> &visit,
                          const std::function<bool(int64_t, int64_t)> &events, int64_t &launches) {
@@ -760,9 +802,17 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
   double *const A0 = A;
   if (want(0)) DACP_TRY(visit(0, A));
   if (kmax < 1) return DACP_OK;
-  dacp_status st = step<double>(ctx, h, gw, A, gw, B, gw, inv_e, nullptr, 0, 0.0, nullptr, 0, 0.0, store_of(1), ldst, 2);
-  if (st) return st;
-  ++launches;
+  dacp_status st = DACP_OK;
+  const int64_t blk = D * gw;
+  for (int y = 0; y < groups; ++y) {
+    double *const s1 = store_of(1);
+    const int nc = std::min(gw, ncols - y * gw);  // a block with zero columns stores by a copy
+    double *const sy = (s1 && nc == gw) ? s1 + y * gw : nullptr;
+    st = step<double>(ctx, h, gw, A + y * blk, gw, B + y * blk, gw, inv_e, nullptr, 0, 0.0, nullptr, 0, 0.0, sy, ldst, 2);
+    if (st) return st;
+    if (s1 && !sy) DACP_HIP(ctx, dacp::launch_copy_cols(B + y * blk, gw, s1 + y * gw, ldst, D, nc, ctx->stream));
+    ++launches;
+  }
   if (want(1)) DACP_TRY(visit(1, B));
   const int64_t report_every = std::max<int64_t>(1, kmax / 8);
   int lo_bits = 0, hw = 1;
@@ -771,14 +821,14 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
     st = split_order(ctx, h, lo_bits);
     if (st) return st;
     const auto &so = h->split[lo_bits];
-    {
+    for (int y = 0; y < groups; ++y) {
       StepArgs<double> sa;
       std::memset(&sa, 0, sizeof(sa));
-      sa.x = B;
+      sa.x = B + y * blk;
       sa.ldx = gw;
-      sa.y = Pp;
+      sa.y = Pp + y * blk;
       sa.ldy = gw;
-      sa.z = A;
+      sa.z = A + y * blk;
       sa.ldz = gw;
       sa.alpha = 2.0 * inv_e;
       sa.gamma = -1.0;
@@ -794,8 +844,10 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
     }
     dacp::RecArgs<double> ra;
     std::memset(&ra, 0, sizeof(ra));
-    ra.ld = gw;
+    ra.groups = groups;
+    ra.gstride = blk;
     ra.ldst = ldst;
+    ra.st_cols = ncols;
     ra.a_fin = ra.a_start = 2.0 * inv_e;
     ra.b_cur = -1.0;
     ra.diag = h->d64;
@@ -892,21 +944,22 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     panel_of[ks[i]] = 2 * i + 2;
   }
   const int64_t kmax = ks.back();
-  const int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
+  const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
+  const ColGroups cg = column_groups(ctx, h, b, gt, 3, {8});
   DevBuf ba, bb, nrm, pbuf;
-  DACP_HIP(ctx, ba.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, bb.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, pbuf.alloc(static_cast<size_t>(D) * g * sizeof(double)));
+  DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, nrm.alloc(static_cast<size_t>(n) * b * sizeof(double)));
   const double inv_e = 1.0 / p->e_bound;
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
-  for (int g0 = 0; g0 < b; g0 += g) {
-    const int gw = std::min(g, b - g0);
+  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
+    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
     double *A = ba.as<double>(), *B = bb.as<double>();
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, A, gw, D, gw, ctx->stream));
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, V + g0, ldv, D, gw, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, V + g0, ldv, D, nc, ctx->stream));
     auto store_of = [&](int64_t k) -> double * {
       auto it = panel_of.find(k);
       return it == panel_of.end() ? nullptr : V + static_cast<int64_t>(it->second) * b + g0;
@@ -917,7 +970,7 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
       return it != panel_of.end() && it->first <= k2;
     };
     dacp_status st = evolve_group(
-        ctx, h, inv_e, kmax, gw, A, B, pbuf.as<double>(), store_of, ldv, [](int64_t) { return false; },
+        ctx, h, inv_e, kmax, gw, groups, nc, A, B, pbuf.as<double>(), store_of, ldv, [](int64_t) { return false; },
         [](int64_t, const double *) { return DACP_OK; }, panel_in, launches);
     if (st) return st;
   }
@@ -945,7 +998,7 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     stats->steps = kmax;
     stats->launches = launches;
     stats->kernel_ms = evol_ms;
-    stats->group = g;
+    stats->group = std::min(b, cg.g * cg.per);
   }
   return DACP_OK;
 }
@@ -1043,11 +1096,12 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
   const std::vector<int> slot_of = moment_slots(mp.orders, nslot);
   int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
   while (g > 1 && b * g > 1024) g /= 2;  // the tall Gram kernel takes b g <= 1024 pairs
+  const ColGroups cg = column_groups(ctx, h, b, g, 3, {8});
   const double inv_e = 1.0 / p->e_bound;
   DevBuf ba, bb, pbuf, gpsi, mu, nu, part, tmp, didx, dord;
-  DACP_HIP(ctx, ba.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, bb.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, pbuf.alloc(static_cast<size_t>(D) * g * sizeof(double)));
+  DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, gpsi.alloc(static_cast<size_t>(D) * b * sizeof(double)));
   DACP_HIP(ctx, mu.alloc(static_cast<size_t>(nslot) * b * b * sizeof(double)));
   DACP_HIP(ctx, nu.alloc(static_cast<size_t>(nslot) * b * b * sizeof(double)));
@@ -1060,20 +1114,24 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
-  for (int g0 = 0; g0 < b; g0 += g) {
-    const int gw = std::min(g, b - g0);
+  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
+    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
     double *A = ba.as<double>(), *B = bb.as<double>();
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, A, gw, D, gw, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return k <= kmax && slot_of[k] >= 0; };
-    // mu_k[:, g0 .. g0 + gw) = psi_E^T (T_k psi_E)[:, group], nu_k likewise with (G psi_E)^T
-    auto visit = [&](int64_t k, const double *tk) -> dacp_status {
-      const int64_t off = static_cast<int64_t>(slot_of[k]) * b * b + g0;
-      DACP_HIP(ctx, dacp::launch_tall_gram(psi_e, b, b, tk, gw, gw, D, part.as<double>(), nblk, tmp.as<double>(),
-                                           ctx->stream));
-      DACP_HIP(ctx, dacp::launch_copy_cols(tmp.as<double>(), gw, mu.as<double>() + off, b, b, gw, ctx->stream));
-      DACP_HIP(ctx, dacp::launch_tall_gram(gpsi.as<double>(), b, b, tk, gw, gw, D, part.as<double>(), nblk,
-                                           tmp.as<double>(), ctx->stream));
-      DACP_HIP(ctx, dacp::launch_copy_cols(tmp.as<double>(), gw, nu.as<double>() + off, b, b, gw, ctx->stream));
+    // mu_k[:, g0 .. g0 + nc) = psi_E^T (T_k psi_E)[:, group by group], nu_k likewise with (G psi_E)^T
+    auto visit = [&](int64_t k, const double *tks) -> dacp_status {
+      for (int y = 0; y < groups; ++y) {
+        const double *tk = tks + y * D * gw;
+        const int yc = std::min(gw, nc - y * gw);
+        const int64_t off = static_cast<int64_t>(slot_of[k]) * b * b + g0 + y * gw;
+        DACP_HIP(ctx, dacp::launch_tall_gram(psi_e, b, b, tk, gw, yc, D, part.as<double>(), nblk, tmp.as<double>(),
+                                             ctx->stream));
+        DACP_HIP(ctx, dacp::launch_copy_cols(tmp.as<double>(), yc, mu.as<double>() + off, b, b, yc, ctx->stream));
+        DACP_HIP(ctx, dacp::launch_tall_gram(gpsi.as<double>(), b, b, tk, gw, yc, D, part.as<double>(), nblk,
+                                             tmp.as<double>(), ctx->stream));
+        DACP_HIP(ctx, dacp::launch_copy_cols(tmp.as<double>(), yc, nu.as<double>() + off, b, b, yc, ctx->stream));
+      }
       return DACP_OK;
     };
     auto events = [&](int64_t k1, int64_t k2) {
@@ -1082,8 +1140,8 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
       return false;
     };
     dacp_status st = evolve_group(
-        ctx, h, inv_e, kmax, gw, A, B, pbuf.as<double>(), [](int64_t) -> double * { return nullptr; }, 0, want,
-        visit, events, launches);
+        ctx, h, inv_e, kmax, gw, groups, nc, A, B, pbuf.as<double>(), [](int64_t) -> double * { return nullptr; }, 0,
+        want, visit, events, launches);
     if (st) return st;
   }
   const double evol_ms = tm.stop_ms();
@@ -1117,14 +1175,14 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
     stats->steps = kmax;
     stats->launches = launches;
     stats->kernel_ms = evol_ms;
-    stats->group = g;
+    stats->group = std::min(b, cg.g * cg.per);
   }
   return DACP_OK;
 }
 
 // Moment mode, second pass: the Ritz vectors of nc candidates, Phi = A Bc (D x nc, row stride nc),
 // accumulated during an evolution to k_n without storing A.  bsel (device nc x m, row stride m):
-// row c is column c of B.  Panels are staged q_slots column groups at a time, then added with one
+// row c is column c of B.  Panels are staged a few hundred columns at a time, then added with one
 // GEMM Phi += Z W^T, W (nc x K) the matching columns of bsel.
 dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, const double *psi_e,
                                 const double *bsel, int nc, double *Phi, EvolStats *stats) {
@@ -1136,13 +1194,13 @@ dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_param
   for (size_t q = 0; q < mp.orders.size(); ++q) panel_of[mp.orders[q]] = static_cast<int>(q);
   const int64_t kmax = mp.orders.back();
   const int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
-  const int q_slots = 32;
-  const int kz = q_slots * g;
+  const ColGroups cg = column_groups(ctx, h, b, g, 3, {8});
+  const int kz = 32 * std::min(b, std::max(g, 8));  // staged columns: at least one launch's
   const double inv_e = 1.0 / p->e_bound;
   DevBuf ba, bb, pbuf, zb, wb, dcols;
-  DACP_HIP(ctx, ba.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, bb.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, pbuf.alloc(static_cast<size_t>(D) * g * sizeof(double)));
+  DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, zb.alloc(static_cast<size_t>(D) * kz * sizeof(double)));
   DACP_HIP(ctx, wb.alloc(static_cast<size_t>(nc) * kz * sizeof(double)));
   DACP_HIP(ctx, dcols.alloc(static_cast<size_t>(kz) * sizeof(int)));
@@ -1161,17 +1219,20 @@ dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_param
     cols.clear();  // the next copies into Z and dcols are queued behind this GEMM on the same stream
     return DACP_OK;
   };
-  for (int g0 = 0; g0 < b; g0 += g) {
-    const int gw = std::min(g, b - g0);
+  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
+    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
     double *A = ba.as<double>(), *B = bb.as<double>();
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, A, gw, D, gw, ctx->stream));
+    DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return panel_of.count(k) > 0; };
     auto visit = [&](int64_t k, const double *tk) -> dacp_status {
-      if (static_cast<int>(cols.size()) + gw > kz) DACP_TRY(flush());
-      const int slot0 = static_cast<int>(cols.size());
-      DACP_HIP(ctx, dacp::launch_copy_cols(tk, gw, zb.as<double>() + slot0, kz, D, gw, ctx->stream));
       const int pidx = panel_of[k];
-      for (int c = 0; c < gw; ++c) cols.push_back(pidx * b + g0 + c);
+      for (int y = 0; y < groups; ++y) {
+        const int yc = std::min(gw, nc - y * gw);
+        if (static_cast<int>(cols.size()) + yc > kz) DACP_TRY(flush());
+        const int slot0 = static_cast<int>(cols.size());
+        DACP_HIP(ctx, dacp::launch_copy_cols(tk + y * D * gw, gw, zb.as<double>() + slot0, kz, D, yc, ctx->stream));
+        for (int c = 0; c < yc; ++c) cols.push_back(pidx * b + g0 + y * gw + c);
+      }
       return DACP_OK;
     };
     auto events = [&](int64_t k1, int64_t k2) {
@@ -1179,8 +1240,8 @@ dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_param
       return it != panel_of.end() && it->first <= k2;
     };
     dacp_status st = evolve_group(
-        ctx, h, inv_e, kmax, gw, A, B, pbuf.as<double>(), [](int64_t) -> double * { return nullptr; }, 0, want, visit,
-        events, launches);
+        ctx, h, inv_e, kmax, gw, groups, nc, A, B, pbuf.as<double>(), [](int64_t) -> double * { return nullptr; }, 0,
+        want, visit, events, launches);
     if (st) return st;
   }
   DACP_TRY(flush());
@@ -1296,30 +1357,32 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
   for (size_t i = 0; i < anchors.size(); ++i) anchor_of[anchors[i]] = static_cast<int>(i);
   const int na = static_cast<int>(anchors.size());
   const int ma = na * b;  // anchor block width
-  const int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
+  const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
+  const ColGroups cg = column_groups(ctx, h, b, gt, 3, {8});
   const double inv_e = 1.0 / p->e_bound;
   DevBuf ba, bb, pbuf, abuf, nrm;
-  DACP_HIP(ctx, ba.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, bb.alloc(static_cast<size_t>(D) * g * sizeof(double)));
-  DACP_HIP(ctx, pbuf.alloc(static_cast<size_t>(D) * g * sizeof(double)));
+  DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, abuf.alloc(static_cast<size_t>(D) * 2 * ma * sizeof(double)));  // anchors | their H images
   DACP_HIP(ctx, nrm.alloc(static_cast<size_t>(n) * b * sizeof(double)));
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
-  for (int g0 = 0; g0 < b; g0 += g) {
-    const int gw = std::min(g, b - g0);
+  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
+    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
     double *A = ba.as<double>(), *B = bb.as<double>();
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, A, gw, D, gw, s));
-    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, V + g0, ldv, D, gw, s));
+    DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, s));
+    DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, V + g0, ldv, D, nc, s));
     auto store_of = [&](int64_t k) -> double * {
       auto it = panel_of.find(k);
       return (k == 0 || it == panel_of.end()) ? nullptr : V + static_cast<int64_t>(it->second) * b + g0;
     };
     auto want = [&](int64_t k) { return anchor_of.count(k) > 0; };
     auto visit = [&](int64_t k, const double *tk) -> dacp_status {
-      DACP_HIP(ctx, dacp::launch_copy_cols(tk, gw, abuf.as<double>() + static_cast<int64_t>(anchor_of[k]) * b + g0,
-                                           2 * ma, D, gw, s));
+      DACP_HIP(ctx, dacp::launch_join_cols(tk, D, gw, groups,
+                                           abuf.as<double>() + static_cast<int64_t>(anchor_of[k]) * b + g0, 2 * ma, nc,
+                                           s));
       return DACP_OK;
     };
     auto events = [&](int64_t k1, int64_t k2) {
@@ -1329,7 +1392,8 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
       return ia != anchor_of.end() && ia->first <= k2;
     };
     dacp_status st =
-        evolve_group(ctx, h, inv_e, kn + 1, gw, A, B, pbuf.as<double>(), store_of, ldv, want, visit, events, launches);
+        evolve_group(ctx, h, inv_e, kn + 1, gw, groups, nc, A, B, pbuf.as<double>(), store_of, ldv, want, visit, events,
+                     launches);
     if (st) return st;
   }
   const double evol_ms = tm.stop_ms();
@@ -1352,7 +1416,7 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
     stats->steps = kn + 1;
     stats->launches = launches;
     stats->kernel_ms = evol_ms;
-    stats->group = g;
+    stats->group = std::min(b, cg.g * cg.per);
   }
   return DACP_OK;
 }
@@ -3513,26 +3577,26 @@ dacp_status dacp_autotune(dacp_ctx ctx, dacp_ham h, int b, int steps, int *best_
   // unit start columns; E_b = sum |c| >= ||H||; a_r = pi / steps puts the first sample pair at k = steps
   DevBuf psi, V;
   const int gmax = std::min(b, 16);
-  DACP_HIP(ctx, psi.alloc(static_cast<size_t>(D) * gmax * sizeof(double)));
-  DACP_HIP(ctx, V.alloc(static_cast<size_t>(D) * 3 * gmax * sizeof(double)));
+  const int bmax = static_cast<int>(std::max<int64_t>(gmax, std::min<int64_t>(b, kRecCacheBytes / (D * 24))));
+  DACP_HIP(ctx, psi.alloc(static_cast<size_t>(D) * bmax * sizeof(double)));
+  DACP_HIP(ctx, V.alloc(static_cast<size_t>(D) * 3 * bmax * sizeof(double)));
   double best = INFINITY;
   Cand bc = cands.front();
-  int g_ready = 0;
+  int n_ready = 0;
   std::set<int64_t> shapes;
   for (const Cand &c : cands) {
-    if (c.group != g_ready) {  // a [D][group] start block for this width
-      DACP_HIP(ctx, dacp::launch_philox_gauss(psi.as<double>(), D, c.group, 12345, ctx->stream));
-      DACP_TRY(normalise_cols(ctx, psi.as<double>(), D, c.group));
-      g_ready = c.group;
-    }
     ctx->rec_threads = c.threads;
     ctx->rec_tile_elems = c.tile;
     ctx->rec_hi_w = c.hi_w;
     // time each distinct launch shape once: knob settings that resolve to the same fused plan (or
     // to the unfused apply for this width) run the same kernels
+    int ncol = c.group;
     {
       int lb = 0, wf = 0;
       const bool fz = fused_plan(ctx, h, c.group, lb, wf, 8);
+      // the columns one launch advances (the general kernels': one group)
+      const ColGroups cg = column_groups(ctx, h, bmax, c.group, 3, {8});
+      ncol = cg.fused ? std::min(bmax, cg.g * cg.per) : c.group;
       const int64_t key = fz ? ((static_cast<int64_t>(c.group) * 4096 + c.threads) * 64 + lb) * 16 + wf : -c.group;
       if (!shapes.insert(key).second) continue;
     }
@@ -3540,19 +3604,24 @@ dacp_status dacp_autotune(dacp_ctx ctx, dacp_ham h, int b, int steps, int *best_
     bp.e_bound = h->sum_abs;
     bp.a = h->sum_abs * M_PI / steps;
     bp.n = 1;
-    bp.b = c.group;
+    bp.b = ncol;
     bp.group = c.group;
     if (!(bp.a < bp.e_bound)) continue;
+    if (ncol != n_ready) {  // a [D][ncol] start block
+      DACP_HIP(ctx, dacp::launch_philox_gauss(psi.as<double>(), D, ncol, 12345, ctx->stream));
+      DACP_TRY(normalise_cols(ctx, psi.as<double>(), D, ncol));
+      n_ready = ncol;
+    }
     EvolStats es;
     int m = 0;
     // first call loads the kernels and the flip tables, the second is timed
-    dacp_status st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * c.group, &m, &es);
-    if (st == DACP_OK) st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * c.group, &m, &es);
+    dacp_status st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * ncol, &m, &es);
+    if (st == DACP_OK) st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * ncol, &m, &es);
     if (st != DACP_OK || es.steps < 1) {
       ctx->err.clear();
       continue;
     }
-    const double us = es.kernel_ms * 1e3 / (static_cast<double>(es.steps) * c.group);
+    const double us = es.kernel_ms * 1e3 / (static_cast<double>(es.steps) * ncol);
     vlog("autotune: group %d threads %d tile %d hi_w %d: %.3f us per column-step", c.group, c.threads, c.tile, c.hi_w,
          us);
     if (us < best) {

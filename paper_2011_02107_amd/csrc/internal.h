@@ -84,16 +84,20 @@ struct HiArgs {
 // filter's two applies per order take the coefficients of its recurrence (filter_steps_fused).
 // T_new may be written over the buffer of an earlier term; P is updated in place.
 // The blocks are contiguous [D][b] with b * sizeof(T) a multiple of 16 bytes and
-// D * b * sizeof(T) < 2^32 (32-bit byte offsets from the block's base).
+// D * b * sizeof(T) < 2^32 (32-bit byte offsets from the block's base).  One launch advances `groups`
+// such blocks, block y of tcur, tnew, p and old at element offset y gstride.
 template <typename T>
 struct RecArgs {
   const T *tcur;
   T *tnew;
   T *p;
   const T *old;  // optional third block of the new partial (same layout)
-  double *st;   // optional FP64 copy of T_new (basis sample), row stride ldst
+  double *st;   // optional FP64 copy of T_new (basis sample), row stride ldst: block y's columns
+                // at st + y b, columns st_cols and above not stored
   int64_t ldst;
-  int64_t ld;   // row stride of tcur, tnew, p (= b)
+  int st_cols;
+  int groups;
+  int64_t gstride;
   T a_fin, a_start, b_cur, c_old;
   const T *diag;
   const FlipEntry *flips;  // read-only while a kernel runs (loaded through the scalar cache)
@@ -184,6 +188,12 @@ hipError_t launch_coldots(const void *x, int64_t ldx, const void *y, int64_t ldy
 int coldots_blocks(int64_t D, int b);
 hipError_t launch_colscale(double *x, int64_t ldx, int64_t D, int b, const double *sq_norms, hipStream_t s);
 hipError_t launch_copy_cols(const double *x, int64_t ldx, double *y, int64_t ldy, int64_t D, int b, hipStream_t s);
+// Columns 0 .. b - 1 of x (row stride ldx) into `groups` contiguous [D][g] blocks of y, block after
+// block, the columns past b zero; and back.
+hipError_t launch_split_cols(const double *x, int64_t ldx, int b, double *y, int64_t D, int g, int groups,
+                             hipStream_t s);
+hipError_t launch_join_cols(const double *x, int64_t D, int g, int groups, double *y, int64_t ldy, int b,
+                            hipStream_t s);
 hipError_t launch_convert_f64_to_f32(const double *x, int64_t ldx, float *y, int64_t ldy, int64_t D, int b,
                                      hipStream_t s);
 hipError_t launch_convert_f32_to_f64(const float *x, int64_t ldx, double *y, int64_t ldy, int64_t D, int b,

@@ -492,10 +492,12 @@ constexpr int rec_min_waves(int nt, int nv) { return (nt == 1024 && nv <= 4) ? 8
 
 template <typename T>
 __device__ __forceinline__ void store_sample(double *st, int64_t ldst, uint32_t row, uint32_t cv,
-                                             const typename Vec16<T>::type &x) {
-  double *d = st + static_cast<int64_t>(row) * ldst + (static_cast<int64_t>(cv) << Vec16<T>::log2n);
+                                             const typename Vec16<T>::type &x, int ncols) {
+  const int c = static_cast<int>(cv) << Vec16<T>::log2n;
+  double *d = st + static_cast<int64_t>(row) * ldst + c;
 #pragma unroll
-  for (int q = 0; q < Vec16<T>::n; ++q) d[q] = static_cast<double>(x[q]);
+  for (int q = 0; q < Vec16<T>::n; ++q)
+    if (c + q < ncols) d[q] = static_cast<double>(x[q]);
 }
 
 // Both kernels keep three vector sets per thread (T_cur, the accumulator and one flip's loads in
@@ -525,9 +527,10 @@ __global__ __launch_bounds__(NT, rec_min_waves(NT, NV)) void k_rec_lo(RecArgs<T>
   if (a.xcd_remap) bid = (bid & 7) * (a.ntiles >> 3) + (bid >> 3);
   const uint32_t row0 = static_cast<uint32_t>(bid) << a.lo_bits;
   const uint32_t vbase = row0 << lbv;
-  const V *tc = reinterpret_cast<const V *>(a.tcur) + vbase;
-  V *tn = reinterpret_cast<V *>(a.tnew) + vbase;
-  V *pp = reinterpret_cast<V *>(a.p) + vbase;
+  const int64_t go = blockIdx.y * a.gstride;  // this launch row's block
+  const V *tc = reinterpret_cast<const V *>(a.tcur + go) + vbase;
+  V *tn = reinterpret_cast<V *>(a.tnew + go) + vbase;
+  V *pp = reinterpret_cast<V *>(a.p + go) + vbase;
   auto rowf = [&](int i) { return row0 + ((lane_tid() + static_cast<uint32_t>(i) * NT) >> lbv); };
   auto dg = [&](int i) { return dtile[(lane_tid() + static_cast<uint32_t>(i) * NT) >> lbv]; };
   V cur[NV], acc[NV];
@@ -554,7 +557,9 @@ __global__ __launch_bounds__(NT, rec_min_waves(NT, NV)) void k_rec_lo(RecArgs<T>
   }
   if (a.st) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) store_sample<T>(a.st, a.ldst, rowf(i), (lane_tid() + i * NT) & cvmask, acc[i]);
+    for (int i = 0; i < NV; ++i)
+      store_sample<T>(a.st + blockIdx.y * a.b, a.ldst, rowf(i), (lane_tid() + i * NT) & cvmask, acc[i],
+                      a.st_cols - static_cast<int>(blockIdx.y) * a.b);
   }
   __syncthreads();
 #pragma unroll
@@ -565,7 +570,7 @@ __global__ __launch_bounds__(NT, rec_min_waves(NT, NV)) void k_rec_lo(RecArgs<T>
   __syncthreads();
   rec_flips<T, NT, NV>(acc, tile, a.flips, a.nplain, a.nflip, lbv, rowf);
   if (a.old) {
-    const V *od = reinterpret_cast<const V *>(a.old) + vbase;
+    const V *od = reinterpret_cast<const V *>(a.old + go) + vbase;
     V o[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) o[i] = *vec_at(od + i * NT, lane_tid());
@@ -595,9 +600,10 @@ __global__ __launch_bounds__(NT, rec_min_waves(NT, NV)) void k_rec_hi(RecArgs<T>
   if (a.xcd_remap) bid = (bid & 7) * (a.ntiles >> 3) + (bid >> 3);
   const uint32_t l0 = static_cast<uint32_t>(bid) << lw;
   const uint32_t istep = static_cast<uint32_t>(NT >> (lw + lbv)) << (a.lo_bits + lbv);
-  const V *tc = reinterpret_cast<const V *>(a.tcur);
-  V *tn = reinterpret_cast<V *>(a.tnew);
-  V *pp = reinterpret_cast<V *>(a.p);
+  const int64_t go = blockIdx.y * a.gstride;
+  const V *tc = reinterpret_cast<const V *>(a.tcur + go);
+  V *tn = reinterpret_cast<V *>(a.tnew + go);
+  V *pp = reinterpret_cast<V *>(a.p + go);
   auto rowf = [&](int i) {
     const uint32_t rv = (lane_tid() + static_cast<uint32_t>(i) * NT) >> lbv;
     return l0 + (rv & wmask) + ((rv >> lw) << a.lo_bits);
@@ -631,7 +637,9 @@ __global__ __launch_bounds__(NT, rec_min_waves(NT, NV)) void k_rec_hi(RecArgs<T>
   }
   if (a.st) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) store_sample<T>(a.st, a.ldst, rowf(i), lane_tid() & cvmask, acc[i]);
+    for (int i = 0; i < NV; ++i)
+      store_sample<T>(a.st + blockIdx.y * a.b, a.ldst, rowf(i), lane_tid() & cvmask, acc[i],
+                      a.st_cols - static_cast<int>(blockIdx.y) * a.b);
   }
   __syncthreads();
 #pragma unroll
@@ -643,7 +651,7 @@ __global__ __launch_bounds__(NT, rec_min_waves(NT, NV)) void k_rec_hi(RecArgs<T>
   if (a.old) {
     V o[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) o[i] = *vec_at(reinterpret_cast<const V *>(a.old) + i * istep, off0());
+    for (int i = 0; i < NV; ++i) o[i] = *vec_at(reinterpret_cast<const V *>(a.old + go) + i * istep, off0());
 #pragma unroll
     for (int i = 0; i < NV; ++i)
       *vec_at(pp + i * istep, off0()) = (a.a_start * acc[i] + a.b_cur * cur[i]) + a.c_old * o[i];
@@ -663,6 +671,7 @@ __global__ __launch_bounds__(NT) void k_rec_lo_p(RecArgs<T> a) {
   V *tile = reinterpret_cast<V *>(smem_raw);
   const int lbv = (__ffs(a.b) - 1) - Vec16<T>::log2n;
   const uint32_t cvmask = (1u << lbv) - 1u;
+  const int64_t go = blockIdx.y * a.gstride;
   const int G = gridDim.x;
   int t = blockIdx.x;
   V cn[NV], pn[NV];
@@ -673,8 +682,8 @@ __global__ __launch_bounds__(NT) void k_rec_lo_p(RecArgs<T> a) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const uint32_t v = threadIdx.x + i * NT;
-      cn[i] = reinterpret_cast<const V *>(a.tcur)[vb + v];
-      pn[i] = reinterpret_cast<const V *>(a.p)[vb + v];
+      cn[i] = reinterpret_cast<const V *>(a.tcur + go)[vb + v];
+      pn[i] = reinterpret_cast<const V *>(a.p + go)[vb + v];
       dn[i] = a.diag[r0 + (v >> lbv)];
     }
   };
@@ -699,13 +708,15 @@ __global__ __launch_bounds__(NT) void k_rec_lo_p(RecArgs<T> a) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) acc[i] = dg[i] * cur[i];
     rec_flips<T, NT, NV>(acc, tile, a.flips, a.nplain, a.nflip, lbv, [&](int i) { return row[i]; });
-    V *tn = reinterpret_cast<V *>(a.tnew) + vbase;
+    V *tn = reinterpret_cast<V *>(a.tnew + go) + vbase;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const uint32_t v = threadIdx.x + i * NT;
       nw[i] += a.a_fin * acc[i];
       tn[v] = nw[i];
-      if (a.st) store_sample<T>(a.st, a.ldst, row[i], v & cvmask, nw[i]);
+      if (a.st)
+        store_sample<T>(a.st + blockIdx.y * a.b, a.ldst, row[i], v & cvmask, nw[i],
+                        a.st_cols - static_cast<int>(blockIdx.y) * a.b);
     }
     __syncthreads();
 #pragma unroll
@@ -714,11 +725,11 @@ __global__ __launch_bounds__(NT) void k_rec_lo_p(RecArgs<T> a) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) acc[i] = dg[i] * nw[i];
     rec_flips<T, NT, NV>(acc, tile, a.flips, a.nplain, a.nflip, lbv, [&](int i) { return row[i]; });
-    V *pp = reinterpret_cast<V *>(a.p) + vbase;
+    V *pp = reinterpret_cast<V *>(a.p + go) + vbase;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       V o = V(T(0));
-      if (a.old) o = reinterpret_cast<const V *>(a.old)[vbase + threadIdx.x + i * NT];
+      if (a.old) o = reinterpret_cast<const V *>(a.old + go)[vbase + threadIdx.x + i * NT];
       pp[threadIdx.x + i * NT] =
           a.old ? (a.a_start * acc[i] + a.b_cur * cur[i]) + a.c_old * o : a.a_start * acc[i] + a.b_cur * cur[i];
     }
@@ -736,6 +747,7 @@ __global__ __launch_bounds__(NT) void k_rec_hi_p(RecArgs<T> a) {
   const uint32_t cvmask = (1u << lbv) - 1u;
   const uint32_t wmask = static_cast<uint32_t>(a.W) - 1u;
   const int hs = lw + lbv - a.lo_bits;
+  const int64_t go = blockIdx.y * a.gstride;
   const int G = gridDim.x;
   int t = blockIdx.x;
   // element offsets relative to the tile's first row l0 = t W (row = l0 + rel)
@@ -752,8 +764,8 @@ __global__ __launch_bounds__(NT) void k_rec_hi_p(RecArgs<T> a) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const uint32_t off = ((l0 + rel[i]) << lbv) | ((threadIdx.x + i * NT) & cvmask);
-      cn[i] = reinterpret_cast<const V *>(a.tcur)[off];
-      pn[i] = reinterpret_cast<const V *>(a.p)[off];
+      cn[i] = reinterpret_cast<const V *>(a.tcur + go)[off];
+      pn[i] = reinterpret_cast<const V *>(a.p + go)[off];
     }
   };
   if (t < a.ntiles) fetch(t);
@@ -778,8 +790,10 @@ __global__ __launch_bounds__(NT) void k_rec_hi_p(RecArgs<T> a) {
     for (int i = 0; i < NV; ++i) {
       const uint32_t cv = (threadIdx.x + i * NT) & cvmask;
       nw[i] += a.a_fin * acc[i];
-      reinterpret_cast<V *>(a.tnew)[(row[i] << lbv) | cv] = nw[i];
-      if (a.st) store_sample<T>(a.st, a.ldst, row[i], cv, nw[i]);
+      reinterpret_cast<V *>(a.tnew + go)[(row[i] << lbv) | cv] = nw[i];
+      if (a.st)
+        store_sample<T>(a.st + blockIdx.y * a.b, a.ldst, row[i], cv, nw[i],
+                        a.st_cols - static_cast<int>(blockIdx.y) * a.b);
     }
     __syncthreads();
 #pragma unroll
@@ -793,8 +807,8 @@ __global__ __launch_bounds__(NT) void k_rec_hi_p(RecArgs<T> a) {
       const uint32_t cv = (threadIdx.x + i * NT) & cvmask;
       const uint32_t gv = (row[i] << lbv) | cv;
       V o = V(T(0));
-      if (a.old) o = reinterpret_cast<const V *>(a.old)[gv];
-      reinterpret_cast<V *>(a.p)[gv] =
+      if (a.old) o = reinterpret_cast<const V *>(a.old + go)[gv];
+      reinterpret_cast<V *>(a.p + go)[gv] =
           a.old ? (a.a_start * acc[i] + a.b_cur * cur[i]) + a.c_old * o : a.a_start * acc[i] + a.b_cur * cur[i];
     }
     __syncthreads();
@@ -820,7 +834,7 @@ hipError_t launch_rec_nt(const RecArgs<T> &a, int nvec, bool hi, hipStream_t s) 
   if (!hi && rows_lo > 8192) return hipErrorInvalidValue;
   // (the 1024-thread persistent form with 4 vectors per thread would spill: launch one tile per workgroup)
   const bool persist = a.grid > 0 && a.grid < a.ntiles && !(NT == 1024 && nvec / NT == 4);
-  dim3 grid(persist ? a.grid : a.ntiles), block(NT);
+  dim3 grid(persist ? a.grid : a.ntiles, a.groups), block(NT);
 #define DACP_REC(nv_)                                                                  \
   do {                                                                                 \
     if (persist) {                                                                     \
@@ -850,7 +864,8 @@ template <typename T>
 hipError_t launch_rec(const RecArgs<T> &a, bool hi, hipStream_t s) {
   const int64_t rows = hi ? (static_cast<int64_t>(a.W) << a.hi_bits) : (int64_t(1) << a.lo_bits);
   const int64_t nel = rows * a.b;
-  if ((a.b * static_cast<int>(sizeof(T))) % 16 != 0 || nel * static_cast<int64_t>(sizeof(T)) > 65536)
+  if ((a.b * static_cast<int>(sizeof(T))) % 16 != 0 || nel * static_cast<int64_t>(sizeof(T)) > 65536 ||
+      a.groups < 1 || a.groups > 65535)
     return hipErrorInvalidValue;
   const int nvec = static_cast<int>(nel * sizeof(T) / 16);
   // 32-bit byte offsets over the whole block (high pass), and W rows of vectors dividing the
@@ -1192,6 +1207,38 @@ hipError_t launch_convert_f32_to_f64(const float *x, int64_t ldx, double *y, int
                                      hipStream_t s) {
   const int64_t n = D * b;
   hipLaunchKernelGGL((k_copy_cols<float, double>), dim3((n + 255) / 256), dim3(256), 0, s, x, ldx, y, ldy, D, b);
+  return hipGetLastError();
+}
+
+__global__ void k_split_cols(const double *x, int64_t ldx, int b, double *y, int64_t D, int g, int64_t n) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  const int64_t rg = e / g;
+  const int y0 = static_cast<int>(rg / D);
+  const int c = y0 * g + static_cast<int>(e - rg * g);
+  y[e] = c < b ? x[(rg - y0 * D) * ldx + c] : 0.0;
+}
+
+hipError_t launch_split_cols(const double *x, int64_t ldx, int b, double *y, int64_t D, int g, int groups,
+                             hipStream_t s) {
+  const int64_t n = D * g * groups;
+  hipLaunchKernelGGL(k_split_cols, dim3((n + 255) / 256), dim3(256), 0, s, x, ldx, b, y, D, g, n);
+  return hipGetLastError();
+}
+
+__global__ void k_join_cols(const double *x, int64_t D, int g, double *y, int64_t ldy, int b) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e >= D * b) return;
+  const int64_t r = e / b;
+  const int c = static_cast<int>(e - r * b);
+  y[r * ldy + c] = x[(static_cast<int64_t>(c / g) * D + r) * g + c % g];
+}
+
+hipError_t launch_join_cols(const double *x, int64_t D, int g, int groups, double *y, int64_t ldy, int b,
+                            hipStream_t s) {
+  if (b > g * groups) return hipErrorInvalidValue;
+  const int64_t n = D * b;
+  hipLaunchKernelGGL(k_join_cols, dim3((n + 255) / 256), dim3(256), 0, s, x, D, g, y, ldy, b);
   return hipGetLastError();
 }
 
