@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdacp.so")
-SOURCES = ["kernels.hip", "gemm.hip", "eig.hip", "dc.hip", "batch.hip", "beig.hip", "mlp.hip", "dacp.hip"]
+SOURCES = ["kernels.hip", "gemm.hip", "eig.hip", "dc.hip", "tridiag.hip", "batch.hip", "beig.hip", "mlp.hip", "dacp.hip"]
 # host-only sources (no device code): compiled by the host C++ compiler
 HOST_SOURCES = ["host_rules.cpp"]
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
@@ -44,7 +44,7 @@ def build(verbose=False):
             print(r.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, SOURCES + HOST_SOURCES))
     tmp = LIB + ".tmp"
     cmd = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", tmp]

@@ -16,7 +16,7 @@
 // Two more launches over every matrix then turn the rows of Zr into eigenvectors of A, Zr Q^T with
 // Q = H_0 H_1 ... H_(n-3), never forming Q: k_wy_prep writes each block of kWY reflectors in
 // compact WY form (the masked rows V and the triangular T), k_wy_apply applies the blocks to Zr
-// from the right, last block first, RB rows of Zr per workgroup held in LDS (rows are
+// from the right, last block first, 16 rows of Zr per workgroup held in registers (rows are
 // independent).  The host sorts the eigenvalues and gathers the rows in that order.
 #include <hip/hip_runtime.h>
 
@@ -43,8 +43,8 @@ constexpr size_t kLdsMax = 160 * 1024;
 constexpr int kPipeLag = 5;     // rotations between consecutive sweeps of a pipelined batch
 constexpr int kPipeMin = 48;    // smallest unreduced block chased as a pipelined batch
 constexpr int kShiftSlots = 8;  // LDS slots for a pipelined batch's shifts (S <= 8)
-constexpr int kWY = 64;         // reflectors per compact-WY block of the back-transformation
-constexpr int kRB = 8;          // rows of Zr per workgroup of the back-transformation
+constexpr int kRB = kWyRows;
+using WyItem = BatchWyItem;
 
 // Sum over the workgroup, the same value returned to every thread (fixed order: lanes by
 // butterfly, then the waves in index order).  red holds kBWaves doubles.
@@ -608,11 +608,6 @@ __global__ __launch_bounds__(kBT) void k_batch_syev(const BatchEigProblem *probs
   for (int i = tid; i < n; i += kBT) pb.w[i] = d[i];
 }
 
-// Work item of the back-transformation launches: matrix `prob`, reflector block or first row `at`.
-struct WyItem {
-  int prob, at;
-};
-
 // Compact-WY factors of the reflectors H_k = I - beta_k v_k v_k^T that k_batch_syev left in the rows
 // of A (row k: beta_k at column k, v_k at columns k+1..), one workgroup per block of kWY reflectors
 // k0 = item.at ..: writes the block's rows of V (row k = v_k, zero at columns <= k; V = the
@@ -663,64 +658,141 @@ __global__ __launch_bounds__(256) void k_wy_prep(const BatchEigProblem *probs, c
   for (int e = tid; e < kb * kb; e += blockDim.x) Tb[e] = Ts[e / kb][e % kb];
 }
 
-// Rows item.at .. item.at + kRB - 1 of Zr <- Zr Q^T = Zr P_B^T ... P_0^T, P_j = I - V_j^T T_j V_j
-// (k_wy_prep): the last block first, Z <- Z - ((Z V_j^T) T_j^T) V_j on the columns after k0 (V_j is
-// zero on the others).  The rows stay in LDS (dynamic: kRB x n doubles) through every block.
-__global__ __launch_bounds__(256) void k_wy_apply(const BatchEigProblem *probs, const WyItem *items) {
-  extern __shared__ double zs[];
-  __shared__ double w1[kRB][kWY], w2[kRB][kWY];
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2du __attribute__((ext_vector_type(2), aligned(8)));  // two doubles of a row of any stride
+
+// Rows item.at .. item.at + 15 of Zr <- Zr Q^T = Zr P_B^T ... P_0^T, P_j = I - V_j^T T_j V_j: the last
+// block first, Z <- Z - ((Z V_j^T) T_j^T) V_j on the columns after k0 (V_j is zero on the others).
+//
+// The rows stay in registers through every block, as FP64 MFMA accumulators of Z^T: tile t of a
+// wave (tiles wave, wave + 4, ...; 16 columns of Z each) has accumulator row q + 4 e (lane 16 q + i, item e)
+// for column 16 t + 4 q + e and accumulator column i for row i of Z.  An accumulator is laid out as
+// the B operand of the next product over its rows, so W1^T = V_j Z^T takes the tiles as they are
+// (A: four consecutive elements of a row of V_j per lane), the four waves' parts are added in LDS,
+// W2^T = T_j W1^T takes that sum, and Z^T -= V_j^T W2^T accumulates into the tiles.  V_j is read
+// twice from L2; nothing else moves.  (With the rows in LDS, a reflector at a time against 8 of
+// them, this took 3.7 ms at n = 1237.)
+template <int NT>
+__global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *probs, const WyItem *items) {
+  __shared__ double part[4][kWY][17];
+  __shared__ double w2[kWY][17];
   const WyItem it = items[blockIdx.x];
   const BatchEigProblem pb = probs[it.prob];
   const int n = pb.n, nref = n - 2;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int rows = min(kRB, n - it.at);
-  double *Z = pb.Zr + static_cast<int64_t>(it.at) * n;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lq = lane >> 4;
+  const int64_t zrow = it.at + li;
+  double *Z = pb.Zr + zrow * n;
   const double *V = pb.work, *T = pb.work + static_cast<int64_t>(n) * n;
-  for (int e = tid; e < rows * n; e += blockDim.x) zs[e] = Z[e];
-  __syncthreads();
+  v4d z[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int c = 16 * (wave + 4 * t) + 4 * lq;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[t][e] = (zrow < n && c + e < n) ? Z[c + e] : 0.0;
+  }
+  const int ci = 4 * (li & 3) + (li >> 2);  // accumulator row i of a tile is column 16 t + ci(i)
+  uint32_t off1 = li * n + 4 * lq, off2 = lq * n + ci;
+  int wt = wave;  // first tile
   const int nblk = (nref + kWY - 1) / kWY;
   for (int j = nblk - 1; j >= 0; --j) {
-    const int k0 = j * kWY, kb = min(kWY, nref - k0), c0 = k0 + 1;
+    const int k0 = j * kWY, kb = min(kWY, nref - k0);
     const double *Vj = V + static_cast<int64_t>(k0) * n;
     const double *Tj = T + static_cast<int64_t>(j) * kWY * kWY;
-    // w1 = Z V_j^T: one (row, reflector) pair per wave at a time, lanes along the columns
-    for (int pq = wave; pq < rows * kb; pq += 4) {
-      const int r = pq / kb, q = pq - r * kb;
-      const double *vq = Vj + static_cast<int64_t>(q) * n;
-      const double *zr = zs + r * n;
-      double acc = 0.0;
-      for (int c = c0 + lane; c < n; c += 64) acc += zr[c] * vq[c];
+    const int t0 = (k0 + 1) >> 4;  // first tile with a column after k0
+    // opaque per block, so that nothing derived per tile is kept in registers across blocks
+    asm volatile("" : "+v"(off1), "+v"(off2), "+s"(wt));
+    // this wave's part of W1^T
+    v4d w1[4];
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-      if (lane == 0) w1[r][q] = acc;
-    }
-    __syncthreads();
-    // w2 = w1 T_j^T
-    for (int e = tid; e < rows * kb; e += blockDim.x) {
-      const int r = e / kb, i = e - r * kb;
-      double acc = 0.0;
-      for (int q = 0; q < kb; ++q) acc += w1[r][q] * Tj[i * kb + q];
-      w2[r][i] = acc;
-    }
-    __syncthreads();
-    // Z -= w2 V_j on the columns after k0: one column per thread, every row of the item
-    for (int c = c0 + tid; c < n; c += blockDim.x) {
-      double acc[kRB];
+    for (int g = 0; g < 4; ++g) w1[g] = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int r = 0; r < kRB; ++r) acc[r] = 0.0;
-      for (int i = 0; i < kb; ++i) {
-        const double v = Vj[static_cast<int64_t>(i) * n + c];
+    for (int t = 0; t < NT; ++t) {
+      const int tt = wt + 4 * t, c = 16 * tt + 4 * lq;
+      asm volatile("" ::: "memory");  // the next tiles' loads stay behind: no registers for them
+      if (tt < t0 || 16 * tt >= n) continue;
+      double a[4][4];
 #pragma unroll
-        for (int r = 0; r < kRB; ++r) acc[r] += w2[r][i] * v;
+      for (int g = 0; g < 4; ++g) {
+        // a uniform base and one 32-bit offset per lane: no 64-bit address registers per tile
+        const double *vr = Vj + (16 * g * n + 16 * tt) + off1;
+        const bool row = 16 * g + li < kb;
+        if (16 * tt + 16 <= n) {
+          const v2du x = row ? *reinterpret_cast<const v2du *>(vr) : v2du{0.0, 0.0};
+          const v2du y = row ? *reinterpret_cast<const v2du *>(vr + 2) : v2du{0.0, 0.0};
+          a[g][0] = x[0];
+          a[g][1] = x[1];
+          a[g][2] = y[0];
+          a[g][3] = y[1];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[g][e] = (row && c + e < n) ? vr[e] : 0.0;
+        }
       }
-      for (int r = 0; r < rows; ++r) zs[r * n + c] -= acc[r];
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w1[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g][e], z[t][e], w1[g], 0, 0, 0);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[wave][16 * g + lq + 4 * e][li] = w1[g][e];
+    __syncthreads();
+    // W2^T = T_j W1^T, wave w the rows 16 w .. 16 w + 15
+    {
+      v4d acc = {0.0, 0.0, 0.0, 0.0};
+      const int r = 16 * wave + li;
+#pragma unroll
+      for (int s = 0; s < kWY / 4; ++s) {
+        const int q = 4 * s + lq;
+        const double tv = (r < kb && q < kb) ? Tj[r * kb + q] : 0.0;
+        const double b = (part[0][q][li] + part[1][q][li]) + (part[2][q][li] + part[3][q][li]);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, b, acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w2[16 * wave + lq + 4 * e][li] = -acc[e];
     }
     __syncthreads();
+    double b2[kWY / 4];
+#pragma unroll
+    for (int s = 0; s < kWY / 4; ++s) b2[s] = w2[4 * s + lq][li];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int tt = wt + 4 * t, c = 16 * tt + ci;
+      asm volatile("" ::: "memory");
+      if (tt < t0 || 16 * tt >= n) continue;
+      double a[kWY / 4];
+#pragma unroll
+      for (int s = 0; s < kWY / 4; ++s)
+        a[s] = (4 * s + lq < kb && c < n) ? (Vj + (4 * s * n + 16 * tt))[off2] : 0.0;
+#pragma unroll
+      for (int s = 0; s < kWY / 4; ++s) z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b2[s], z[t], 0, 0, 0);
+    }
   }
-  for (int e = tid; e < rows * n; e += blockDim.x) Z[e] = zs[e];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int c = 16 * (wave + 4 * t) + 4 * lq;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (zrow < n && c + e < n) Z[c + e] = z[t][e];
+  }
 }
 
 }  // namespace
+
+hipError_t launch_wy_apply(const BatchEigProblem *probs, const BatchWyItem *items, int count, int max_n,
+                           hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>(count)), block(256);
+  if (max_n <= 512) hipLaunchKernelGGL(k_wy_apply<8>, grid, block, 0, s, probs, items);
+  else if (max_n <= 1024) hipLaunchKernelGGL(k_wy_apply<16>, grid, block, 0, s, probs, items);
+  else if (max_n <= 1536) hipLaunchKernelGGL(k_wy_apply<24>, grid, block, 0, s, probs, items);
+  else if (max_n <= kBatchEigMaxN) hipLaunchKernelGGL(k_wy_apply<32>, grid, block, 0, s, probs, items);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
 
 size_t batch_syev_lds_for(int max_n, int S) {
   return (4 * static_cast<size_t>(max_n) + kBWaves + kShiftSlots + 4 * static_cast<size_t>(S) * max_n) *
@@ -817,12 +889,7 @@ dacp_status batch_syev_raw_on(dacp_ctx ctx, int count, const int *n, double *con
       DACP_TRY(to_device(ctx, wk.items, all.data(), sizeof(WyItem) * all.size()));
       hipLaunchKernelGGL(k_wy_prep, dim3(static_cast<unsigned>(prep.size())), dim3(256), 0, st, wk.probs, wk.items);
       DACP_HIP(ctx, hipGetLastError());
-      const size_t lds = static_cast<size_t>(kRB) * max_n * sizeof(double);
-      DACP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_wy_apply),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-      hipLaunchKernelGGL(k_wy_apply, dim3(static_cast<unsigned>(apply.size())), dim3(256), lds, st, wk.probs,
-                         wk.items + prep.size());
-      DACP_HIP(ctx, hipGetLastError());
+      DACP_HIP(ctx, launch_wy_apply(wk.probs, wk.items + prep.size(), static_cast<int>(apply.size()), max_n, st));
     }
   }
   std::vector<int> status(count);

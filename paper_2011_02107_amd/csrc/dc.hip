@@ -24,6 +24,7 @@
 #include "host_rules.h"
 #include "internal.h"
 #include "secular.h"
+#include "wave.h"
 
 namespace dacp {
 
@@ -78,11 +79,7 @@ struct DcRows {
 struct WaveLanes {
   __device__ __forceinline__ int first() const { return threadIdx.x & 63; }
   __device__ __forceinline__ int stride() const { return 64; }
-  __device__ __forceinline__ double sum(double v) const {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-  }
+  __device__ __forceinline__ double sum(double v) const { return wave_sum(v); }
 };
 
 // Leaf eigenproblem, one wave each: implicit QR with a Wilkinson shift on the torn diagonal (every

@@ -1,9 +1,11 @@
-// Dense symmetric eigen-decomposition for the subspace problem (App. C):
-// Householder tridiagonalisation on the GPU, implicit symmetric QR with a
-// Wilkinson shift on the host (O(n^2) scalar work), and the QR rotations
-// replayed on the GPU onto the Householder Q.  Eigenvectors are returned as
-// rows (row j = eigenvector j), the layout in which the rotations of one QR
-// sweep stream through memory with every lane owning one column.
+// Dense symmetric eigen-decomposition for the subspace problem (App. C).  Up
+// to 2048 rows: tridiag.hip.  Beyond: Householder tridiagonalisation on the
+// GPU column by column (in panels from the "blocked" knob on), divide and
+// conquer (dc.hip) and the product with the Householder Q; with the "dc" knob
+// off, implicit symmetric QR with a Wilkinson shift on the host (O(n^2) scalar
+// work) and its rotations replayed on the GPU onto Q.  Eigenvectors are
+// returned as rows (row j = eigenvector j), the layout in which the rotations
+// of one QR sweep stream through memory with every lane owning one column.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -405,6 +407,10 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
     }
     return DACP_OK;
   }
+  // Up to 2048 rows the matrix stays in registers across the GPU (tridiag.hip), unless the knobs ask
+  // for the panel form or for implicit QR.
+  if (n <= kBatchEigMaxN && ctx->dc_min_n > 0 && !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB)))
+    return syev_jobs(ctx, {{n, A, ld, w, Zrows}});
   double *dv = nullptr, *dp = nullptr, *dd = nullptr, *de = nullptr, *db = nullptr;
   DACP_HIP(ctx, hipMalloc(&dv, sizeof(double) * n));
   DACP_HIP(ctx, hipMalloc(&dp, sizeof(double) * n));

@@ -161,6 +161,16 @@ struct BatchEigProblem {
   int n;
 };
 constexpr int kBatchEigMaxN = 2048;
+// Compact-WY back-transformation (beig.hip): reflectors per block, rows of Zr per workgroup, a work
+// item (reflector block or first row `at` of matrix `prob`), and Zr <- Zr Q^T from the blocks' V and T
+// in each problem's work (V n x n, then T block after block), max_n the largest n of the items.
+constexpr int kWY = 64;
+constexpr int kWyRows = 16;
+struct BatchWyItem {
+  int prob, at;
+};
+hipError_t launch_wy_apply(const BatchEigProblem *probs, const BatchWyItem *items, int count, int max_n,
+                           hipStream_t s);
 // dacp_central_eigs_batched calls with at most this many realisations use the per-problem
 // eigensolver on the finishing threads' streams instead of the batched launch.
 constexpr int kBatchEigMinCount = 8;
@@ -432,6 +442,16 @@ struct DcJob {
   double *Z, *work, *w;
 };
 size_t dc_work_doubles(int n);
+// Eigen-decompositions of matrices of up to 2048 rows (tridiag.hip): A device symmetric (row stride
+// lda, read only), w host ascending, Z device n x n (row j = eigenvector j) or null.  Waits for the
+// context's stream.
+struct SyevJob {
+  int n;
+  const double *A;
+  int64_t lda;
+  double *w, *Z;
+};
+dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &jobs);
 dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs);
 }  // namespace dacp
 
