@@ -108,19 +108,17 @@ dacp_status dacp_set_tile(dacp_ctx ctx, int tile_elems);
  *                 tiles dealt round-robin in launch order (default 2: high pass only)
  *   "batch_workers" host threads finishing the realisations of dacp_central_eigs_batched (1..64, default 16)
  *   "batch_eig"   dacp_central_eigs_batched: 1 = the finishing threads' dense eigen-decompositions are
- *                 collected and solved in batched launches when the call has more than 8
- *                 realisations (default; smaller calls, such as a retry round, solve each problem
- *                 on its thread's stream), 2 = batched launches always, 0 = one solver per
- *                 problem always
+ *                 collected and solved together when the call has more than one realisation
+ *                 (default), 2 = always, 0 = each problem on its thread's stream
  *   "moment_explicit" dacp_central_eigs and the batched calls with moment_mode 2: 1 = when the
  *                 certified core falls short of N, S and P of the same stored basis are formed
  *                 explicitly and solved again (by the per-problem eigensolver in a batched call)
  *                 before the window is widened (default); 2 = always after the moment solve;
  *                 0 = never
- *   "beig_pipe"   batched eigensolver: 1 = on unreduced blocks of 48 rows or more, the QR sweeps
+ *   "beig_pipe"   allocation-free batched eigensolver: 1 = on unreduced blocks of 48 rows or more, the QR sweeps
  *                 of a batch take their shifts at its start and are chased in lockstep, one lane
  *                 per sweep (default); 0 = one sweep after another
- *   "beig_sweeps" batched eigensolver: at most this many QR sweeps per batch, 1..8 (default 6;
+ *   "beig_sweeps" allocation-free batched eigensolver: at most this many QR sweeps per batch, 1..8 (default 6;
  *                 fewer where the rotation buffers would not fit the LDS)
  *   "group"       evolution column-group width when L >= 15 (power of two, default 8)
  *   "filter_group_f64", "filter_group_f32"
@@ -287,10 +285,10 @@ dacp_status dacp_rayleigh_ritz(dacp_ctx ctx, int m, const double *S, const doubl
  * destroyed; w host ascending; Zrows device n x n (row j = eigenvector j) or NULL. */
 dacp_status dacp_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows);
 
-/* The same decomposition for `count` matrices in one launch, one workgroup per matrix (App. C's
- * two eigen-decompositions for many small subspace problems, the batched-realisation path):
- * Householder tridiagonalisation, the tridiagonal's eigenvalues by bisection, implicit symmetric
- * QR shifted by the nearest of those not yet deflated (else Wilkinson's shift), Householder Q.
+/* The same decomposition for `count` matrices together (App. C's two eigen-decompositions for many
+ * small subspace problems, the batched-realisation path): Householder tridiagonalisation, divide
+ * and conquer, and the reflectors applied to the eigenvectors, each in launches shared by all
+ * matrices.  Device memory besides A and Z: about 4 sum n[i]^2 doubles during the call.
  * n[i] (host): 1 <= n[i] <= 2048.  A[i] (host array of device pointers): symmetric n[i] x n[i],
  * row-major, ld n[i], destroyed.  w[i] (host array of host pointers): n[i] eigenvalues ascending.
  * Z[i] (host array of device pointers, entries may be NULL): n[i] x n[i], row j = eigenvector j.
@@ -299,8 +297,10 @@ dacp_status dacp_syev_batched(dacp_ctx ctx, int count, const int *n, double *con
                               double *const *Z);
 
 /* dacp_syev_batched that allocates nothing, for callers that cannot allocate device memory (code
- * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same arguments,
- * results and errors as dacp_syev_batched (same kernels).  Every device buffer besides A[i] and
+ * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same arguments
+ * and errors as dacp_syev_batched, the same results up to rounding: one workgroup per matrix runs
+ * Householder tridiagonalisation, bisection for the QR shifts and implicit symmetric QR, which need
+ * less scratch.  Every device buffer besides A[i] and
  * Z[i] -- the tridiagonal's eigenvectors, the Householder product, w and beta per matrix, the
  * convergence flags, the problem table and the sort permutation -- lives in one fixed workspace of
  * 128 MiB per device, held from the library's first use on that device until the process ends.  A

@@ -1,6 +1,6 @@
-// Batched dense symmetric eigensolver for many small subspace problems (App. C, one workgroup per
-// matrix).  The per-problem solver of eig.hip issues several kernels per column and is bound by
-// launches at n of a few hundred; here one launch covers every problem of a batch:
+// The allocation-free batched eigensolver (dacp_syev_batched_noalloc): one workgroup per matrix, with
+// two n x n buffers besides the matrix itself (the solver of tridiag.hip, which the other entry
+// points take, needs four).  One launch covers every problem of a batch:
 //   1. Householder tridiagonalisation in place (one column per step, the step's vectors in LDS;
 //      each step's rank-2 update is applied in the next step's pass over the trailing block);
 //   2. every eigenvalue of the tridiagonal by bisection, one per thread, for the QR shifts;
@@ -930,76 +930,6 @@ size_t batch_syev_items(int count, const int *n) {
   for (int i = 0; i < count; ++i)
     if (n[i] > 2) k += (static_cast<size_t>(n[i]) - 2 + kWY - 1) / kWY + (static_cast<size_t>(n[i]) + kRB - 1) / kRB;
   return std::max<size_t>(k, 1);
-}
-
-// Host side, first half: launches over `count` matrices A[i] (device, n[i] x n[i], ld n[i],
-// destroyed); w[i] (host) receives the eigenvalues, unsorted; Zr[i] (device, n x n) the eigenvectors
-// of A[i] as rows in the same order when work[i] (device, batch_syev_work_doubles(n[i]) doubles) is
-// given (work null: Zr holds the tridiagonal's eigenvectors only).
-dacp_status batch_syev_raw(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *Zr,
-                           double *const *work, double *const *w) {
-  if (count <= 0) return DACP_OK;
-  size_t total = 0;
-  for (int i = 0; i < count; ++i) {
-    if (n[i] < 1 || n[i] > kBatchEigMaxN) return set_err(ctx, DACP_E_INVALID, "batch_syev: 1 <= n <= 2048");
-    total += static_cast<size_t>(n[i]);
-  }
-  DevBuf wbuf, dprobs, dstat, ditems;
-  DACP_HIP(ctx, wbuf.alloc(total * sizeof(double)));
-  DACP_HIP(ctx, dstat.alloc(sizeof(int) * count));
-  DACP_HIP(ctx, dprobs.alloc(sizeof(BatchEigProblem) * count));
-  DACP_HIP(ctx, ditems.alloc(sizeof(WyItem) * batch_syev_items(count, n)));
-  BatchEigWork wk;
-  wk.wb = wbuf.as<double>();
-  wk.stat = dstat.as<int>();
-  wk.probs = dprobs.as<BatchEigProblem>();
-  wk.items = ditems.as<WyItem>();
-  return batch_syev_raw_on(ctx, count, n, A, Zr, work, w, wk);
-}
-
-// Second half, for one matrix on the caller's stream: eigenvalues ascending into w_out and, if
-// Zrows is set, the rows of Zr (eigenvectors of A from batch_syev_raw with work) in that order.
-dacp_status batch_syev_finish(dacp_ctx ctx, int n, const double *w_raw, const double *Zr, double *w_out,
-                              double *Zrows) {
-  DevBuf dperm;
-  if (Zrows) DACP_HIP(ctx, dperm.alloc(sizeof(int) * n));
-  return batch_syev_finish_on(ctx, n, w_raw, Zr, w_out, Zrows, dperm.as<int>());
-}
-
-// Both halves: eigen-decompositions of `count` symmetric matrices A[i] (device, n[i] x n[i], ld n[i],
-// destroyed) in one launch.  w[i] (host) ascending; Zrows[i] (device, n x n) row j = eigenvector j.
-dacp_status batch_syev(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
-                       double *const *Zrows) {
-  if (count <= 0) return DACP_OK;
-  size_t total = 0;
-  std::vector<size_t> off(count);
-  for (int i = 0; i < count; ++i) {
-    if (n[i] < 1 || n[i] > kBatchEigMaxN) return set_err(ctx, DACP_E_INVALID, "batch_syev: 1 <= n <= 2048");
-    off[i] = total;
-    total += static_cast<size_t>(n[i]) * n[i];
-  }
-  bool vectors = false;
-  size_t wtotal = 0;
-  std::vector<size_t> woff(count);
-  for (int i = 0; i < count; ++i) {
-    vectors = vectors || Zrows[i] != nullptr;
-    woff[i] = wtotal;
-    wtotal += batch_syev_work_doubles(n[i]);
-  }
-  DevBuf scratch_z, scratch_w;
-  DACP_HIP(ctx, scratch_z.alloc(total * sizeof(double)));
-  if (vectors) DACP_HIP(ctx, scratch_w.alloc(wtotal * sizeof(double)));
-  std::vector<double *> zr(count), wk(count), wr(count);
-  std::vector<std::vector<double>> wraw(count);
-  for (int i = 0; i < count; ++i) {
-    zr[i] = scratch_z.as<double>() + off[i];
-    wk[i] = vectors ? scratch_w.as<double>() + woff[i] : nullptr;
-    wraw[i].resize(n[i]);
-    wr[i] = wraw[i].data();
-  }
-  DACP_TRY(batch_syev_raw(ctx, count, n, A, zr.data(), vectors ? wk.data() : nullptr, wr.data()));
-  for (int i = 0; i < count; ++i) DACP_TRY(batch_syev_finish(ctx, n[i], wr[i], zr[i], w[i], Zrows[i]));
-  return DACP_OK;
 }
 
 // ------------------------------------------------------------------ allocation-free form

@@ -64,19 +64,6 @@ void vlog(const char *fmt, ...) {
   va_end(ap);
 }
 
-// fn(i) for i in [0, count) on up to `threads` host threads (thread t takes i = t, t + threads, ...).
-template <typename F>
-void host_parallel(int count, int threads, F fn) {
-  threads = std::max(1, std::min(threads, count));
-  std::vector<std::thread> ts;
-  for (int t = 1; t < threads; ++t)
-    ts.emplace_back([&, t] {
-      for (int i = t; i < count; i += threads) fn(i);
-    });
-  for (int i = 0; i < count; i += threads) fn(i);
-  for (auto &th : ts) th.join();
-}
-
 AllocState &alloc_state_tl() {
   static thread_local AllocState st;
   return st;
@@ -2124,7 +2111,9 @@ dacp_status dacp_syev_batched(dacp_ctx ctx, int count, const int *n, double *con
   for (int i = 0; i < count; ++i)
     if (n[i] < 1 || n[i] > dacp::kBatchEigMaxN || !A[i] || !w[i])
       return set_err(ctx, DACP_E_INVALID, "syev_batched: need 1 <= n <= 2048 and A, w for every matrix");
-  return dacp::batch_syev(ctx, count, n, A, w, Z);
+  std::vector<dacp::SyevJob> jobs;
+  for (int i = 0; i < count; ++i) jobs.push_back({n[i], A[i], n[i], w[i], Z[i]});
+  return dacp::syev_jobs(ctx, jobs);
 }
 
 dacp_status dacp_syev_batched_noalloc(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
@@ -2733,10 +2722,9 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
 
 // The dense eigen-decompositions of the threads that finish batched realisations, solved together:
 // each thread hands in all of its pending problems (possibly none) and waits; once every running
-// thread has arrived the batch's reductions and QR iterations run as one launch (one workgroup per
-// matrix), a new round starts, and each thread then forms its own eigenvectors (a GEMM and a row
-// gather per problem) on its own stream.  Problems above the batched solver's size limit go
-// through the per-problem solver.
+// thread has arrived the last one solves the whole round (syev_jobs: every stage one launch or a few
+// for all of its matrices) and a new round starts.  Problems above that solver's size limit go
+// through the per-problem one.
 class EigRendezvous {
  public:
   struct Req {
@@ -2749,51 +2737,32 @@ class EigRendezvous {
   ~EigRendezvous() {
     if (stream_) (void)hipStreamDestroy(stream_);
   }
-  // The matrices of reqs are complete at the current end of ctx's stream: the round's launch, on
-  // the rendezvous' own stream, waits for that point through an event.
+  // The matrices of reqs are complete at the current end of ctx's stream: the round's launches, on
+  // the rendezvous' own stream, wait for that point through an event.  Results are complete on return.
   dacp_status solve_many(dacp_ctx ctx, const std::vector<Req> &reqs) {
     dacp_status big = DACP_OK;
     Arrival me;
     me.ctx = ctx;
-    size_t scratch = 0;
     for (const Req &r : reqs) {
-      if (r.n <= dacp::kBatchEigMaxN) {
-        me.reqs.push_back(r);
-        scratch += static_cast<size_t>(r.n) * r.n + dacp::batch_syev_work_doubles(r.n);
-      } else if (big == DACP_OK) {
-        big = dacp::gpu_syev(ctx, r.n, r.A, r.n, r.w, r.Z);
-      }
-    }
-    dacp::DevBuf zq;
-    hipError_t e = zq.alloc(std::max<size_t>(scratch, 1) * sizeof(double));
-    size_t off = 0;
-    for (const Req &r : me.reqs) {
-      me.zr.push_back(e == hipSuccess ? zq.as<double>() + off : nullptr);
-      me.work.push_back(e == hipSuccess ? zq.as<double>() + off + static_cast<size_t>(r.n) * r.n : nullptr);
-      me.wraw.emplace_back(r.n);
-      off += static_cast<size_t>(r.n) * r.n + dacp::batch_syev_work_doubles(r.n);
+      if (r.n <= dacp::kBatchEigMaxN) me.jobs.push_back({r.n, r.A, r.n, r.w, r.Z});
+      else if (big == DACP_OK) big = dacp::gpu_syev(ctx, r.n, r.A, r.n, r.w, r.Z);
     }
     hipEvent_t ev = nullptr;
-    if (e == hipSuccess && !stream_) e = hipErrorInvalidResourceHandle;
+    hipError_t e = stream_ ? hipSuccess : hipErrorInvalidResourceHandle;
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(ev, ctx->stream);
     if (e == hipSuccess) me.ready = ev;
     {
       std::unique_lock<std::mutex> lk(mu_);
-      if (e != hipSuccess) me.reqs.clear();  // still arrive, so that the others are not held up
+      if (e != hipSuccess) me.jobs.clear();  // still arrive, so that the others are not held up
       arrived_.push_back(&me);
       const long gen = generation_;
       if (static_cast<int>(arrived_.size()) == active_) run_locked(ctx);
       else cv_.wait(lk, [&] { return generation_ != gen; });
     }
     if (ev) (void)hipEventDestroy(ev);  // the launch's wait on it is enqueued
-    if (e != hipSuccess) return hip_err(ctx, e, "batched eigensolver: scratch, stream or event");
-    if (me.st != DACP_OK) return me.st;
-    for (size_t i = 0; i < me.reqs.size(); ++i) {
-      const Req &r = me.reqs[i];
-      DACP_TRY(dacp::batch_syev_finish(ctx, r.n, me.wraw[i].data(), me.zr[i], r.w, r.Z));
-    }
-    return big;
+    if (e != hipSuccess) return hip_err(ctx, e, "batched eigensolver: stream or event");
+    return me.st != DACP_OK ? me.st : big;
   }
   // this thread has no further problems
   void leave(dacp_ctx ctx) {
@@ -2805,9 +2774,7 @@ class EigRendezvous {
  private:
   struct Arrival {
     dacp_ctx ctx = nullptr;
-    std::vector<Req> reqs;
-    std::vector<double *> zr, work;
-    std::vector<std::vector<double>> wraw;
+    std::vector<dacp::SyevJob> jobs;
     hipEvent_t ready = nullptr;
     dacp_status st = DACP_OK;
   };
@@ -2828,40 +2795,21 @@ class EigRendezvous {
     cv_.notify_all();
   }
   dacp_status launch_round(dacp_ctx ctx) {
-    std::vector<int> n;
-    std::vector<double *> A, zr, work, w;
-    for (Arrival *a : arrived_)
-      for (size_t i = 0; i < a->reqs.size(); ++i) {
-        n.push_back(a->reqs[i].n);
-        A.push_back(a->reqs[i].A);
-        zr.push_back(a->zr[i]);
-        work.push_back(a->work[i]);
-        w.push_back(a->wraw[i].data());
-      }
-    dacp_status st = DACP_OK;
-    if (!n.empty()) {
-      // the launch goes on the rendezvous' own stream, after every arrival's event; the leader's
-      // context lends its error slot, its buffers come from the cache ordered on that stream
-      dacp::AllocStream scope(stream_, device_);
-      const hipStream_t own = ctx->stream;
-      ctx->stream = stream_;
-      for (const Arrival *a : arrived_)
-        if (a->ready && st == DACP_OK) {
-          const hipError_t e = hipStreamWaitEvent(stream_, a->ready, 0);
-          if (e != hipSuccess) st = hip_err(ctx, e, "batched eigensolver: wait");
-        }
-      if (st == DACP_OK) {
-        try {
-          st = dacp::batch_syev_raw(ctx, static_cast<int>(n.size()), n.data(), A.data(), zr.data(), work.data(),
-                                    w.data());
-        } catch (...) {
-          ctx->stream = own;
-          throw;
-        }
-      }
-      ctx->stream = own;
-    }
-    return st;
+    std::vector<dacp::SyevJob> jobs;
+    for (Arrival *a : arrived_) jobs.insert(jobs.end(), a->jobs.begin(), a->jobs.end());
+    if (jobs.empty()) return DACP_OK;
+    // the launches go on the rendezvous' own stream, after every arrival's event; the leader's
+    // context lends its error slot, its buffers come from the cache ordered on that stream
+    dacp::AllocStream scope(stream_, device_);
+    struct OwnStream {
+      dacp_ctx c;
+      hipStream_t own;
+      ~OwnStream() { c->stream = own; }
+    } restore{ctx, ctx->stream};
+    ctx->stream = stream_;
+    for (const Arrival *a : arrived_)
+      if (a->ready) DACP_HIP(ctx, hipStreamWaitEvent(stream_, a->ready, 0));
+    return dacp::syev_jobs(ctx, jobs);
   }
   std::mutex mu_;
   std::condition_variable cv_;

@@ -549,7 +549,9 @@ dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
     DcRot *rots = reinterpret_cast<DcRot *>(blob.data() + o_rot);
     int nrot = 0, max_k = 0;
     std::vector<int> flag, dorder;
-    for (size_t i = 0; i < nodes.size(); ++i) {
+    // the merges' deflations are independent: over host threads when there is work for them
+    std::vector<rules::DcDeflation> dfs(nodes.size());
+    auto deflate = [&](int i) {
       DcMerge &M = ms[i];
       const int n = M.hi - M.lo, n1 = M.m - M.lo;
       const double beta = eh[woff[nodes[i].job] + M.m - 1];
@@ -563,12 +565,21 @@ dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
         if (q < n1 && beta < 0.0) z[q] = -z[q];
         zn += z[q] * z[q];
       }
-      if (!std::isfinite(zn) || !(zn > 0.0))
-        return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite update vector");
+      if (!std::isfinite(zn) || !(zn > 0.0)) {
+        M.rho = NAN;
+        return;
+      }
       zn = std::sqrt(zn);
       for (double &x : z) x /= zn;
       M.rho = std::fabs(beta) * zn * zn;
-      const rules::DcDeflation df = rules::dc_deflate(dv, z, M.rho, M.lo);
+      dfs[i] = rules::dc_deflate(dv, z, M.rho, M.lo);
+    };
+    host_parallel(static_cast<int>(nodes.size()), std::min(ctx->batch_workers, off / 4096), deflate);
+    for (size_t i = 0; i < nodes.size(); ++i) {
+      DcMerge &M = ms[i];
+      const int n = M.hi - M.lo, n1 = M.m - M.lo;
+      if (std::isnan(M.rho)) return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite update vector");
+      const rules::DcDeflation &df = dfs[i];
       // halves each row is supported on: its own, both once a rotation has mixed it
       flag.assign(n, 0);
       for (int q = 0; q < n; ++q) flag[q] = q < n1 ? 1 : 2;

@@ -3,9 +3,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/dacp.h"
@@ -171,12 +174,14 @@ struct BatchWyItem {
 };
 hipError_t launch_wy_apply(const BatchEigProblem *probs, const BatchWyItem *items, int count, int max_n,
                            hipStream_t s);
-// dacp_central_eigs_batched calls with at most this many realisations use the per-problem
-// eigensolver on the finishing threads' streams instead of the batched launch.
-constexpr int kBatchEigMinCount = 8;
+// dacp_central_eigs_batched calls with at most this many realisations solve each problem on its
+// finishing thread's stream instead of collecting them.
+constexpr int kBatchEigMinCount = 1;
 // pipe = 1: pipelined multishift batches on large blocks; max_sweeps caps the sweeps per batch.
 hipError_t launch_batch_syev(const BatchEigProblem *probs, int count, int max_n, hipStream_t s, int pipe,
                              int max_sweeps);
+// Doubles of BatchEigProblem::work for an n x n matrix: V (n x n) and the blocks' T.
+size_t batch_syev_work_doubles(int n);
 
 // Launch helpers (kernels.hip).
 template <typename T>
@@ -402,6 +407,22 @@ typedef dacp_ham_s::SplitOrder SplitOrder_t;
 }  // namespace dacp
 
 namespace dacp {
+// fn(i) for i in [0, count) on up to `threads` host threads, the caller among them (fewer, down to the
+// caller alone, when the system gives no more).
+template <typename F>
+void host_parallel(int count, int threads, F fn) {
+  std::atomic<int> next{0};
+  auto work = [&] {
+    for (int i = next++; i < count; i = next++) fn(i);
+  };
+  std::vector<std::thread> ts;
+  try {
+    for (int t = 1; t < std::min(threads, count); ++t) ts.emplace_back(work);
+  } catch (...) {
+  }
+  work();
+  for (auto &th : ts) th.join();
+}
 // Error helpers used by the API layer.
 dacp_status set_err(dacp_ctx ctx, dacp_status st, const std::string &msg);
 dacp_status hip_err(dacp_ctx ctx, hipError_t e, const char *what);
@@ -410,19 +431,6 @@ bool verbose();
 void vlog(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
 // Dense symmetric eigensolver (eig.hip).
 dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows);
-// Batched form (beig.hip): count matrices A[i] (device, n[i] x n[i], ld n[i], destroyed, n <= 2048)
-// in one launch; w[i] (host) ascending; Zrows[i] (device, n x n, may be null) row j = eigenvector j.
-dacp_status batch_syev(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
-                       double *const *Zrows);
-// Its two halves: the launches (Zr device n x n scratch per matrix, which receives the eigenvectors
-// of A as unsorted rows when work[i] gives batch_syev_work_doubles(n) device doubles; w host,
-// unsorted) and, per matrix on the caller's stream, the sort and the gather of Zr's rows into Zrows
-// in ascending order.
-dacp_status batch_syev_raw(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *Zr,
-                           double *const *work, double *const *w);
-dacp_status batch_syev_finish(dacp_ctx ctx, int n, const double *w_raw, const double *Zr, double *w_out,
-                              double *Zrows);
-size_t batch_syev_work_doubles(int n);
 // The allocation-free form (dacp_syev_batched_noalloc): every device buffer besides A and Zrows comes
 // from one fixed device array of kNoAllocScratchBytes per device (beig.hip).  noalloc_scratch_init
 // resolves that device's address once (call it with the device current); batch_syev_noalloc_bytes
