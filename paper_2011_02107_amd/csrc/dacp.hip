@@ -268,6 +268,39 @@ dacp_status split_order(dacp_ctx ctx, dacp_ham h, int lo_bits) {
   return DACP_OK;
 }
 
+// Tables of the on-chip column kernels (L <= 14): one coefficient per spin for the single-spin
+// sign-free flips, the other flips with the sign-free ones first.
+dacp_status onchip_order(dacp_ctx ctx, dacp_ham h) {
+  std::lock_guard<std::mutex> lock(h->tables_mu);
+  auto &oc = h->onchip;
+  if (oc.xc) return DACP_OK;
+  std::vector<double> xc(14, 0.0);
+  std::vector<FlipEntry> rest;
+  for (const FlipEntry &f : h->flips_host) {
+    if (f.zmask == 0 && (f.xmask & (f.xmask - 1)) == 0) xc[__builtin_ctz(f.xmask)] = f.coef;
+    else rest.push_back(f);
+  }
+  const auto mid =
+      std::stable_partition(rest.begin(), rest.end(), [](const FlipEntry &f) { return f.zmask == 0; });
+  // both tables in one allocation
+  const size_t bytes = 14 * sizeof(double) + rest.size() * sizeof(FlipEntry);
+  double *p = nullptr;
+  DACP_HIP(ctx, hipMalloc(&p, bytes));
+  FlipEntry *flips = reinterpret_cast<FlipEntry *>(p + 14);
+  hipError_t e = hipMemcpy(p, xc.data(), 14 * sizeof(double), hipMemcpyHostToDevice);
+  if (e == hipSuccess && !rest.empty())
+    e = hipMemcpy(flips, rest.data(), rest.size() * sizeof(FlipEntry), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    (void)hipFree(p);
+    return hip_err(ctx, e, "flip tables");
+  }
+  oc.flips = flips;
+  oc.nplain = static_cast<int>(mid - rest.begin());
+  oc.nflip = static_cast<int>(rest.size());
+  oc.xc = p;
+  return DACP_OK;
+}
+
 // Two-pass apply (low-bit tiles, then high-bit cosets), used when both tiles fit the budget.
 // Returns false (nothing launched) when the shape does not allow it.
 template <typename T>
@@ -2005,6 +2038,7 @@ void dacp_free_hamiltonian(dacp_ham h) {
   }
   for (auto &to : h->by_log2r)
     if (to.dev) (void)hipFree(to.dev);
+  if (h->onchip.xc) (void)hipFree(h->onchip.xc);
   if (h->d64) (void)hipFree(h->d64);
   if (h->d32) (void)hipFree(h->d32);
   if (h->flips) (void)hipFree(h->flips);
@@ -2598,15 +2632,16 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
   const int steps0 = o.lanczos_steps > 0 ? o.lanczos_steps : 80;
   const int M = o.kpm_moments > 1 ? o.kpm_moments : 256;
   const int nvec = o.kpm_vectors > 0 ? o.kpm_vectors : 8;
-  std::vector<DevBuf> v0(count), out(count), scr(count), R(count), mout(count), mscr(count);
+  std::vector<DevBuf> v0(count), out(count), R(count), mout(count);
   std::vector<BatchSpec> specs;
   std::vector<int> steps(count);
-  auto base_spec = [&](dacp_ham h, const dacp::SplitOrder_t &so) {
+  auto base_spec = [&](dacp_ham h) {
     BatchSpec c;
     std::memset(&c, 0, sizeof(c));
-    c.flips = so.lo;
-    c.nflip = so.nlo;
-    c.nplain = so.nlo_plain;
+    c.xc = h->onchip.xc;
+    c.flips = h->onchip.flips;
+    c.nflip = h->onchip.nflip;
+    c.nplain = h->onchip.nplain;
     c.d64 = h->d64;
     c.L = h->L;
     return c;
@@ -2617,15 +2652,13 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
       dacp_ham h = hams[r];
       const int64_t D = h->D;
       steps[r] = static_cast<int>(std::min<int64_t>(steps0, D));
-      DACP_TRY(split_order(ctx, h, h->L));
+      DACP_TRY(onchip_order(ctx, h));
       DACP_HIP(ctx, v0[r].alloc(D * sizeof(double)));
       DACP_HIP(ctx, dacp::launch_philox_gauss(v0[r].as<double>(), D, 1, o.seed ^ 0x5bd1e995ULL, ctx->stream));
-      DACP_HIP(ctx, out[r].alloc((2 * steps[r] + 1) * sizeof(double)));
-      if (h->L == 14) DACP_HIP(ctx, scr[r].alloc(D * sizeof(double)));
-      BatchSpec c = base_spec(h, h->split[h->L]);
+      DACP_HIP(ctx, out[r].alloc((2 * steps[r] + 2) * sizeof(double)));
+      BatchSpec c = base_spec(h);
       c.start = v0[r].as<double>();
       c.ld = 1;
-      c.scratch = scr[r].as<double>();
       c.out = out[r].as<double>();
       c.kind = 0;
       c.steps = steps[r];
@@ -2673,16 +2706,14 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
     for (int r = 0; r < count; ++r) {
       dacp_ham h = hams[r];
       const int64_t D = h->D;
-      DACP_TRY(split_order(ctx, h, h->L));
+      DACP_TRY(onchip_order(ctx, h));
       DACP_HIP(ctx, R[r].alloc(static_cast<size_t>(D) * nvec * sizeof(double)));
       DACP_HIP(ctx, dacp::launch_philox_gauss(R[r].as<double>(), D, nvec, o.seed ^ 0x2545f491ULL, ctx->stream));
       DACP_HIP(ctx, mout[r].alloc(static_cast<size_t>(M) * nvec * sizeof(double)));
-      if (h->L == 14) DACP_HIP(ctx, mscr[r].alloc(static_cast<size_t>(D) * nvec * sizeof(double)));
       for (int q = 0; q < nvec; ++q) {
-        BatchSpec c = base_spec(h, h->split[h->L]);
+        BatchSpec c = base_spec(h);
         c.start = R[r].as<double>() + q;
         c.ld = nvec;
-        c.scratch = h->L == 14 ? mscr[r].as<double>() + static_cast<int64_t>(D) * q : nullptr;
         c.out = mout[r].as<double>() + static_cast<int64_t>(M) * q;
         c.inv_e = 1.0 / e_bs[r];
         c.kind = 1;
@@ -2907,7 +2938,7 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
   const double t_setup = now_ms();
 
   // start blocks, bases and the column table of the persistent launch
-  std::vector<DevBuf> psi(count), vb(count), ksd(count), scr(count), ab(count), kad(count);
+  std::vector<DevBuf> psi(count), vb(count), ksd(count), ab(count), kad(count);
   // moment projection (moment_mode 2): panel orders on the uniform grid and the anchor orders
   const bool anchored = o.moment_mode == 2;
   std::vector<std::vector<int64_t>> orders_of(count), anchors_of(count);
@@ -2927,9 +2958,7 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
     DACP_HIP(ctx, vb[r].alloc(static_cast<size_t>(D) * pl.m * sizeof(double)));
     if (static_cast<double>(D) * pl.m * 8.0 >= 4294967296.0)
       return set_err(ctx, DACP_E_INVALID, "batched: basis of realisation " + std::to_string(r) + " exceeds 4 GiB");
-    if (h->L == 14) DACP_HIP(ctx, scr[r].alloc(static_cast<size_t>(2 * D) * pl.b * sizeof(double)));
-    DACP_TRY(split_order(ctx, h, h->L));  // every flip in one list, sign-free flips first
-    const auto &so = h->split[h->L];
+    DACP_TRY(onchip_order(ctx, h));
     std::vector<int64_t> ks64;
     if (anchored) {
       const MomentPlan mp = moment_plan(pl.a_r, pl.n);
@@ -2953,11 +2982,10 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
     for (int j = 0; j < pl.b; ++j) {
       BatchCol c;
       std::memset(&c, 0, sizeof(c));
-      c.flips = so.lo;
-      c.nflip = so.nlo;
-      c.nplain = so.nlo_plain;
-      c.scratch = h->L == 14 ? scr[r].as<double>() + static_cast<int64_t>(2 * D) * j : nullptr;
-      if (h->L == 14 && !c.scratch) return set_err(ctx, DACP_E_INVALID, "batched: missing column scratch");
+      c.xc = h->onchip.xc;
+      c.flips = h->onchip.flips;
+      c.nflip = h->onchip.nflip;
+      c.nplain = h->onchip.nplain;
       c.d64 = h->d64;
       c.d32 = h->d32;
       c.psi0 = psi[r].as<double>() + j;
@@ -3004,7 +3032,6 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
   std::vector<char> redo(count, 0);  // given windows only: realisations redone with Lanczos / KPM
   for (int r = 0; r < count; ++r) {
     psi[r].release();
-    scr[r].release();
     rep[r].t_evol_ms = t_batch;
     if (flag[r] && given) {
       redo[r] = 1;

@@ -118,15 +118,16 @@ struct RecArgs {
 
 // One column of one realisation for the batched persistent kernel (batch.hip).  Read by the
 // kernel through the scalar cache: the table is not written while the kernel runs.
+enum BatchMode { kBatchBoth = 0, kBatchFilter = 1, kBatchEvolve = 2 };
 struct BatchCol {
-  const FlipEntry *flips;  // the realisation's flip table, sign-free flips first (all applied from LDS)
+  const double *xc;        // 14 coefficients of sigma^x_b (0 where there is none)
+  const FlipEntry *flips;  // every other flip, sign-free ones first
   const double *d64;       // diagonal tables
   const float *d32;
   const double *psi0;      // start column: psi0[s * ld_psi]
   double *V;               // the realisation's basis shifted to this column: panel p at V[s * ldv + p * b]
   const int *ks;           // sample orders k_1 < ... < k_n (device)
   int *bound_flag;         // set to 1 when |T_k(G) psi_E| > 1 is seen (bound below ||H||)
-  double *scratch;         // 2 x 2^L doubles owned by this column (older recurrence terms at L = 14)
   double *A;               // anchors (moment projection) shifted to this column: anchor i at A[s * lda + i * b]
   const int *ka;           // anchor orders, ascending (device; n_anchor of them, 0 = none)
   int64_t ld_psi, ldv, lda;
@@ -134,17 +135,18 @@ struct BatchCol {
   double f_first_a, f_first_b;      // first order: T^_1 = a H (H psi) + b psi
   double inv_e;                     // 1 / E_b
   int L, nflip, nplain, K, n32, n_samples, b, n_anchor;  // flips[0, nplain) have z-mask 0
+  int mode;  // kBatchFilter: the filter alone, T^_K to panel 0 not normalised; kBatchEvolve: the evolution alone
 };
 hipError_t launch_batch_chebyshev(const BatchCol *cols, int ncols, int max_L, hipStream_t s);
 
 // One Lanczos run (kind 0) or one Chebyshev-moment vector (kind 1) of one realisation for the
 // batched spectral kernel (batch.hip); output layout documented there.
 struct BatchSpec {
-  const FlipEntry *flips;  // sign-free flips first
+  const double *xc;        // as in BatchCol
+  const FlipEntry *flips;
   const double *d64;
   const double *start;     // start vector: start[s * ld]
-  double *scratch;         // 2^L doubles at L = 14, else unused
-  double *out;             // kind 0: 2 steps + 1 doubles; kind 1: steps doubles
+  double *out;             // kind 0: 2 steps + 2 doubles; kind 1: steps doubles
   int64_t ld;
   double inv_e;            // kind 1: 1 / E_b
   int L, nflip, nplain, kind, steps;
@@ -401,11 +403,12 @@ struct dacp_ham_s {
     int nlo_plain = 0, nhi_plain = 0;  // leading z-mask-free entries of lo / of the pure part of hi
   };
   SplitOrder split[31];  // flip tables for the two-pass apply with lo_bits = index
+  struct OnChipOrder {
+    double *xc = nullptr;           // 14 coefficients of the single-spin sign-free flips, by spin
+    dacp::FlipEntry *flips = nullptr;  // the others, sign-free ones first
+    int nplain = 0, nflip = 0;
+  } onchip;                          // tables of the on-chip column kernels (L <= 14)
 };
-namespace dacp {
-typedef dacp_ham_s::SplitOrder SplitOrder_t;
-}  // namespace dacp
-
 namespace dacp {
 // fn(i) for i in [0, count) on up to `threads` host threads, the caller among them (fewer, down to the
 // caller alone, when the system gives no more).

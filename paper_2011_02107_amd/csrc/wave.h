@@ -7,12 +7,16 @@
 
 namespace dacp {
 
-// The value of `v` moved by a DPP control; lanes outside the row mask get 0.
+// The value of `v` moved by a DPP control; lanes outside the row mask get 0.  (With every row in the
+// mask nothing is left of the destination's old value, and the move needs none.)
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int dpp_move(int v) {
+  if constexpr (kRowMask == 0xf) return __builtin_amdgcn_mov_dpp(v, kCtrl, 0xf, 0xf, true);
+  else return __builtin_amdgcn_update_dpp(0, v, kCtrl, kRowMask, 0xf, false);
+}
 template <int kCtrl, int kRowMask>
 __device__ __forceinline__ double dpp_move(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRowMask, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRowMask, 0xf, false);
-  return __hiloint2double(hi, lo);
+  return __hiloint2double(dpp_move<kCtrl, kRowMask>(__double2hiint(v)), dpp_move<kCtrl, kRowMask>(__double2loint(v)));
 }
 
 // The same lane's value of the lane `lane` (uniform) in every lane.
