@@ -808,19 +808,19 @@ struct GraphRun {
 // or columns past ncols, only for a shape with a fused plan).
 //   store_of(k)       device pointer (row stride ldst) that the kernel writing T_k also fills with an
 //                     FP64 copy of its ncols columns, or null
-//   visit(k, T_k)     called once T_k is complete (the blocks of A's layout) for every k with want(k);
-//                     it may queue work on the context stream that reads T_k (queued before T_k's
-//                     buffer is reused)
+//   visit(k, T_k, T_{k-1})  called once T_k is complete (the blocks of A's layout; T_{k-1} null at
+//                     k = 0) for every k with want(k); it may queue work on the context stream that
+//                     reads them (queued before their buffers are reused)
 //   events(k1, k2)    whether a store or a visit falls on k1..k2 (such steps are not replayed from a
 //                     captured graph)
 dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, int gw, int groups, int ncols,
                          double *A, double *B, double *Pp, const std::function<double *(int64_t)> &store_of, int64_t ldst,
                          const std::function<bool(int64_t)> &want,
-                         const std::function<dacp_status(int64_t, const double *)> &visit,
+                         const std::function<dacp_status(int64_t, const double *, const double *)> &visit,
                          const std::function<bool(int64_t, int64_t)> &events, int64_t &launches) {
   const int64_t D = h->D;
   double *const A0 = A;
-  if (want(0)) DACP_TRY(visit(0, A));
+  if (want(0)) DACP_TRY(visit(0, A, nullptr));
   if (kmax < 1) return DACP_OK;
   dacp_status st = DACP_OK;
   const int64_t blk = D * gw;
@@ -833,7 +833,7 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
     if (s1 && !sy) DACP_HIP(ctx, dacp::launch_copy_cols(B + y * blk, gw, s1 + y * gw, ldst, D, nc, ctx->stream));
     ++launches;
   }
-  if (want(1)) DACP_TRY(visit(1, B));
+  if (want(1)) DACP_TRY(visit(1, B, A));
   const int64_t report_every = std::max<int64_t>(1, kmax / 8);
   int lo_bits = 0, hw = 1;
   if (kmax > 1 && fused_plan(ctx, h, gw, lo_bits, hw, 8)) {
@@ -925,7 +925,7 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
       ++k;
       ++launches;
       std::swap(A, B);
-      if (want(k)) DACP_TRY(visit(k, B));
+      if (want(k)) DACP_TRY(visit(k, B, A));
       if (verbose() && k % report_every == 0) {
         (void)hipStreamSynchronize(ctx->stream);
         vlog("evolution: step %lld of %lld (fused)", static_cast<long long>(k), static_cast<long long>(kmax));
@@ -939,7 +939,7 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
     if (st) return st;
     ++launches;
     std::swap(A, B);
-    if (want(k + 1)) DACP_TRY(visit(k + 1, B));
+    if (want(k + 1)) DACP_TRY(visit(k + 1, B, A));
     if (verbose() && (k + 1) % report_every == 0) {
       (void)hipStreamSynchronize(ctx->stream);
       vlog("evolution: step %lld of %lld", static_cast<long long>(k + 1), static_cast<long long>(kmax));
@@ -991,7 +991,7 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     };
     dacp_status st = evolve_group(
         ctx, h, inv_e, kmax, gw, groups, nc, A, B, pbuf.as<double>(), store_of, ldv, [](int64_t) { return false; },
-        [](int64_t, const double *) { return DACP_OK; }, panel_in, launches);
+        [](int64_t, const double *, const double *) { return DACP_OK; }, panel_in, launches);
     if (st) return st;
   }
   const double evol_ms = tm.stop_ms();
@@ -1140,7 +1140,7 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return k <= kmax && slot_of[k] >= 0; };
     // mu_k[:, g0 .. g0 + nc) = psi_E^T (T_k psi_E)[:, group by group], nu_k likewise with (G psi_E)^T
-    auto visit = [&](int64_t k, const double *tks) -> dacp_status {
+    auto visit = [&](int64_t k, const double *tks, const double *) -> dacp_status {
       for (int y = 0; y < groups; ++y) {
         const double *tk = tks + y * D * gw;
         const int yc = std::min(gw, nc - y * gw);
@@ -1244,7 +1244,7 @@ dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_param
     double *A = ba.as<double>(), *B = bb.as<double>();
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return panel_of.count(k) > 0; };
-    auto visit = [&](int64_t k, const double *tk) -> dacp_status {
+    auto visit = [&](int64_t k, const double *tk, const double *) -> dacp_status {
       const int pidx = panel_of[k];
       for (int y = 0; y < groups; ++y) {
         const int yc = std::min(gw, nc - y * gw);
@@ -1399,7 +1399,7 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
       return (k == 0 || it == panel_of.end()) ? nullptr : V + static_cast<int64_t>(it->second) * b + g0;
     };
     auto want = [&](int64_t k) { return anchor_of.count(k) > 0; };
-    auto visit = [&](int64_t k, const double *tk) -> dacp_status {
+    auto visit = [&](int64_t k, const double *tk, const double *) -> dacp_status {
       DACP_HIP(ctx, dacp::launch_join_cols(tk, D, gw, groups,
                                            abuf.as<double>() + static_cast<int64_t>(anchor_of[k]) * b + g0, 2 * ma, nc,
                                            s));
@@ -1641,99 +1641,170 @@ dacp_status lanczos_bound(dacp_ctx ctx, const std::vector<double> &al, const std
   return DACP_OK;
 }
 
+// Table entry of the on-chip spectral kernel for h (its flip tables built).
+BatchSpec spectral_spec(dacp_ham h, int kind, int steps, const double *start, int64_t ld, double *out) {
+  BatchSpec c;
+  std::memset(&c, 0, sizeof(c));
+  c.xc = h->onchip.xc;
+  c.flips = h->onchip.flips;
+  c.nflip = h->onchip.nflip;
+  c.nplain = h->onchip.nplain;
+  c.d64 = h->d64;
+  c.L = h->L;
+  c.kind = kind;
+  c.steps = steps;
+  c.start = start;
+  c.ld = ld;
+  c.out = out;
+  return c;
+}
+
+// Up to kOnChipL spins a column fits one compute unit, and a recurrence of single columns runs
+// there whole: one launch, where a step through memory is two to four of about 5 us each whatever
+// the size (an on-chip apply takes 5 us at 2^14 rows, under 2 at 2^11).
+constexpr int kOnChipL = 14;
+
 dacp_status run_bound(dacp_ctx ctx, dacp_ham h, int steps, const double *v0, uint64_t seed, double safety,
                       double *e_bound, double *tmin, double *tmax) {
   const int64_t D = h->D;
   if (steps < 1) return set_err(ctx, DACP_E_INVALID, "bound: steps >= 1");
   steps = static_cast<int>(std::min<int64_t>(steps, D));
-  DevBuf bv, bp, bw;
-  DACP_HIP(ctx, bv.alloc(D * sizeof(double)));
-  DACP_HIP(ctx, bp.alloc(D * sizeof(double)));
-  DACP_HIP(ctx, bw.alloc(D * sizeof(double)));
-  double *v = bv.as<double>(), *vp = bp.as<double>(), *w = bw.as<double>();
-  if (v0) DACP_HIP(ctx, hipMemcpyAsync(v, v0, D * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-  else DACP_HIP(ctx, dacp::launch_philox_gauss(v, D, 1, seed, ctx->stream));
-  double nv;
-  dacp_status st = coldots_host(ctx, v, 1, v, 1, DACP_F64, D, 1, &nv);
-  if (st) return st;
-  if (!(nv > 0.0)) return set_err(ctx, DACP_E_INVALID, "bound: zero start vector");
-  DACP_HIP(ctx, dacp::launch_axpby(v, v, 0.0, 1.0 / std::sqrt(nv), D, ctx->stream));
-  std::vector<double> al, be;
-  double bprev = 0.0;
-  for (int j = 0; j < steps; ++j) {
-    st = step<double>(ctx, h, 1, v, 1, w, 1, 1.0, j ? vp : nullptr, 1, -bprev);
-    if (st) return st;
-    double alpha;
-    st = coldots_host(ctx, w, 1, v, 1, DACP_F64, D, 1, &alpha);
-    if (st) return st;
-    DACP_HIP(ctx, dacp::launch_axpby(w, v, -alpha, 1.0, D, ctx->stream));
-    double nw;
-    st = coldots_host(ctx, w, 1, w, 1, DACP_F64, D, 1, &nw);
-    if (st) return st;
-    const double beta = std::sqrt(std::max(nw, 0.0));
-    al.push_back(alpha);
-    be.push_back(beta);
-    if (!std::isfinite(alpha) || !std::isfinite(beta)) return set_err(ctx, DACP_E_NUMERIC, "bound: non-finite Lanczos");
-    if (beta <= 1e-300 || j + 1 == steps) break;
-    DACP_HIP(ctx, dacp::launch_axpby(w, w, 0.0, 1.0 / beta, D, ctx->stream));
-    double *t = vp;
-    vp = v;
-    v = w;
-    w = t;
-    bprev = beta;
+  hipStream_t s = ctx->stream;
+  const bool onchip = h->L <= kOnChipL;
+  DevBuf bv, bp, bw, bs, dspec;
+  const double *start = v0;
+  if (!v0 || !onchip) {
+    DACP_HIP(ctx, bv.alloc(D * sizeof(double)));
+    if (v0) DACP_HIP(ctx, hipMemcpyAsync(bv.p, v0, D * sizeof(double), hipMemcpyDeviceToDevice, s));
+    else DACP_HIP(ctx, dacp::launch_philox_gauss(bv.as<double>(), D, 1, seed, s));
+    start = bv.as<double>();
   }
+  std::vector<double> al, be;
+  int taken = steps;
+  double nv = 0.0;
+  if (onchip) {
+    DACP_TRY(onchip_order(ctx, h));
+    DACP_HIP(ctx, bs.alloc((2 * steps + 2) * sizeof(double)));
+    DACP_HIP(ctx, dspec.alloc(sizeof(BatchSpec)));
+    const BatchSpec c = spectral_spec(h, 0, steps, start, 1, bs.as<double>());
+    DACP_TRY(to_device(ctx, dspec.p, &c, sizeof(c)));
+    DACP_HIP(ctx, dacp::launch_batch_spectral(dspec.as<BatchSpec>(), 1, h->L, s));
+    std::vector<double> out(2 * steps + 2);
+    DACP_TRY(to_host(ctx, out.data(), bs.p, out.size() * sizeof(double)));
+    nv = out[2 * steps + 1];
+    taken = static_cast<int>(out[2 * steps]);
+    al.assign(out.begin(), out.begin() + steps);
+    be.assign(out.begin() + steps, out.begin() + 2 * steps);
+  } else {
+    const int nb = dacp::scalar_blocks(D);
+    DACP_HIP(ctx, bp.alloc(D * sizeof(double)));
+    DACP_HIP(ctx, bw.alloc(D * sizeof(double)));
+    DACP_HIP(ctx, bs.alloc((2 * steps + 2 * nb) * sizeof(double)));
+    double *u = bv.as<double>(), *up = bp.as<double>(), *y = bw.as<double>();
+    double *alpha = bs.as<double>(), *norms = alpha + steps, *pb = norms + steps, *pa = pb + nb;
+    DACP_HIP(ctx, dacp::launch_sumsq(u, D, pb, s));
+    for (int j = 0; j < steps; ++j) {
+      DACP_TRY(step<double>(ctx, h, 1, u, 1, y, 1, 1.0));
+      DACP_HIP(ctx, dacp::launch_lanczos_step(y, u, up, D, j, norms, alpha, pa, pb, s));
+      std::swap(u, up);
+    }
+    std::vector<double> out(2 * steps + nb);
+    DACP_TRY(to_host(ctx, out.data(), bs.p, out.size() * sizeof(double)));
+    double last = 0.0;
+    for (int q = 0; q < nb; ++q) last += out[2 * steps + q];
+    al.assign(out.begin(), out.begin() + steps);
+    be.assign(out.begin() + steps + 1, out.begin() + 2 * steps);  // beta_(j+1) couples v_j and v_(j+1)
+    be.push_back(std::sqrt(std::max(last, 0.0)));
+    nv = out[steps] * out[steps];
+  }
+  if (!(nv > 0.0)) return set_err(ctx, DACP_E_INVALID, "bound: zero start vector");
+  // the recurrence ends at the first vanishing residual; what the device computed past it is unused
+  int k = 0;
+  while (k < taken) {
+    if (!std::isfinite(al[k]) || !std::isfinite(be[k])) return set_err(ctx, DACP_E_NUMERIC, "bound: non-finite Lanczos");
+    ++k;
+    if (be[k - 1] <= 1e-300) break;
+  }
+  al.resize(k);
+  be.resize(k);
   return lanczos_bound(ctx, al, be, safety, h->sum_abs, e_bound, tmin, tmax);
 }
 
 // ----------------------------------------------------------- KPM moments
+// d[2 k] = <T_k R, T_k R> and d[2 k + 1] = <T_k R, T_(k-1) R> summed over the nvec columns, k = 0 .. M / 2.
+dacp_status moment_dots(dacp_ctx ctx, dacp_ham h, double e_bound, int M, int nvec, const double *r,
+                        std::vector<double> &d) {
+  const int64_t D = h->D;
+  hipStream_t s = ctx->stream;
+  const int kmax = M / 2;
+  d.assign(2 * kmax + 2, 0.0);
+  if (h->L <= kOnChipL) {
+    DACP_TRY(onchip_order(ctx, h));
+    DevBuf dout, dspec;
+    DACP_HIP(ctx, dout.alloc(static_cast<size_t>(M) * nvec * sizeof(double)));
+    DACP_HIP(ctx, dspec.alloc(sizeof(BatchSpec) * nvec));
+    std::vector<BatchSpec> specs;
+    for (int q = 0; q < nvec; ++q) {
+      specs.push_back(spectral_spec(h, 1, M, r + q, nvec, dout.as<double>() + static_cast<size_t>(M) * q));
+      specs.back().inv_e = 1.0 / e_bound;
+    }
+    DACP_TRY(to_device(ctx, dspec.p, specs.data(), sizeof(BatchSpec) * nvec));
+    DACP_HIP(ctx, dacp::launch_batch_spectral(dspec.as<BatchSpec>(), nvec, h->L, s));
+    std::vector<double> out(static_cast<size_t>(M) * nvec);
+    DACP_TRY(to_host(ctx, out.data(), dout.p, out.size() * sizeof(double)));
+    for (int q = 0; q < nvec; ++q)  // entry i: <T_k, T_k> at i = 2 k, <T_(k+1), T_k> at i = 2 k + 1
+      for (int i = 0; i < M; ++i) d[(i & 1) ? i + 2 : i] += out[static_cast<size_t>(q) * M + i];
+    return DACP_OK;
+  }
+  const ColGroups cg = column_groups(ctx, h, nvec, recurrence_group(ctx, h, nvec), 3, {8});
+  DevBuf ba, bb, bp, part, sums;
+  DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, bp.alloc(cg.elems(D) * sizeof(double)));
+  DACP_HIP(ctx, part.alloc(2 * static_cast<size_t>(kmax + 1) * 256 * sizeof(double)));
+  DACP_HIP(ctx, sums.alloc(2 * static_cast<size_t>(kmax + 1) * sizeof(double)));
+  std::vector<double> got(2 * kmax + 2);
+  int64_t launches = 0;
+  for (int g0 = 0; g0 < nvec; g0 += cg.g * cg.per) {
+    const int nc = cg.cols(g0, nvec), gw = cg.width(nc), groups = cg.groups(nc);
+    const int64_t n = D * gw * groups;  // zero columns add nothing
+    const int nb = dacp::scalar_blocks(n);
+    DACP_HIP(ctx, dacp::launch_split_cols(r + g0, nvec, nc, ba.as<double>(), D, gw, groups, s));
+    auto visit = [&](int64_t k, const double *tk, const double *tk1) -> dacp_status {
+      DACP_HIP(ctx, dacp::launch_dot_pair(tk, tk1, n, part.as<double>() + 2 * nb * k, s));
+      return DACP_OK;
+    };
+    DACP_TRY(evolve_group(
+        ctx, h, 1.0 / e_bound, kmax, gw, groups, nc, ba.as<double>(), bb.as<double>(), bp.as<double>(),
+        [](int64_t) -> double * { return nullptr; }, 0, [](int64_t) { return true; }, visit,
+        [](int64_t, int64_t) { return true; }, launches));
+    DACP_HIP(ctx, dacp::launch_sum_pairs(part.as<double>(), kmax + 1, n, sums.as<double>(), s));
+    DACP_TRY(to_host(ctx, got.data(), sums.p, got.size() * sizeof(double)));
+    for (size_t i = 0; i < got.size(); ++i) d[i] += got[i];
+  }
+  return DACP_OK;
+}
+
 dacp_status run_moments(dacp_ctx ctx, dacp_ham h, double e_bound, int M, int nvec, const double *R, uint64_t seed,
                         double *mu) {
   const int64_t D = h->D;
   if (M < 1 || nvec < 1 || !(e_bound > 0.0)) return set_err(ctx, DACP_E_INVALID, "moments: bad arguments");
-  const size_t blk = static_cast<size_t>(D) * nvec;
-  DevBuf br, b0, b1;
+  DevBuf br;
   const double *r = R;
   if (!r) {
-    DACP_HIP(ctx, br.alloc(blk * sizeof(double)));
+    DACP_HIP(ctx, br.alloc(static_cast<size_t>(D) * nvec * sizeof(double)));
     DACP_HIP(ctx, dacp::launch_philox_gauss(br.as<double>(), D, nvec, seed, ctx->stream));
     r = br.as<double>();
   }
-  DACP_HIP(ctx, b0.alloc(blk * sizeof(double)));
-  DACP_HIP(ctx, b1.alloc(blk * sizeof(double)));
-  std::vector<double> c(nvec);
-  auto total = [&](const double *x, const double *y, double &out) -> dacp_status {
-    dacp_status st = coldots_host(ctx, x, nvec, y, nvec, DACP_F64, D, nvec, c.data());
-    out = 0.0;
-    for (double v : c) out += v;
-    return st;
-  };
-  double n0;
-  dacp_status st = total(r, r, n0);
-  if (st) return st;
+  std::vector<double> d;
+  DACP_TRY(moment_dots(ctx, h, e_bound, M, nvec, r, d));
+  // mu_{2k} = 2 <T_k r, T_k r> - mu_0,  mu_{2k+1} = 2 <T_{k+1} r, T_k r> - mu_1
+  const double n0 = d[0];
   mu[0] = 1.0;
-  if (M == 1) return DACP_OK;
-  double *A = b0.as<double>(), *B = b1.as<double>();
-  DACP_HIP(ctx, dacp::launch_copy_cols(r, nvec, A, nvec, D, nvec, ctx->stream));
-  st = step<double>(ctx, h, nvec, A, nvec, B, nvec, 1.0 / e_bound);  // B = T_1 r
-  if (st) return st;
-  double m1;
-  st = total(r, B, m1);
-  if (st) return st;
-  mu[1] = m1 / n0;
-  // A = T_{k-1} r, B = T_k r (k = 1):  mu_{2k} = 2 <T_k r, T_k r> - mu_0,  mu_{2k+1} = 2 <T_{k+1} r, T_k r> - mu_1
+  if (M > 1) mu[1] = d[3] / n0;
   for (int k = 1; 2 * k < M; ++k) {
-    double tkk;
-    st = total(B, B, tkk);
-    if (st) return st;
-    mu[2 * k] = 2.0 * tkk / n0 - mu[0];
-    if (2 * k + 1 >= M) break;
-    st = step<double>(ctx, h, nvec, B, nvec, A, nvec, 2.0 / e_bound, nullptr, 0, 0.0, A, nvec, -1.0);
-    if (st) return st;
-    std::swap(A, B);  // B = T_{k+1} r, A = T_k r
-    double tk1k;
-    st = total(B, A, tk1k);
-    if (st) return st;
-    mu[2 * k + 1] = 2.0 * tk1k / n0 - mu[1];
+    mu[2 * k] = 2.0 * d[2 * k] / n0 - mu[0];
+    if (2 * k + 1 < M) mu[2 * k + 1] = 2.0 * d[2 * k + 3] / n0 - mu[1];
   }
   return DACP_OK;
 }
@@ -2635,17 +2706,6 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
   std::vector<DevBuf> v0(count), out(count), R(count), mout(count);
   std::vector<BatchSpec> specs;
   std::vector<int> steps(count);
-  auto base_spec = [&](dacp_ham h) {
-    BatchSpec c;
-    std::memset(&c, 0, sizeof(c));
-    c.xc = h->onchip.xc;
-    c.flips = h->onchip.flips;
-    c.nflip = h->onchip.nflip;
-    c.nplain = h->onchip.nplain;
-    c.d64 = h->d64;
-    c.L = h->L;
-    return c;
-  };
   const double tl0 = now_ms();
   if (!(o.e_bound > 0.0)) {
     for (int r = 0; r < count; ++r) {
@@ -2656,13 +2716,7 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
       DACP_HIP(ctx, v0[r].alloc(D * sizeof(double)));
       DACP_HIP(ctx, dacp::launch_philox_gauss(v0[r].as<double>(), D, 1, o.seed ^ 0x5bd1e995ULL, ctx->stream));
       DACP_HIP(ctx, out[r].alloc((2 * steps[r] + 2) * sizeof(double)));
-      BatchSpec c = base_spec(h);
-      c.start = v0[r].as<double>();
-      c.ld = 1;
-      c.out = out[r].as<double>();
-      c.kind = 0;
-      c.steps = steps[r];
-      specs.push_back(c);
+      specs.push_back(spectral_spec(h, 0, steps[r], v0[r].as<double>(), 1, out[r].as<double>()));
     }
     DevBuf dspecs;
     DACP_HIP(ctx, dspecs.alloc(sizeof(BatchSpec) * specs.size()));
@@ -2711,14 +2765,9 @@ dacp_status batched_estimates(dacp_ctx ctx, int count, const dacp_ham *hams, con
       DACP_HIP(ctx, dacp::launch_philox_gauss(R[r].as<double>(), D, nvec, o.seed ^ 0x2545f491ULL, ctx->stream));
       DACP_HIP(ctx, mout[r].alloc(static_cast<size_t>(M) * nvec * sizeof(double)));
       for (int q = 0; q < nvec; ++q) {
-        BatchSpec c = base_spec(h);
-        c.start = R[r].as<double>() + q;
-        c.ld = nvec;
-        c.out = mout[r].as<double>() + static_cast<int64_t>(M) * q;
-        c.inv_e = 1.0 / e_bs[r];
-        c.kind = 1;
-        c.steps = M;
-        specs.push_back(c);
+        specs.push_back(spectral_spec(h, 1, M, R[r].as<double>() + q, nvec,
+                                      mout[r].as<double>() + static_cast<int64_t>(M) * q));
+        specs.back().inv_e = 1.0 / e_bs[r];
       }
     }
     DevBuf dspecs;

@@ -219,7 +219,18 @@ hipError_t launch_philox_gauss(double *out, int64_t D, int b, uint64_t seed, hip
 // Columns j < b_even of the [D][b] block <- psi + P psi, the others psi - P psi, P the global spin
 // flip (s -> s ^ (D - 1)).
 hipError_t launch_parity_split(double *psi, int64_t D, int b, int b_even, hipStream_t s);
-hipError_t launch_axpby(double *y, const double *x, double a, double bcoef, int64_t n, hipStream_t s);
+// Recurrence scalars kept on the device (kernels.hip): partial sums of scalar_blocks(n) workgroups.
+//   launch_sumsq         part[blk] of |x|^2
+//   launch_lanczos_step  step j: y = H u on entry; up = u_(j-1) becomes u_(j+1); alpha[j] and
+//                        norms[j] = |u| (from part_b) are recorded
+//   launch_dot_pair      part[2 blk], part[2 blk + 1] of x . x and x . y (y may be null)
+//   launch_sum_pairs     sums of `count` such tables, out[2 k], out[2 k + 1]
+int scalar_blocks(int64_t n);
+hipError_t launch_sumsq(const double *x, int64_t n, double *part, hipStream_t s);
+hipError_t launch_lanczos_step(double *y, const double *u, double *up, int64_t D, int j, double *norms, double *alpha,
+                               double *part_a, double *part_b, hipStream_t s);
+hipError_t launch_dot_pair(const double *x, const double *y, int64_t n, double *part, hipStream_t s);
+hipError_t launch_sum_pairs(const double *part, int count, int64_t n, double *out, hipStream_t s);
 // residual: with r_j = hx_j - theta_j x_j, out[3j] = ||r_j||^2, out[3j+1] = ||x_j||^2,
 // out[3j+2] = x_j . r_j (two stages; partial holds nblk * 3 b doubles).
 hipError_t launch_resid(const double *x, const double *hx, int64_t ld, const double *theta, int64_t D, int b,

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
+#include "wave.h"
 
 namespace dacp {
 
@@ -956,12 +957,28 @@ __global__ __launch_bounds__(256) void k_coldots(const T *x, int64_t ldx, const 
   }
 }
 
-__global__ void k_reduce_partials(const double *partial, int nblk, int w, double *out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= w) return;
+// out[j] = sum over q of partial[q][j]: 2^lc columns a workgroup, the q dealt to its 256 / 2^lc rows of
+// threads, whose sums are added in order.  (One thread a column took 134 us for 1024 partials.)
+__global__ __launch_bounds__(256) void k_reduce_partials(const double *partial, int nblk, int w, int lc, double *out) {
+  __shared__ double sm[256];
+  const int cols = 1 << lc, rows = 256 >> lc;
+  const int c = threadIdx.x & (cols - 1), r = threadIdx.x >> lc;
+  const int j = blockIdx.x * cols + c;
   double s = 0.0;
-  for (int q = 0; q < nblk; ++q) s += partial[static_cast<int64_t>(q) * w + j];
-  out[j] = s;
+  if (j < w)
+    for (int q = r; q < nblk; q += rows) s += partial[static_cast<int64_t>(q) * w + j];
+  sm[threadIdx.x] = s;
+  __syncthreads();
+  if (r == 0 && j < w) {
+    for (int q = 1; q < rows; ++q) s += sm[q * cols + c];
+    out[j] = s;
+  }
+}
+
+void reduce_partials(const double *partial, int nblk, int w, double *out, hipStream_t s) {
+  int lc = 0;
+  while (lc < 5 && (1 << lc) < w) ++lc;
+  hipLaunchKernelGGL(k_reduce_partials, dim3((w + (1 << lc) - 1) >> lc), dim3(256), 0, s, partial, nblk, w, lc, out);
 }
 
 hipError_t launch_coldots(const void *x, int64_t ldx, const void *y, int64_t ldy, int dtype, int64_t D, int b,
@@ -972,7 +989,126 @@ hipError_t launch_coldots(const void *x, int64_t ldx, const void *y, int64_t ldy
   else
     hipLaunchKernelGGL((k_coldots<float>), dim3(nblk), dim3(256), 0, s, static_cast<const float *>(x), ldx,
                        static_cast<const float *>(y), ldy, D, b, partial);
-  hipLaunchKernelGGL(k_reduce_partials, dim3((b + 255) / 256), dim3(256), 0, s, partial, nblk, b, out);
+  reduce_partials(partial, nblk, b, out, s);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Scalars of the Lanczos and moment recurrences kept on the device.  A recurrence whose coefficients
+// came back to the host cost two or three round trips a step (20 ms for 80 Lanczos steps and 256
+// moments at 2^16 rows, of which 13 on the GPU); here a kernel leaves one partial sum per workgroup
+// and the next one adds them for itself, every workgroup in the same order.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ double block_sum_256(double v, double *sm) {
+  v = wave_sum_last(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 63) sm[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (sm[0] + sm[1]) + (sm[2] + sm[3]);
+}
+
+int scalar_blocks(int64_t n) {
+  const int64_t nb = n / 1024;
+  return static_cast<int>(nb < 1 ? 1 : nb > 256 ? 256 : nb);
+}
+
+// part[blk] = the workgroup's share of |x|^2.
+__global__ __launch_bounds__(256) void k_sumsq(const double *x, int64_t n, double *part) {
+  __shared__ double sm[4];
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) s += x[i] * x[i];
+  s = block_sum_256(s, sm);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// First half of Lanczos step j on unnormalised vectors, v_j = u / beta_j: y = H u on entry,
+// y = H v_j - beta_j v_(j-1) on exit (up = u_(j-1)), and the shares of alpha_j = y . v_j in part_a.
+// beta_j is the square root of the sum of part_b and is kept in norms[j].
+__global__ __launch_bounds__(256) void k_lanczos_a(double *y, const double *u, const double *up, int64_t D, int j,
+                                                   double *norms, const double *part_b, double *part_a) {
+  __shared__ double sm[4];
+  const double b2 = block_sum_256(threadIdx.x < gridDim.x ? part_b[threadIdx.x] : 0.0, sm);
+  const double beta = sqrt(fmax(b2, 0.0));
+  const double inv = 1.0 / beta, cp = j > 0 ? beta / norms[j - 1] : 0.0;
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < D; i += gridDim.x * 256) {
+    double w = y[i] * inv;
+    if (j > 0) w -= cp * up[i];
+    y[i] = w;
+    s += w * (u[i] * inv);
+  }
+  s = block_sum_256(s, sm);
+  if (threadIdx.x == 0) part_a[blockIdx.x] = s;
+  if (blockIdx.x == 0 && threadIdx.x == 0) norms[j] = beta;
+}
+
+// Second half: u_(j+1) = y - alpha_j v_j over u_(j-1), the shares of its squared norm in part_b.
+__global__ __launch_bounds__(256) void k_lanczos_b(const double *y, const double *u, double *un, int64_t D, int j,
+                                                   const double *norms, double *alpha, const double *part_a,
+                                                   double *part_b) {
+  __shared__ double sm[4];
+  const double al = block_sum_256(threadIdx.x < gridDim.x ? part_a[threadIdx.x] : 0.0, sm);
+  const double c = al / norms[j];
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < D; i += gridDim.x * 256) {
+    const double w = y[i] - c * u[i];
+    un[i] = w;
+    s += w * w;
+  }
+  s = block_sum_256(s, sm);
+  if (threadIdx.x == 0) part_b[blockIdx.x] = s;
+  if (blockIdx.x == 0 && threadIdx.x == 0) alpha[j] = al;
+}
+
+hipError_t launch_sumsq(const double *x, int64_t n, double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_sumsq, dim3(scalar_blocks(n)), dim3(256), 0, s, x, n, part);
+  return hipGetLastError();
+}
+
+hipError_t launch_lanczos_step(double *y, const double *u, double *up, int64_t D, int j, double *norms, double *alpha,
+                               double *part_a, double *part_b, hipStream_t s) {
+  const dim3 grid(scalar_blocks(D)), block(256);
+  hipLaunchKernelGGL(k_lanczos_a, grid, block, 0, s, y, u, up, D, j, norms, part_b, part_a);
+  hipLaunchKernelGGL(k_lanczos_b, grid, block, 0, s, y, u, up, D, j, norms, alpha, part_a, part_b);
+  return hipGetLastError();
+}
+
+// Shares of x . x and (y not null) x . y over n elements: part[2 blk], part[2 blk + 1].
+__global__ __launch_bounds__(256) void k_dot_pair(const double *x, const double *y, int64_t n, double *part) {
+  __shared__ double sm[4];
+  double a = 0.0, b = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const double v = x[i];
+    a += v * v;
+    if (y) b += v * y[i];
+  }
+  a = block_sum_256(a, sm);
+  b = block_sum_256(b, sm);
+  if (threadIdx.x == 0) {
+    part[2 * blockIdx.x] = a;
+    part[2 * blockIdx.x + 1] = b;
+  }
+}
+
+// out[2 k], out[2 k + 1] = the sums of part[k][..][0] and part[k][..][1] over nb workgroups.
+__global__ __launch_bounds__(256) void k_sum_pairs(const double *part, int nb, double *out) {
+  __shared__ double sm[4];
+  const double *p = part + static_cast<int64_t>(blockIdx.x) * 2 * nb;
+  const double a = block_sum_256(static_cast<int>(threadIdx.x) < nb ? p[2 * threadIdx.x] : 0.0, sm);
+  const double b = block_sum_256(static_cast<int>(threadIdx.x) < nb ? p[2 * threadIdx.x + 1] : 0.0, sm);
+  if (threadIdx.x == 0) {
+    out[2 * blockIdx.x] = a;
+    out[2 * blockIdx.x + 1] = b;
+  }
+}
+
+hipError_t launch_dot_pair(const double *x, const double *y, int64_t n, double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_dot_pair, dim3(scalar_blocks(n)), dim3(256), 0, s, x, y, n, part);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_pairs(const double *part, int count, int64_t n, double *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_sum_pairs, dim3(count), dim3(256), 0, s, part, scalar_blocks(n), out);
   return hipGetLastError();
 }
 
@@ -1024,7 +1160,7 @@ __global__ __launch_bounds__(256) void k_resid(const double *x, const double *hx
 hipError_t launch_resid(const double *x, const double *hx, int64_t ld, const double *theta, int64_t D, int b,
                         double *partial, int nblk, double *out, hipStream_t s) {
   hipLaunchKernelGGL(k_resid, dim3(nblk), dim3(256), 0, s, x, hx, ld, theta, D, b, partial);
-  hipLaunchKernelGGL(k_reduce_partials, dim3((3 * b + 255) / 256), dim3(256), 0, s, partial, nblk, 3 * b, out);
+  reduce_partials(partial, nblk, 3 * b, out, s);
   return hipGetLastError();
 }
 
@@ -1087,7 +1223,7 @@ hipError_t launch_tall_gram(const double *X, int64_t ldx, int bx, const double *
   if (bx < 1 || gy < 1 || bx * gy > 1024) return hipErrorInvalidValue;
   const size_t lds = sizeof(double) * kGramRows * (bx + gy);
   hipLaunchKernelGGL(k_tall_gram, dim3(nblk), dim3(256), lds, s, X, ldx, bx, Y, ldy, gy, D, partial);
-  hipLaunchKernelGGL(k_reduce_partials, dim3((bx * gy + 255) / 256), dim3(256), 0, s, partial, nblk, bx * gy, out);
+  reduce_partials(partial, nblk, bx * gy, out, s);
   return hipGetLastError();
 }
 
@@ -1239,16 +1375,6 @@ hipError_t launch_join_cols(const double *x, int64_t D, int g, int groups, doubl
   if (b > g * groups) return hipErrorInvalidValue;
   const int64_t n = D * b;
   hipLaunchKernelGGL(k_join_cols, dim3((n + 255) / 256), dim3(256), 0, s, x, D, g, y, ldy, b);
-  return hipGetLastError();
-}
-
-__global__ void k_axpby(double *y, const double *x, double a, double bcoef, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) y[i] = a * x[i] + bcoef * y[i];
-}
-
-hipError_t launch_axpby(double *y, const double *x, double a, double bcoef, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_axpby, dim3((n + 255) / 256), dim3(256), 0, s, y, x, a, bcoef, n);
   return hipGetLastError();
 }
 
