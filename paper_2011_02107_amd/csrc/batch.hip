@@ -220,7 +220,8 @@ __device__ __forceinline__ void sample_at(const BatchCol &c, ConstInts ks, int &
   if (kk == km) {
     store_panel<E>(c.V, c.ldv, static_cast<int64_t>(2 * next + 2) * c.b, T, D);
     const double n2 = dot<E>(T, T, red);
-    if (!(n2 <= norm2 * (1.0 + 2e-6)) && threadIdx.x == 0) *c.bound_flag = 1;
+    if (!(n2 <= norm2 * (1.0 + 2e-6)) && threadIdx.x == 0)
+      atomicMin(c.bound_flag, 2 * next + (isfinite(n2) ? 0 : 1));  // the earliest sample's
     ++next;
   }
 }

@@ -510,6 +510,84 @@ struct Timer {
   }
 };
 
+// ------------------------------------------------------- on-chip columns
+// Up to kOnChipL spins a column fits one compute unit, and a recurrence runs there whole, a
+// workgroup per column (batch.hip): one launch, where a step through memory is one to four
+// launches of about 5 us each whatever the size (an on-chip apply takes 5 us at 2^14 rows, under 2
+// at 2^11).  Orders past kOnChipSteps (seconds in one launch) take the general kernels.
+constexpr int kOnChipL = 14;
+constexpr int64_t kOnChipSteps = int64_t(1) << 20;
+bool onchip_fits(dacp_ham h, int b, int64_t ld, int64_t steps) {
+  return h->L <= kOnChipL && steps <= kOnChipSteps && h->D * std::max<int64_t>(b, ld) * 8 < (int64_t(1) << 32);
+}
+
+// A column's table entry without its buffers: h's tables and the recurrences' coefficients (a > 0:
+// the filter's too).
+BatchCol onchip_col(dacp_ham h, int mode, double e_b, double a) {
+  BatchCol c;
+  std::memset(&c, 0, sizeof(c));
+  c.xc = h->onchip.xc;
+  c.flips = h->onchip.flips;
+  c.nflip = h->onchip.nflip;
+  c.nplain = h->onchip.nplain;
+  c.d64 = h->d64;
+  c.d32 = h->d32;
+  c.L = h->L;
+  c.mode = mode;
+  c.inv_e = 1.0 / e_b;
+  if (a > 0.0) {
+    const double e_c = 0.5 * (e_b * e_b + a * a), e_0 = 0.5 * (e_b * e_b - a * a);
+    const double rho = std::exp(std::acosh(1.0 + 2.0 * a * a / (e_b * e_b - a * a)));
+    c.f_alpha = 2.0 / (e_0 * rho);
+    c.f_beta = -2.0 * e_c / (e_0 * rho);
+    c.f_gamma = -1.0 / (rho * rho);
+    c.f_first_a = 1.0 / (e_0 * rho);
+    c.f_first_b = -e_c / (e_0 * rho);
+  }
+  return c;
+}
+
+// The evolution of all b columns from psi_e (D x b) on chip: panels at 0 and the sample orders ks into
+// V and, with anchors, the panels of the anchor orders into abuf (row stride lda).  Returns the norm
+// check's outcome as run_basis does (`what` names the entry point).
+dacp_status onchip_evolve(dacp_ctx ctx, dacp_ham h, double e_bound, int b, const double *psi_e,
+                          const std::vector<int64_t> &ks, double *V, int64_t ldv, const std::vector<int64_t> *anchors,
+                          double *abuf, int64_t lda, const char *what) {
+  DACP_TRY(onchip_order(ctx, h));
+  std::vector<int> tab(ks.begin(), ks.end());
+  const int na = anchors ? static_cast<int>(anchors->size()) : 0;
+  if (anchors) tab.insert(tab.end(), anchors->begin(), anchors->end());
+  tab.push_back(dacp::kBatchNoFlag);
+  DevBuf dtab, dcols;
+  DACP_HIP(ctx, dtab.alloc(tab.size() * sizeof(int)));
+  DACP_HIP(ctx, dcols.alloc(sizeof(BatchCol) * b));
+  std::vector<BatchCol> cols;
+  for (int j = 0; j < b; ++j) {
+    BatchCol c = onchip_col(h, dacp::kBatchEvolve, e_bound, 0.0);
+    c.psi0 = psi_e + j;
+    c.ld_psi = b;
+    c.V = V + j;
+    c.ldv = ldv;
+    c.b = b;
+    c.ks = dtab.as<int>();
+    c.n_samples = static_cast<int>(ks.size());
+    c.n_anchor = na;
+    c.ka = dtab.as<int>() + ks.size();
+    c.A = abuf ? abuf + j : nullptr;
+    c.lda = lda;
+    c.bound_flag = dtab.as<int>() + ks.size() + na;
+    cols.push_back(c);
+  }
+  DACP_TRY(to_device(ctx, dtab.p, tab.data(), tab.size() * sizeof(int)));
+  DACP_TRY(to_device(ctx, dcols.p, cols.data(), sizeof(BatchCol) * b));
+  DACP_HIP(ctx, dacp::launch_batch_chebyshev(dcols.as<BatchCol>(), b, h->L, ctx->stream));
+  int flag = 0;
+  DACP_TRY(to_host(ctx, &flag, cols[0].bound_flag, sizeof(int)));
+  if (flag == dacp::kBatchNoFlag) return DACP_OK;
+  if (flag & 1) return set_err(ctx, DACP_E_NUMERIC, std::string(what) + ": non-finite evolved state");
+  return set_err(ctx, DACP_E_BOUNDS, std::string(what) + ": |T_k(H/e_bound)| grew above 1; e_bound is below ||H||");
+}
+
 // ------------------------------------------------------------- filter core
 // Damped recurrence: with rho = exp(theta_0), theta_0 = arccosh(1 + 2a^2/(E_b^2 - a^2))
 // the growth rate of the band-centre component, the kernels carry
@@ -739,6 +817,29 @@ dacp_status run_filter(dacp_ctx ctx, dacp_ham h, const dacp_filter_params *p, co
     DACP_HIP(ctx, dacp::launch_philox_gauss(s0.as<double>(), D, b, p->seed, ctx->stream));
     psi = s0.as<double>();
   }
+  if (p->K > 0 && onchip_fits(h, b, b, p->K)) {
+    DACP_TRY(onchip_order(ctx, h));
+    const int tail = p->precision == DACP_F32 ? std::max(0, std::min(p->fp64_tail, p->K)) : p->K;
+    std::vector<BatchCol> cols;
+    for (int j = 0; j < b; ++j) {
+      BatchCol c = onchip_col(h, dacp::kBatchFilter, p->e_bound, p->a);
+      c.psi0 = psi + j;
+      c.ld_psi = b;
+      c.V = psi_out + j;
+      c.ldv = b;
+      c.b = b;
+      c.K = p->K;
+      c.n32 = p->K - tail;
+      cols.push_back(c);
+    }
+    DevBuf dcols;
+    DACP_HIP(ctx, dcols.alloc(sizeof(BatchCol) * b));
+    DACP_TRY(to_device(ctx, dcols.p, cols.data(), sizeof(BatchCol) * b));
+    DACP_HIP(ctx, dacp::launch_batch_chebyshev(dcols.as<BatchCol>(), b, h->L, ctx->stream));
+    DACP_TRY(normalise_cols(ctx, psi_out, D, b));
+    DACP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    return DACP_OK;
+  }
   const int gf = p->precision == DACP_F32 ? ctx->filter_group_f32 : ctx->filter_group_f64;
   // four live blocks: T_(k-1), T_k, w and the partial
   const int gt = (h->L >= 15 && b > gf) ? gf : b;
@@ -964,6 +1065,14 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     panel_of[ks[i]] = 2 * i + 2;
   }
   const int64_t kmax = ks.back();
+  if (onchip_fits(h, b, ldv, kmax)) {
+    Timer tm(ctx);
+    tm.start();
+    DACP_TRY(onchip_evolve(ctx, h, p->e_bound, b, psi_e, ks, V, ldv, nullptr, nullptr, 0, "basis"));
+    if (m_out) *m_out = m;
+    if (stats) *stats = {kmax, 1, tm.stop_ms(), b};
+    return DACP_OK;
+  }
   const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
   const ColGroups cg = column_groups(ctx, h, b, gt, 3, {8});
   DevBuf ba, bb, nrm, pbuf;
@@ -1378,6 +1487,21 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
   const int na = static_cast<int>(anchors.size());
   const int ma = na * b;  // anchor block width
   const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
+  if (onchip_fits(h, b, std::max<int64_t>(ldv, 2 * ma), kn + 1)) {
+    std::vector<int64_t> ks;
+    for (int j = 1; j <= n; ++j) ks.push_back(mp.orders[2 * j]);
+    DevBuf abuf;
+    DACP_HIP(ctx, abuf.alloc(static_cast<size_t>(D) * 2 * ma * sizeof(double)));
+    Timer tm(ctx);
+    tm.start();
+    DACP_TRY(onchip_evolve(ctx, h, p->e_bound, b, psi_e, ks, V, ldv, &anchors, abuf.as<double>(), 2 * ma,
+                           "basis_stored_moments"));
+    const double evol_ms = tm.stop_ms();
+    DACP_TRY(anchor_projection(ctx, h, mp.orders, anchors, abuf.as<double>(), V, ldv, b, p->e_bound, S, P, ld, gram_ms));
+    if (m_out) *m_out = m;
+    if (stats) *stats = {kn + 1, 1, evol_ms, b};
+    return DACP_OK;
+  }
   const ColGroups cg = column_groups(ctx, h, b, gt, 3, {8});
   const double inv_e = 1.0 / p->e_bound;
   DevBuf ba, bb, pbuf, abuf, nrm;
@@ -1658,11 +1782,6 @@ BatchSpec spectral_spec(dacp_ham h, int kind, int steps, const double *start, in
   c.out = out;
   return c;
 }
-
-// Up to kOnChipL spins a column fits one compute unit, and a recurrence of single columns runs
-// there whole: one launch, where a step through memory is two to four of about 5 us each whatever
-// the size (an on-chip apply takes 5 us at 2^14 rows, under 2 at 2^11).
-constexpr int kOnChipL = 14;
 
 dacp_status run_bound(dacp_ctx ctx, dacp_ham h, int steps, const double *v0, uint64_t seed, double safety,
                       double *e_bound, double *tmin, double *tmax) {
@@ -2993,8 +3112,9 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
   std::vector<std::vector<int64_t>> orders_of(count), anchors_of(count);
   DevBuf flags;
   DACP_HIP(ctx, flags.alloc(sizeof(int) * count));
-  DACP_HIP(ctx, hipMemsetAsync(flags.p, 0, sizeof(int) * count, ctx->stream));
+  DACP_HIP(ctx, hipMemsetAsync(flags.p, dacp::kBatchNoFlag & 0xff, sizeof(int) * count, ctx->stream));
   std::vector<BatchCol> cols;
+  std::vector<double> col_work;
   for (int r = 0; r < count; ++r) {
     dacp_ham h = hams[r];
     const Plan &pl = plans[r];
@@ -3024,19 +3144,9 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
     std::vector<int> ks(ks64.begin(), ks64.end());
     DACP_HIP(ctx, ksd[r].alloc(sizeof(int) * ks.size()));
     DACP_TRY(to_device(ctx, ksd[r].p, ks.data(), sizeof(int) * ks.size()));
-    const double e_b = e_bs[r], a = pl.a;
-    const double e_c = 0.5 * (e_b * e_b + a * a), e_0 = 0.5 * (e_b * e_b - a * a);
-    const double rho = std::exp(std::acosh(1.0 + 2.0 * a * a / (e_b * e_b - a * a)));
     const int tail = (o.precision == DACP_F32) ? std::max(0, std::min(pl.K, static_cast<int>(std::ceil(o.fp64_tail_frac * pl.K)))) : pl.K;
     for (int j = 0; j < pl.b; ++j) {
-      BatchCol c;
-      std::memset(&c, 0, sizeof(c));
-      c.xc = h->onchip.xc;
-      c.flips = h->onchip.flips;
-      c.nflip = h->onchip.nflip;
-      c.nplain = h->onchip.nplain;
-      c.d64 = h->d64;
-      c.d32 = h->d32;
+      BatchCol c = onchip_col(h, dacp::kBatchBoth, e_bs[r], pl.a);
       c.psi0 = psi[r].as<double>() + j;
       c.ld_psi = pl.b;
       c.V = vb[r].as<double>() + j;
@@ -3050,23 +3160,22 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
         c.ka = kad[r].as<int>();
       }
       c.bound_flag = flags.as<int>() + r;
-      c.f_alpha = 2.0 / (e_0 * rho);
-      c.f_beta = -2.0 * e_c / (e_0 * rho);
-      c.f_gamma = -1.0 / (rho * rho);
-      c.f_first_a = 1.0 / (e_0 * rho);
-      c.f_first_b = -e_c / (e_0 * rho);
-      c.inv_e = 1.0 / e_b;
-      c.L = h->L;
       c.K = pl.K;
       c.n32 = pl.K - tail;
       c.b = pl.b;
       cols.push_back(c);
+      col_work.push_back((2.0 * pl.K + ks.back()) * static_cast<double>(D));
     }
   }
-  // longest columns first, so the short ones fill in behind them
-  std::stable_sort(cols.begin(), cols.end(), [](const BatchCol &x, const BatchCol &y) {
-    return static_cast<double>(x.K + x.n_samples) * (1 << x.L) > static_cast<double>(y.K + y.n_samples) * (1 << y.L);
-  });
+  // longest columns first (applies times elements), so the short ones fill in behind them
+  {
+    std::vector<int> order(cols.size());
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return col_work[x] > col_work[y]; });
+    std::vector<BatchCol> sorted;
+    for (int i : order) sorted.push_back(cols[i]);
+    cols.swap(sorted);
+  }
   DevBuf dcols;
   DACP_HIP(ctx, dcols.alloc(sizeof(BatchCol) * cols.size()));
   DACP_TRY(to_device(ctx, dcols.p, cols.data(), sizeof(BatchCol) * cols.size()));
@@ -3082,12 +3191,12 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
   for (int r = 0; r < count; ++r) {
     psi[r].release();
     rep[r].t_evol_ms = t_batch;
-    if (flag[r] && given) {
+    if (flag[r] != dacp::kBatchNoFlag && given) {
       redo[r] = 1;
       vb[r].release();
       continue;
     }
-    if (flag[r])
+    if (flag[r] != dacp::kBatchNoFlag)
       return set_err(ctx, DACP_E_BOUNDS, "batched: realisation " + std::to_string(r) +
                                              ": |T_k(H/e_bound)| grew above 1; e_bound is below ||H||");
   }

@@ -118,6 +118,7 @@ struct RecArgs {
 
 // One column of one realisation for the batched persistent kernel (batch.hip).  Read by the
 // kernel through the scalar cache: the table is not written while the kernel runs.
+constexpr int kBatchNoFlag = 0x7f7f7f7f;  // four equal bytes
 enum BatchMode { kBatchBoth = 0, kBatchFilter = 1, kBatchEvolve = 2 };
 struct BatchCol {
   const double *xc;        // 14 coefficients of sigma^x_b (0 where there is none)
@@ -127,7 +128,8 @@ struct BatchCol {
   const double *psi0;      // start column: psi0[s * ld_psi]
   double *V;               // the realisation's basis shifted to this column: panel p at V[s * ldv + p * b]
   const int *ks;           // sample orders k_1 < ... < k_n (device)
-  int *bound_flag;         // set to 1 when |T_k(G) psi_E| > 1 is seen (bound below ||H||)
+  int *bound_flag;         // lowered to 2 m (2 m + 1: not finite) when sample m's norm exceeds psi_E's
+                           // (bound below ||H||); the caller sets it to kBatchNoFlag
   double *A;               // anchors (moment projection) shifted to this column: anchor i at A[s * lda + i * b]
   const int *ka;           // anchor orders, ascending (device; n_anchor of them, 0 = none)
   int64_t ld_psi, ldv, lda;
