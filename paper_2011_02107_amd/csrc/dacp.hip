@@ -370,10 +370,11 @@ bool fused_plan(dacp_ctx ctx, dacp_ham h, int g, int &lo_bits, int &W, int esize
 // general kernels take twice as long per step), and `per` groups advance in one launch.  One group
 // of 8 columns is 2 to 32 MB a block below 2^19 rows, whose launches are bound by their own start
 // and end (6-8 us each at 2^16 rows, the streams' rate would take 2.5); together they stream at the
-// rate of a large copy.  A launch's groups stay within the Infinity Cache: past kRecCacheBytes
-// every step would go to HBM (two groups at once at 2^20 rows: 50-60 us a group, alone 44).
+// rate of a large copy.  A launch's groups stay within the 256 MB Infinity Cache: past it every step
+// would go to HBM (two groups at once at 2^20 rows: 50-60 us a group, alone 43); half of it costs
+// the FP64 filter at 2^17 to 2^19 rows 5-8 %.
 // A shape without a fused plan keeps its width and runs one group at a time.
-constexpr int64_t kRecCacheBytes = int64_t(200) << 20;
+constexpr int64_t kRecCacheBytes = int64_t(256) << 20;
 struct ColGroups {
   int g, per;
   bool fused;
