@@ -239,7 +239,7 @@ dacp_status dacp_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, con
  * x, y the orders of panels p, q.  psi_e: device [D][b] FP64, 1 <= b <= 128.  S, P: device m x m,
  * row stride ld >= m = b (2n + 1), both triangles written (symmetric parts of the assembled
  * blocks).  m_out (host, may be NULL) gets m.  Memory besides S and P: three D x g FP64 blocks,
- * G psi_E (D x b) and the moments.  Errors as dacp_basis (DACP_E_BOUNDS when |T_{k_m}(G) psi|
+ * [psi_E | G psi_E] (D x 2b), up to 256 columns of recorded T_k psi_E (D x 256) and the moments.  Errors as dacp_basis (DACP_E_BOUNDS when |T_{k_m}(G) psi|
  * exceeds |psi|). */
 dacp_status dacp_basis_moments(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, const double *psi_e, double *S,
                                double *P, int64_t ld, int *m_out);

@@ -1224,23 +1224,28 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
   const int64_t kmax = 2 * mp.orders.back();
   int nslot = 0;
   const std::vector<int> slot_of = moment_slots(mp.orders, nslot);
-  int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
-  while (g > 1 && b * g > 1024) g /= 2;  // the tall Gram kernel takes b g <= 1024 pairs
+  const int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
   const ColGroups cg = column_groups(ctx, h, b, g, 3, {8});
   const double inv_e = 1.0 / p->e_bound;
-  DevBuf ba, bb, pbuf, gpsi, mu, nu, part, tmp, didx, dord;
+  // The recorded T_k are staged side by side, up to kz columns, and multiplied by [psi_E | G psi_E]^T
+  // in one GEMM that gives mu and nu of them all: the left factor is read once for several orders.
+  // (One 8-column group and factor at a time, on the vector ALU, a 2^16 x 32 order took 630 us.)
+  const int kz = std::max(256, std::min(b, cg.g * cg.per));
+  DevBuf ba, bb, pbuf, left, mu, nu, zb, prod, work, didx, dord;
   DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
-  DACP_HIP(ctx, gpsi.alloc(static_cast<size_t>(D) * b * sizeof(double)));
+  DACP_HIP(ctx, left.alloc(static_cast<size_t>(D) * 2 * b * sizeof(double)));
   DACP_HIP(ctx, mu.alloc(static_cast<size_t>(nslot) * b * b * sizeof(double)));
   DACP_HIP(ctx, nu.alloc(static_cast<size_t>(nslot) * b * b * sizeof(double)));
-  const int nblk = dacp::tall_gram_blocks(D);
-  DACP_HIP(ctx, part.alloc(static_cast<size_t>(nblk) * b * g * sizeof(double)));
-  DACP_HIP(ctx, tmp.alloc(static_cast<size_t>(b) * g * sizeof(double)));
-  // G psi_E, the left factor of nu
+  DACP_HIP(ctx, zb.alloc(static_cast<size_t>(D) * kz * sizeof(double)));
+  DACP_HIP(ctx, prod.alloc(2 * static_cast<size_t>(b) * kz * sizeof(double)));
+  const int sp = dacp::gemm_splits(2 * b, kz, D, 0, ctx->num_cus, 512, 128);
+  if (sp > 1) DACP_HIP(ctx, work.alloc(2 * static_cast<size_t>(sp) * b * kz * sizeof(double)));
+  double *X = left.as<double>();
+  DACP_HIP(ctx, dacp::launch_copy_cols(psi_e, b, X, 2 * b, D, b, ctx->stream));
   for (int c0 = 0; c0 < b; c0 += 64)
-    DACP_TRY(step<double>(ctx, h, std::min(64, b - c0), psi_e + c0, b, gpsi.as<double>() + c0, b, inv_e));
+    DACP_TRY(step<double>(ctx, h, std::min(64, b - c0), psi_e + c0, b, X + b + c0, 2 * b, inv_e));
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
@@ -1249,19 +1254,31 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
     double *A = ba.as<double>(), *B = bb.as<double>();
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return k <= kmax && slot_of[k] >= 0; };
-    // mu_k[:, g0 .. g0 + nc) = psi_E^T (T_k psi_E)[:, group by group], nu_k likewise with (G psi_E)^T
-    auto visit = [&](int64_t k, const double *tks, const double *) -> dacp_status {
-      for (int y = 0; y < groups; ++y) {
-        const double *tk = tks + y * D * gw;
-        const int yc = std::min(gw, nc - y * gw);
-        const int64_t off = static_cast<int64_t>(slot_of[k]) * b * b + g0 + y * gw;
-        DACP_HIP(ctx, dacp::launch_tall_gram(psi_e, b, b, tk, gw, yc, D, part.as<double>(), nblk, tmp.as<double>(),
+    // mu_k[:, g0 .. g0 + nc) = psi_E^T (T_k psi_E)[:, these columns], nu_k likewise with (G psi_E)^T
+    std::vector<int64_t> staged;  // orders of the staged blocks of nc columns
+    auto flush = [&]() -> dacp_status {
+      const int w = static_cast<int>(staged.size()) * nc;
+      if (w == 0) return DACP_OK;
+      if (sp > 1)
+        DACP_HIP(ctx, dacp::launch_dgemm_splitk(1, 0, 2 * b, w, D, 1.0, X, 2 * b, zb.as<double>(), kz, 0.0,
+                                                prod.as<double>(), w, 0, sp, work.as<double>(), ctx->stream));
+      else
+        DACP_HIP(ctx, dacp::launch_dgemm(1, 0, 2 * b, w, D, 1.0, X, 2 * b, zb.as<double>(), kz, 0.0, prod.as<double>(),
+                                         w, 0, ctx->stream));
+      for (size_t i = 0; i < staged.size(); ++i) {
+        const int64_t off = static_cast<int64_t>(slot_of[staged[i]]) * b * b + g0;
+        const double *src = prod.as<double>() + static_cast<int64_t>(i) * nc;
+        DACP_HIP(ctx, dacp::launch_copy_cols(src, w, mu.as<double>() + off, b, b, nc, ctx->stream));
+        DACP_HIP(ctx, dacp::launch_copy_cols(src + static_cast<int64_t>(b) * w, w, nu.as<double>() + off, b, b, nc,
                                              ctx->stream));
-        DACP_HIP(ctx, dacp::launch_copy_cols(tmp.as<double>(), yc, mu.as<double>() + off, b, b, yc, ctx->stream));
-        DACP_HIP(ctx, dacp::launch_tall_gram(gpsi.as<double>(), b, b, tk, gw, yc, D, part.as<double>(), nblk,
-                                             tmp.as<double>(), ctx->stream));
-        DACP_HIP(ctx, dacp::launch_copy_cols(tmp.as<double>(), yc, nu.as<double>() + off, b, b, yc, ctx->stream));
       }
+      staged.clear();
+      return DACP_OK;
+    };
+    auto visit = [&](int64_t k, const double *tk, const double *) -> dacp_status {
+      DACP_HIP(ctx, dacp::launch_join_cols(tk, D, gw, groups, zb.as<double>() + staged.size() * nc, kz, nc, ctx->stream));
+      staged.push_back(k);
+      if (static_cast<int>(staged.size() + 1) * nc > kz) return flush();
       return DACP_OK;
     };
     auto events = [&](int64_t k1, int64_t k2) {
@@ -1273,6 +1290,7 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
         ctx, h, inv_e, kmax, gw, groups, nc, A, B, pbuf.as<double>(), [](int64_t) -> double * { return nullptr; }, 0,
         want, visit, events, launches);
     if (st) return st;
+    DACP_TRY(flush());
   }
   const double evol_ms = tm.stop_ms();
   // |T_k(G)| <= 1 for e_bound >= ||H||: |T_{k_j} psi|^2 = (mu_{2 k_j} + mu_0) / 2 on the diagonal

@@ -248,11 +248,11 @@ hipError_t launch_dgemm_impl(int transA, int transB, int64_t M, int64_t N, int64
   if (M <= 0 || N <= 0) return hipSuccess;
   if (splits < 1 || (splits > 1 && !work)) return hipErrorInvalidValue;
   if (upper && M != N) return hipErrorInvalidValue;
-  // 64 x 64 tiles when 128 x 128 ones would leave compute units without a workgroup: they reach
-  // about two thirds of the large tiles' rate, on four times as many units.
+  // 64 x 64 tiles when 128 x 128 ones would leave compute units without a workgroup (they reach about
+  // two thirds of the large tiles' rate, on four times as many units) or be half empty.
   const int64_t t128 = tile_count(static_cast<int>((M + 127) / 128), static_cast<int>((N + 127) / 128), upper) * splits;
   hipError_t e;
-  if (splits == 1 && t128 < 256)
+  if ((splits == 1 && t128 < 256) || M <= 64 || N <= 64)
     e = launch_dgemm_tm<64>(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, upper, splits, work, s);
   else
     e = launch_dgemm_tm<128>(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, upper, splits, work, s);

@@ -238,11 +238,6 @@ hipError_t launch_sum_pairs(const double *part, int count, int64_t n, double *ou
 hipError_t launch_resid(const double *x, const double *hx, int64_t ld, const double *theta, int64_t D, int b,
                         double *partial, int nblk, double *out, hipStream_t s);
 
-// Moment mode (App. C, Eq. shift; kernels.hip).  out (bx x gy, contiguous) = X^T Y for X (D x bx)
-// and Y (D x gy), bx gy <= 1024; partial holds nblk bx gy doubles, nblk = tall_gram_blocks(D).
-int tall_gram_blocks(int64_t D);
-hipError_t launch_tall_gram(const double *X, int64_t ldx, int bx, const double *Y, int64_t ldy, int gy, int64_t D,
-                            double *partial, int nblk, double *out, hipStream_t s);
 // The anchors' moments on the device (kernels.hip): M (2 x nrules b x b blocks, mu then nu) from the
 // Gram product G ((2 na b) x m) by the derivation rules (ai, q, other; other = -1 or an earlier rule).
 hipError_t launch_moment_chain(const double *G, int64_t m, int b, int na, const int *rules, int nrules, double scale0,

@@ -1182,66 +1182,6 @@ hipError_t launch_resid(const double *x, const double *hx, int64_t ld, const dou
 // ---------------------------------------------------------------------------
 // Moment mode (App. C, Eq. shift).
 // ---------------------------------------------------------------------------
-// Tall Gram block X^T Y of X (D x bx, row stride ldx) and Y (D x gy, stride ldy): each workgroup
-// sums a range of rows into partial[blk][i gy + j]; rows are staged 32 at a time through LDS with
-// coalesced loads, and each thread accumulates its (i, j) pairs over them in row order.
-constexpr int kGramRows = 32;
-__global__ __launch_bounds__(256) void k_tall_gram(const double *X, int64_t ldx, int bx, const double *Y, int64_t ldy,
-                                                   int gy, int64_t D, double *partial) {
-  extern __shared__ double gsm[];
-  double *xs = gsm;                    // kGramRows x bx
-  double *ys = gsm + kGramRows * bx;   // kGramRows x gy
-  const int npair = bx * gy;
-  const int64_t rows_per = (D + gridDim.x - 1) / gridDim.x;
-  const int64_t rbeg = static_cast<int64_t>(blockIdx.x) * rows_per;
-  const int64_t rend = rbeg + rows_per < D ? rbeg + rows_per : D;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};  // pairs tid, tid + 256, ... (npair <= 1024)
-  for (int64_t r0 = rbeg; r0 < rend; r0 += kGramRows) {
-    const int nr = static_cast<int>(rend - r0 < kGramRows ? rend - r0 : kGramRows);
-    for (int e = threadIdx.x; e < nr * bx; e += 256) {
-      const int rr = e / bx, c = e - rr * bx;
-      xs[e] = X[(r0 + rr) * ldx + c];
-    }
-    for (int e = threadIdx.x; e < nr * gy; e += 256) {
-      const int rr = e / gy, c = e - rr * gy;
-      ys[e] = Y[(r0 + rr) * ldy + c];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int pr = threadIdx.x + q * 256;
-      if (pr < npair) {
-        const int i = pr / gy, j = pr - (pr / gy) * gy;
-        double a = acc[q];
-        for (int rr = 0; rr < nr; ++rr) a += xs[rr * bx + i] * ys[rr * gy + j];
-        acc[q] = a;
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int pr = threadIdx.x + q * 256;
-    if (pr < npair) partial[static_cast<int64_t>(blockIdx.x) * npair + pr] = acc[q];
-  }
-}
-
-int tall_gram_blocks(int64_t D) {
-  int64_t nb = D / 1024;
-  if (nb < 1) nb = 1;
-  if (nb > 1024) nb = 1024;
-  return static_cast<int>(nb);
-}
-
-hipError_t launch_tall_gram(const double *X, int64_t ldx, int bx, const double *Y, int64_t ldy, int gy, int64_t D,
-                            double *partial, int nblk, double *out, hipStream_t s) {
-  if (bx < 1 || gy < 1 || bx * gy > 1024) return hipErrorInvalidValue;
-  const size_t lds = sizeof(double) * kGramRows * (bx + gy);
-  hipLaunchKernelGGL(k_tall_gram, dim3(nblk), dim3(256), lds, s, X, ldx, bx, Y, ldy, gy, D, partial);
-  reduce_partials(partial, nblk, bx * gy, out, s);
-  return hipGetLastError();
-}
-
 // Moments from the anchors' Gram products (see anchor_projection): thread (part, i, j) walks the
 // derivation rules in order; rule c takes block (part na + ai, q) of the Gram product G (row-major,
 // row stride m) scaled by scale[part], and gives M_c[i][j] = s G[.][.] (other < 0) or
