@@ -295,45 +295,76 @@ __global__ void k_fill_empty(unsigned long long *p, int64_t n) {
   if (i < n) p[i] = kEmpty;
 }
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2du __attribute__((ext_vector_type(2), aligned(8)));  // two doubles of a row of any stride
+
 // T of each compact-WY block of kWY reflectors, k0 = items[].at: H_k0 ... H_(k0+kb-1) = I - V^T T V
 // with T_jj = beta_j and T[0:j, j] = -beta_j T[0:j, 0:j] G[0:j, j], G the Gram matrix of the block's
-// rows of V (tiles of 32 columns through LDS, 4 x 4 entries a thread).
+// rows of V.  G's ten 16 x 16 tiles on or above the diagonal on the FP64 matrix cores: each wave
+// takes a quarter of the columns, 16 at a time (a lane's four elements of a row are the k of four
+// steps, in the same order for both operands), and the parts are added in LDS.
 __global__ __launch_bounds__(256) void k_wy_t(const TriProb *probs, const BatchWyItem *items) {
-  __shared__ double Vs[kWY][33];
   __shared__ double G[kWY][kWY + 1];
   __shared__ double Ts[kWY][kWY + 1];
   __shared__ double bet[kWY];
   const BatchWyItem it = items[blockIdx.x];
   const TriProb P = probs[it.prob];
   const int n = P.n, tid = threadIdx.x, k0 = it.at, kb = min(kWY, n - 2 - k0);
-  const int ti = (tid >> 4) * 4, tj = (tid & 15) * 4;
-  double acc[4][4] = {};
-  for (int c0 = (k0 + 1) / 32 * 32; c0 < n; c0 += 32) {
-    for (int e = tid; e < kWY * 32; e += 256) {
-      const int r = e >> 5, c = c0 + (e & 31);
-      Vs[r][e & 31] = (r < kb && c < n) ? P.V[static_cast<int64_t>(k0 + r) * n + c] : 0.0;
-    }
-    __syncthreads();
-    for (int c = 0; c < 32; ++c) {
-      double vi[4], vj[4];
+  const int lane = tid & 63, wave = tid >> 6, li = lane & 15, lq = lane >> 4;
+  v4d acc[10];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        vi[q] = Vs[ti + q][c];
-        vj[q] = Vs[tj + q][c];
+  for (int t = 0; t < 10; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](double(&v)[4][4], int c0) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const double *row = P.V + static_cast<int64_t>(k0 + 16 * g + li) * n + c0 + 4 * lq;
+      const bool in = 16 * g + li < kb;
+      if (c0 + 16 <= n) {
+        const v2du a = in ? *reinterpret_cast<const v2du *>(row) : v2du{0.0, 0.0};
+        const v2du b = in ? *reinterpret_cast<const v2du *>(row + 2) : v2du{0.0, 0.0};
+        v[g][0] = a[0];
+        v[g][1] = a[1];
+        v[g][2] = b[0];
+        v[g][3] = b[1];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[g][e] = (in && c0 + 4 * lq + e < n) ? row[e] : 0.0;
       }
+    }
+  };
+  double cur[4][4], nxt[4][4];
+  int c0 = ((k0 + 1) / 16 + wave) * 16;  // the block's rows are zero before column k0 + 1
+  if (c0 < n) load(cur, c0);
+  for (; c0 < n; c0 += 64) {
+    if (c0 + 64 < n) load(nxt, c0 + 64);
+    int t = 0;
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] += vi[p] * vj[q];
+      for (int j = i; j < 4; ++j, ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[i][e], cur[j][e], acc[t], 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cur[g][e] = nxt[g][e];
+  }
+  if (tid < kb) bet[tid] = P.beta[k0 + tid];
+  for (int w = 0; w < 4; ++w) {  // the waves' parts in order
+    if (wave == w) {
+      int t = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = i; j < 4; ++j, ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            double &g = G[16 * i + lq + 4 * e][16 * j + li];
+            g = (w == 0 ? 0.0 : g) + acc[t][e];
+          }
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int p = 0; p < 4; ++p)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) G[ti + p][tj + q] = acc[p][q];
-  if (tid < kb) bet[tid] = P.beta[k0 + tid];
-  __syncthreads();
   for (int j = 0; j < kb; ++j) {
     if (tid < j) {
       double t = 0.0;
