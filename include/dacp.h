@@ -127,7 +127,7 @@ dacp_status dacp_set_tile(dacp_ctx ctx, int tile_elems);
  *   "blocked"     dense eigensolver: panel tridiagonalisation and compact-WY Q formation for
  *                 n >= value (default 3500, at least 256; 0 = never)
  *   "dc"          dense eigensolver: eigenvectors by divide and conquer for n >= value
- *                 (default 96; matrices below the "blocked" value of up to 2048 rows always take it,
+ *                 (default 96; matrices below the "blocked" value of up to 3072 rows always take it,
  *                 unless it is 0 = always implicit QR with replayed rotations)
  * Results agree for every setting up to the rounding order of each element's sum ("moment_explicit":
  * within the values' certified error estimates, since S and P are formed differently).

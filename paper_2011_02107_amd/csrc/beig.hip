@@ -789,7 +789,7 @@ hipError_t launch_wy_apply(const BatchEigProblem *probs, const BatchWyItem *item
   if (max_n <= 512) hipLaunchKernelGGL(k_wy_apply<8>, grid, block, 0, s, probs, items);
   else if (max_n <= 1024) hipLaunchKernelGGL(k_wy_apply<16>, grid, block, 0, s, probs, items);
   else if (max_n <= 1536) hipLaunchKernelGGL(k_wy_apply<24>, grid, block, 0, s, probs, items);
-  else if (max_n <= kBatchEigMaxN) hipLaunchKernelGGL(k_wy_apply<32>, grid, block, 0, s, probs, items);
+  else if (max_n <= kWyApplyMaxN) hipLaunchKernelGGL(k_wy_apply<32>, grid, block, 0, s, probs, items);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -2962,7 +2962,7 @@ class EigRendezvous {
     Arrival me;
     me.ctx = ctx;
     for (const Req &r : reqs) {
-      if (r.n <= dacp::kBatchEigMaxN) me.jobs.push_back({r.n, r.A, r.n, r.w, r.Z});
+      if (dacp::syev_on_chip(ctx, r.n)) me.jobs.push_back({r.n, r.A, r.n, r.w, r.Z});
       else if (big == DACP_OK) big = dacp::gpu_syev(ctx, r.n, r.A, r.n, r.w, r.Z);
     }
     hipEvent_t ev = nullptr;

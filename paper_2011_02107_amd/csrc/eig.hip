@@ -1,5 +1,5 @@
 // Dense symmetric eigen-decomposition for the subspace problem (App. C).  Up
-// to 2048 rows: tridiag.hip.  Beyond: Householder tridiagonalisation on the
+// to 3072 rows: tridiag.hip.  Beyond: Householder tridiagonalisation on the
 // GPU column by column (in panels from the "blocked" knob on), divide and
 // conquer (dc.hip) and the product with the Householder Q; with the "dc" knob
 // off, implicit symmetric QR with a Wilkinson shift on the host (O(n^2) scalar
@@ -407,9 +407,9 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
     }
     return DACP_OK;
   }
-  // Up to 2048 rows the matrix stays in registers across the GPU (tridiag.hip), unless the knobs ask
-  // for the panel form or for implicit QR.
-  if (n <= kBatchEigMaxN && ctx->dc_min_n > 0 && !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB)))
+  // While the registers of the GPU hold the matrix it stays there (tridiag.hip; 3072 rows on 256 compute
+  // units), unless the knobs ask for the panel form or for implicit QR.
+  if (syev_on_chip(ctx, n) && ctx->dc_min_n > 0 && !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB)))
     return syev_jobs(ctx, {{n, A, ld, w, Zrows}});
   double *dv = nullptr, *dp = nullptr, *dd = nullptr, *de = nullptr, *db = nullptr;
   DACP_HIP(ctx, hipMalloc(&dv, sizeof(double) * n));

@@ -173,6 +173,7 @@ constexpr int kBatchEigMaxN = 2048;
 // in each problem's work (V n x n, then T block after block), max_n the largest n of the items.
 constexpr int kWY = 64;
 constexpr int kWyRows = 16;
+constexpr int kWyApplyMaxN = 2048;  // launch_wy_apply's rows are held in registers
 struct BatchWyItem {
   int prob, at;
 };
@@ -461,15 +462,17 @@ struct DcJob {
   double *Z, *work, *w;
 };
 size_t dc_work_doubles(int n);
-// Eigen-decompositions of matrices of up to 2048 rows (tridiag.hip): A device symmetric (row stride
-// lda, read only), w host ascending, Z device n x n (row j = eigenvector j) or null.  Waits for the
-// context's stream.
+// Eigen-decompositions of several matrices at once (tridiag.hip): A device symmetric (row stride lda),
+// w host ascending, Z device n x n (row j = eigenvector j) or null.  Waits for the context's stream.
+// Matrices that syev_on_chip refuses go through gpu_syev, which destroys A, one after the other.
 struct SyevJob {
   int n;
-  const double *A;
+  double *A;
   int64_t lda;
   double *w, *Z;
 };
+// the compute units' registers hold a matrix of n rows
+bool syev_on_chip(dacp_ctx ctx, int n);
 dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &jobs);
 dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs);
 }  // namespace dacp

@@ -1,4 +1,4 @@
-// Dense symmetric eigensolver for matrices of up to 2048 rows, one or many at once (App. C's two
+// Dense symmetric eigensolver for matrices of up to 3072 rows, one or many at once (App. C's two
 // eigen-decompositions): Householder tridiagonalisation with the matrix held in registers across
 // the GPU, divide and conquer on the tridiagonals (dc.hip), and the reflectors applied to the
 // eigenvectors in compact WY blocks.
@@ -392,12 +392,42 @@ struct TriShape {
 const TriShape kTriShapes[] = {
     DACP_TRI(4, 1, 8), DACP_TRI(4, 1, 64), DACP_TRI(8, 1, 8), DACP_TRI(8, 1, 64), DACP_TRI(12, 1, 8), DACP_TRI(12, 1, 48),
     DACP_TRI(8, 2, 8), DACP_TRI(8, 2, 36), DACP_TRI(8, 3, 8), DACP_TRI(8, 3, 24), DACP_TRI(8, 4, 8), DACP_TRI(8, 4, 16),
+    DACP_TRI(8, 5, 12), DACP_TRI(12, 4, 12),
 };
 #undef DACP_TRI
 
 int tri_wgs(int n, int r) { return (n + r - 1) / r; }
 
+// Z <- Z Q^T for one matrix of more rows than k_wy_apply's registers take, the same product a block
+// at a time through the GEMM: W1 = Z V_j^T, W2 = W1 T_j^T, Z -= W2 V_j on the columns after k0.
+// w: 2 n kWY doubles.
+dacp_status wy_gemm(dacp_ctx ctx, int n, const double *V, double *Z, double *w) {
+  hipStream_t st = ctx->stream;
+  const double *T = V + static_cast<int64_t>(n) * n;
+  double *w2 = w + static_cast<int64_t>(n) * kWY;
+  for (int k0 = (n - 3) / kWY * kWY; k0 >= 0; k0 -= kWY) {
+    const int kb = std::min(kWY, n - 2 - k0), c0 = k0 + 1;
+    const double *Vj = V + static_cast<int64_t>(k0) * n + c0;
+    const double *Tj = T + static_cast<int64_t>(k0 / kWY) * kWY * kWY;
+    DACP_HIP(ctx, launch_dgemm(0, 1, n, kb, n - c0, 1.0, Z + c0, n, Vj, n, 0.0, w, kb, 0, st));
+    DACP_HIP(ctx, launch_dgemm(0, 1, n, kb, kb, 1.0, w, kb, Tj, kb, 0.0, w2, kb, 0, st));
+    DACP_HIP(ctx, launch_dgemm(0, 0, n, n - c0, kb, -1.0, w2, kb, Vj, n, 1.0, Z + c0, n, 0, st));
+  }
+  return DACP_OK;
+}
+
 }  // namespace
+
+bool syev_on_chip(dacp_ctx ctx, int n) {
+  int row = 0, wgs = 0;
+  for (const TriShape &s : kTriShapes) {
+    const int len = 64 * s.nwv * s.ne;
+    if (len < n || (row && len > row)) continue;
+    row = len;
+    wgs = tri_wgs(n, s.r);  // the last shape of a row length has the most rows a workgroup
+  }
+  return row > 0 && wgs <= ctx->num_cus;
+}
 
 // The tridiagonalisations: matrices of similar size go together, largest first, each launch taking
 // as many as the compute units hold (one workgroup each).
@@ -429,7 +459,7 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
       shape = &s;
       if (need <= ctx->num_cus) break;
     }
-    if (!shape || tri_wgs(probs[order[at]].n, shape->r) > ctx->num_cus)
+    if (!shape || tri_wgs(probs[order[at]].n, shape->r) > ctx->num_cus)  // syev_on_chip's rule
       return set_err(ctx, DACP_E_HIP, "eigensolver: matrix does not fit the device's compute units");
     Launch ln{shape->fn, 64 * shape->nwv, static_cast<int>(wg_prob.size()), 0};
     for (; at < np; ++at) {
@@ -468,13 +498,17 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
   return DACP_OK;
 }
 
-dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &jobs) {
+dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
   hipStream_t st = ctx->stream;
+  std::vector<SyevJob> jobs;
+  for (const SyevJob &j : all) {
+    if (syev_on_chip(ctx, j.n)) jobs.push_back(j);
+    else DACP_TRY(gpu_syev(ctx, j.n, j.A, j.lda, j.w, j.Z));
+  }
   const int np = static_cast<int>(jobs.size());
   if (np == 0) return DACP_OK;
   size_t zs = 0, vs = 0, xs = 0, ds = 0;
   for (const SyevJob &j : jobs) {
-    if (j.n < 1 || j.n > kBatchEigMaxN) return set_err(ctx, DACP_E_INVALID, "eigensolver: need 1 <= n <= 2048");
     const size_t nn = static_cast<size_t>(j.n) * j.n;
     if (!j.Z) zs += nn;
     vs += batch_syev_work_doubles(j.n);
@@ -504,9 +538,10 @@ dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &jobs) {
     x += std::max(dc_work_doubles(j.n), 2 * nn);
     d += 3 * static_cast<size_t>(j.n);
     if (j.Z && j.n > 2) {
-      max_n = std::max(max_n, j.n);
+      if (j.n <= kWyApplyMaxN) max_n = std::max(max_n, j.n);
       for (int k0 = 0; k0 < j.n - 2; k0 += kWY) prep.push_back({i, k0});
-      for (int r0 = 0; r0 < j.n; r0 += kWyRows) apply.push_back({i, r0});
+      if (j.n <= kWyApplyMaxN)
+        for (int r0 = 0; r0 < j.n; r0 += kWyRows) apply.push_back({i, r0});
     }
   }
   DACP_TRY(tridiagonalise(ctx, probs, bp.as<TriProb>()));
@@ -524,6 +559,9 @@ dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &jobs) {
     DACP_HIP(ctx, hipGetLastError());
     DACP_HIP(ctx, launch_wy_apply(bw.as<BatchEigProblem>(), bi.as<BatchWyItem>() + np_items,
                                   static_cast<int>(apply.size()), max_n, st));
+    for (int i = 0; i < np; ++i)  // the divide and conquer's scratch is free again
+      if (jobs[i].Z && jobs[i].n > kWyApplyMaxN)
+        DACP_TRY(wy_gemm(ctx, jobs[i].n, wy[i].work, jobs[i].Z, probs[i].X));
     DACP_HIP(ctx, hipStreamSynchronize(st));  // the scratch is released on return
   }
   return DACP_OK;

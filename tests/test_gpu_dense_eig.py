@@ -72,3 +72,24 @@ def test_syev_sizes(ctx, n):
 @pytest.mark.parametrize("n", [40, 97, 300, 777])
 def test_syev_deflation(ctx, kind, n):
     check(ctx, matrix(kind, n))
+
+
+@pytest.mark.parametrize("n", [2050, 2561, 3072, 3073])
+def test_syev_largest_on_chip(ctx, n):
+    """Beyond 2048 rows the reflectors are applied a block at a time through the GEMM; beyond 3072 the
+    matrix stays in memory.  A = Q diag(lam) Q^T by one reflector Q, so that the spectrum is known."""
+    rng = np.random.default_rng(n)
+    lam = np.sort(rng.standard_normal(n))
+    u = rng.standard_normal(n)
+    u *= np.sqrt(2.0) / np.linalg.norm(u)
+    a = np.diag(lam) - np.outer(u, u * lam) - np.outer(u * lam, u) + (u @ (u * lam)) * np.outer(u, u)
+    a = 0.5 * (a + a.T)
+    A = torch.as_tensor(a, device="cuda:0").contiguous()
+    Z = torch.empty_like(A)
+    w = B.dacp_syev(ctx, A.clone(), Z)
+    norm = np.abs(lam).max()
+    wt = torch.as_tensor(w, device="cuda:0")
+    eye = torch.eye(n, dtype=torch.float64, device="cuda:0")
+    assert np.abs(w - lam).max() <= 20 * n * EPS * norm
+    assert float((Z @ Z.T - eye).abs().max()) <= 20 * n * EPS
+    assert float((Z @ A - wt[:, None] * Z).abs().max()) <= 20 * n * EPS * norm
