@@ -665,16 +665,19 @@ typedef double v2du __attribute__((ext_vector_type(2), aligned(8)));  // two dou
 // block first, Z <- Z - ((Z V_j^T) T_j^T) V_j on the columns after k0 (V_j is zero on the others).
 //
 // The rows stay in registers through every block, as FP64 MFMA accumulators of Z^T: tile t of a
-// wave (tiles wave, wave + 4, ...; 16 columns of Z each) has accumulator row q + 4 e (lane 16 q + i, item e)
+// wave (tiles wave, wave + 8, ...; 16 columns of Z each) has accumulator row q + 4 e (lane 16 q + i, item e)
 // for column 16 t + 4 q + e and accumulator column i for row i of Z.  An accumulator is laid out as
 // the B operand of the next product over its rows, so W1^T = V_j Z^T takes the tiles as they are
-// (A: four consecutive elements of a row of V_j per lane), the four waves' parts are added in LDS,
+// (A: four consecutive elements of a row of V_j per lane), the eight waves' parts are added in LDS,
 // W2^T = T_j W1^T takes that sum, and Z^T -= V_j^T W2^T accumulates into the tiles.  V_j is read
-// twice from L2; nothing else moves.  (With the rows in LDS, a reflector at a time against 8 of
-// them, this took 3.7 ms at n = 1237.)
+// twice from L2; nothing else moves.  A matrix has n / 16 workgroups, a third of the compute units at
+// n = 1237, so each is as wide as its registers allow: eight waves 448 us there, four with twice the
+// tiles 558 (and 604 bytes of spills a lane at 2048 columns).  (With the rows in LDS, a reflector at a
+// time against 8 of them: 3.7 ms.)
+constexpr int kWyWaves = 8;
 template <int NT>
-__global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *probs, const WyItem *items) {
-  __shared__ double part[4][kWY][17];
+__global__ __launch_bounds__(64 * kWyWaves, 2) void k_wy_apply(const BatchEigProblem *probs, const WyItem *items) {
+  __shared__ double part[kWyWaves][kWY][17];
   __shared__ double w2[kWY][17];
   const WyItem it = items[blockIdx.x];
   const BatchEigProblem pb = probs[it.prob];
@@ -688,7 +691,7 @@ __global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *prob
   v4d z[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int c = 16 * (wave + 4 * t) + 4 * lq;
+    const int c = 16 * (wave + kWyWaves * t) + 4 * lq;
 #pragma unroll
     for (int e = 0; e < 4; ++e) z[t][e] = (zrow < n && c + e < n) ? Z[c + e] : 0.0;
   }
@@ -709,7 +712,7 @@ __global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *prob
     for (int g = 0; g < 4; ++g) w1[g] = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int tt = wt + 4 * t, c = 16 * tt + 4 * lq;
+      const int tt = wt + kWyWaves * t, c = 16 * tt + 4 * lq;
       asm volatile("" ::: "memory");  // the next tiles' loads stay behind: no registers for them
       if (tt < t0 || 16 * tt >= n) continue;
       double a[4][4];
@@ -740,16 +743,26 @@ __global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *prob
 #pragma unroll
       for (int e = 0; e < 4; ++e) part[wave][16 * g + lq + 4 * e][li] = w1[g][e];
     __syncthreads();
-    // W2^T = T_j W1^T, wave w the rows 16 w .. 16 w + 15
-    {
+    double sum[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int q = 32 * h + (tid >> 4), c = tid & 15;
+      sum[h] = part[0][q][c];
+#pragma unroll
+      for (int w = 1; w < kWyWaves; ++w) sum[h] += part[w][q][c];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) part[0][32 * h + (tid >> 4)][tid & 15] = sum[h];
+    __syncthreads();
+    // W2^T = T_j W1^T, wave w < 4 the rows 16 w .. 16 w + 15
+    if (wave < 4) {
       v4d acc = {0.0, 0.0, 0.0, 0.0};
       const int r = 16 * wave + li;
 #pragma unroll
       for (int s = 0; s < kWY / 4; ++s) {
         const int q = 4 * s + lq;
         const double tv = (r < kb && q < kb) ? Tj[r * kb + q] : 0.0;
-        const double b = (part[0][q][li] + part[1][q][li]) + (part[2][q][li] + part[3][q][li]);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, b, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, part[0][q][li], acc, 0, 0, 0);
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) w2[16 * wave + lq + 4 * e][li] = -acc[e];
@@ -760,7 +773,7 @@ __global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *prob
     for (int s = 0; s < kWY / 4; ++s) b2[s] = w2[4 * s + lq][li];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int tt = wt + 4 * t, c = 16 * tt + ci;
+      const int tt = wt + kWyWaves * t, c = 16 * tt + ci;
       asm volatile("" ::: "memory");
       if (tt < t0 || 16 * tt >= n) continue;
       double a[kWY / 4];
@@ -773,7 +786,7 @@ __global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *prob
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int c = 16 * (wave + 4 * t) + 4 * lq;
+    const int c = 16 * (wave + kWyWaves * t) + 4 * lq;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (zrow < n && c + e < n) Z[c + e] = z[t][e];
@@ -785,11 +798,11 @@ __global__ __launch_bounds__(256, 1) void k_wy_apply(const BatchEigProblem *prob
 hipError_t launch_wy_apply(const BatchEigProblem *probs, const BatchWyItem *items, int count, int max_n,
                            hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>(count)), block(256);
-  if (max_n <= 512) hipLaunchKernelGGL(k_wy_apply<8>, grid, block, 0, s, probs, items);
-  else if (max_n <= 1024) hipLaunchKernelGGL(k_wy_apply<16>, grid, block, 0, s, probs, items);
-  else if (max_n <= 1536) hipLaunchKernelGGL(k_wy_apply<24>, grid, block, 0, s, probs, items);
-  else if (max_n <= kWyApplyMaxN) hipLaunchKernelGGL(k_wy_apply<32>, grid, block, 0, s, probs, items);
+  const dim3 grid(static_cast<unsigned>(count)), block(64 * kWyWaves);
+  if (max_n <= 512) hipLaunchKernelGGL(k_wy_apply<4>, grid, block, 0, s, probs, items);
+  else if (max_n <= 1024) hipLaunchKernelGGL(k_wy_apply<8>, grid, block, 0, s, probs, items);
+  else if (max_n <= 1536) hipLaunchKernelGGL(k_wy_apply<12>, grid, block, 0, s, probs, items);
+  else if (max_n <= kWyApplyMaxN) hipLaunchKernelGGL(k_wy_apply<16>, grid, block, 0, s, probs, items);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
