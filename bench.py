@@ -28,12 +28,12 @@ HBM_PEAK_GBPS = 8000.0
 # HBM bytes per evolution launch measured with the FETCH_SIZE and WRITE_SIZE counters (each scaled by
 # its reading on a 256 MiB device copy), for the kernel build and launch shape named by the key:
 # (workload, kernel pair, column group).  Reported as roofline.traffic only for that configuration.
-EVOLUTION_KERNELS = "k_rec_lo/k_rec_hi v5"
+EVOLUTION_KERNELS = "k_rec_lo/k_rec_hi v6"
 # key: (workload, kernel build, group, threads, fused tile, high-tile rows knob, XCD tile order knob)
-MEASURED_TRAFFIC = {("chain_L20_N5000", EVOLUTION_KERNELS, 8, 1024, 8192, 0, 2): 279.67e6}
+MEASURED_TRAFFIC = {("chain_L20_N5000", EVOLUTION_KERNELS, 8, 1024, 8192, 0, 2): 275.38e6}
 # Filter chain: counted bytes per order of one 8-column group (low + high kernel), FP32 and FP64 orders;
 # key: (workload, kernel build, FP32 filter group, FP64 filter group).
-FILTER_TRAFFIC_PER_ORDER = {("chain_L20_N5000", EVOLUTION_KERNELS, 8, 8): {"fp32": 306.3e6, "fp64": 628.0e6}}
+FILTER_TRAFFIC_PER_ORDER = {("chain_L20_N5000", EVOLUTION_KERNELS, 8, 8): {"fp32": 306.4e6, "fp64": 613.5e6}}
 
 
 def parse():
