@@ -15,8 +15,9 @@ namespace dacp {
 
 namespace {
 
-// polls of one value before a workgroup gives up (seconds; a step takes microseconds)
-constexpr int kSpinLimit = 1 << 21;
+// polls of one value before a workgroup gives up: tens of seconds, where a step takes microseconds, since
+// other streams' kernels may hold the compute units that the launch's last workgroups wait for
+constexpr int kSpinLimit = 1 << 24;
 constexpr unsigned long long kEmpty = ~0ull;  // exchange slot not written yet
 
 // One matrix of a launch: workgroups wg0 .. wg0 + G - 1 hold its rows.
@@ -67,7 +68,8 @@ __device__ __forceinline__ void publish(double *slot, double v) {
 // Householder tridiagonalisation of every matrix of the launch at once.  A column's step is a
 // matrix-vector product and a rank-2 update, microseconds of arithmetic at n of a thousand, so the
 // cost is what surrounds it: as four launches a column (15 us and the gaps between them, the matrix
-// read and written through L2 each time) n = 1237 took 25 ms.  Here
+// read and written through L2 each time) n = 1237 took 25 ms; now 5.7 ms, 4.65 us a column (5.3 at n = 2047,
+// 6.3 at 2400), of which the exchange's way through the Infinity Cache is most.  Here
 //   - the matrix lives in registers: workgroup g of the matrix's G holds rows g, g + G, ..., thread t of
 //     it the columns t + e * (its threads), so a step touches no memory but the exchange, and a
 //     thread's share of the vectors v, w and of row k is as small as its share of a row;
@@ -383,7 +385,9 @@ __global__ __launch_bounds__(256) void k_wy_t(const TriProb *probs, const BatchW
 
 // Shapes of k_tridiag: rows of up to 64 nwv ne elements, r of them a workgroup.  Of the two r of a row
 // length the smaller gives the shortest step, the larger (as much as the registers hold) room for
-// more matrices in a launch.
+// more matrices in a launch.  Past 2048 rows 256 compute units need 12 rows each: at n = 2400 five
+// elements a thread of eight waves take 20.6 ms a solve, four of twelve waves 27.2; six of eight
+// spill, so twelve waves take the rest.
 struct TriShape {
   int nwv, ne, r;
   const void *fn;
@@ -400,7 +404,7 @@ int tri_wgs(int n, int r) { return (n + r - 1) / r; }
 
 // Z <- Z Q^T for one matrix of more rows than k_wy_apply's registers take, the same product a block
 // at a time through the GEMM: W1 = Z V_j^T, W2 = W1 T_j^T, Z -= W2 V_j on the columns after k0.
-// w: 2 n kWY doubles.
+// w: 2 n kWY doubles.  3.8 ms at n = 2400; one reflector a launch (15 us each) took 36.
 dacp_status wy_gemm(dacp_ctx ctx, int n, const double *V, double *Z, double *w) {
   hipStream_t st = ctx->stream;
   const double *T = V + static_cast<int64_t>(n) * n;
