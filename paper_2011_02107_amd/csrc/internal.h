@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
+#include <exception>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -420,12 +421,20 @@ struct dacp_ham_s {
 };
 namespace dacp {
 // fn(i) for i in [0, count) on up to `threads` host threads, the caller among them (fewer, down to the
-// caller alone, when the system gives no more).
+// caller alone, when the system gives no more).  The first exception of an fn is thrown again here, once
+// every thread has ended.
 template <typename F>
 void host_parallel(int count, int threads, F fn) {
   std::atomic<int> next{0};
+  std::exception_ptr err;
+  std::mutex mu;
   auto work = [&] {
-    for (int i = next++; i < count; i = next++) fn(i);
+    try {
+      for (int i = next++; i < count; i = next++) fn(i);
+    } catch (...) {
+      std::lock_guard<std::mutex> lk(mu);
+      if (!err) err = std::current_exception();
+    }
   };
   std::vector<std::thread> ts;
   try {
@@ -434,6 +443,7 @@ void host_parallel(int count, int threads, F fn) {
   }
   work();
   for (auto &th : ts) th.join();
+  if (err) std::rethrow_exception(err);
 }
 // Error helpers used by the API layer.
 dacp_status set_err(dacp_ctx ctx, dacp_status st, const std::string &msg);

@@ -502,7 +502,7 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
   return DACP_OK;
 }
 
-dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
+static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
   hipStream_t st = ctx->stream;
   std::vector<SyevJob> jobs;
   for (const SyevJob &j : all) {
@@ -569,6 +569,14 @@ dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
     DACP_HIP(ctx, hipStreamSynchronize(st));  // the scratch is released on return
   }
   return DACP_OK;
+}
+
+dacp_status syev_jobs(dacp_ctx ctx, const std::vector<SyevJob> &jobs) {
+  try {
+    return solve_jobs(ctx, jobs);
+  } catch (...) {  // the host tables; the callers are C entry points
+    return set_err(ctx, DACP_E_NOMEM, "eigensolver: host allocation failed");
+  }
 }
 
 }  // namespace dacp
