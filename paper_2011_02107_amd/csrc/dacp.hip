@@ -1876,7 +1876,7 @@ dacp_status moment_dots(dacp_ctx ctx, dacp_ham h, double e_bound, int M, int nve
   hipStream_t s = ctx->stream;
   const int kmax = M / 2;
   d.assign(2 * kmax + 2, 0.0);
-  if (h->L <= kOnChipL) {
+  if (onchip_fits(h, nvec, nvec, M)) {
     DACP_TRY(onchip_order(ctx, h));
     DevBuf dout, dspec;
     DACP_HIP(ctx, dout.alloc(static_cast<size_t>(M) * nvec * sizeof(double)));
