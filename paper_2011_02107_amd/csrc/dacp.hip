@@ -3229,11 +3229,7 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
   std::vector<int> acc(count, 0);
   for (int w = 0; w < nw; ++w) {
     dacp_ctx_s &c = wctx[w];
-    c.device = ctx->device;
-    c.tile_elems = ctx->tile_elems;
-    c.two_pass_min_L = ctx->two_pass_min_L;
-    c.dc_min_n = ctx->dc_min_n;
-    c.blocked_min_n = ctx->blocked_min_n;
+    c.worker_of(*ctx);
     DACP_HIP(ctx, hipStreamCreateWithFlags(&c.stream, hipStreamNonBlocking));
   }
   EigRendezvous rendezvous(nw, ctx->device);

@@ -385,6 +385,17 @@ struct dacp_ctx_s {
   int dc_min_n = 96;           // eigenvectors by divide and conquer from this size on (0 = never)
   int blocked_min_n = 3500;    // blocked tridiagonalisation and compact-WY Q from this size on (0 = never);
                                // below it the unblocked form issues fewer launches and is faster
+  // A worker thread's context for o's device: what the device is (num_cus bounds the cooperative launches
+  // and not only the tuning) and the knobs of the stages that workers run.
+  void worker_of(const dacp_ctx_s &o) {
+    device = o.device;
+    num_cus = o.num_cus;
+    batch_workers = o.batch_workers;
+    tile_elems = o.tile_elems;
+    two_pass_min_L = o.two_pass_min_L;
+    dc_min_n = o.dc_min_n;
+    blocked_min_n = o.blocked_min_n;
+  }
 };
 
 struct dacp_ham_s {

@@ -1,0 +1,25 @@
+"""Host code that needs the runtime's headers but no device, in harnesses of tests/native/ (CPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2011_02107_amd", "csrc")
+NATIVE = os.path.join(ROOT, "tests", "native")
+CXX = shutil.which(os.environ.get("CXX", "g++"))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+pytestmark = pytest.mark.skipif(
+    CXX is None or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime.h")),
+    reason="no host C++ compiler or HIP headers")
+
+
+def test_worker_contexts_describe_the_callers_device(tmp_path):
+    exe = str(tmp_path / "worker_context")
+    cmd = [CXX, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-isystem", os.path.join(ROCM, "include"),
+           os.path.join(NATIVE, "worker_context_harness.cpp"), "-o", exe, "-lpthread"]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "0 failures" in r.stdout, r.stderr
