@@ -2354,9 +2354,13 @@ dacp_status dacp_syev_batched(dacp_ctx ctx, int count, const int *n, double *con
   for (int i = 0; i < count; ++i)
     if (n[i] < 1 || n[i] > dacp::kBatchEigMaxN || !A[i] || !w[i])
       return set_err(ctx, DACP_E_INVALID, "syev_batched: need 1 <= n <= 2048 and A, w for every matrix");
-  std::vector<dacp::SyevJob> jobs;
-  for (int i = 0; i < count; ++i) jobs.push_back({n[i], A[i], n[i], w[i], Z[i]});
-  return dacp::syev_jobs(ctx, jobs);
+  try {
+    std::vector<dacp::SyevJob> jobs;
+    for (int i = 0; i < count; ++i) jobs.push_back({n[i], A[i], n[i], w[i], Z[i]});
+    return dacp::syev_jobs(ctx, jobs);
+  } catch (...) {
+    return set_err(ctx, DACP_E_NOMEM, "syev_batched: host allocation failed");
+  }
 }
 
 dacp_status dacp_syev_batched_noalloc(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,

@@ -393,7 +393,7 @@ static double wall_ms() {
   return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
-dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows) {
+static dacp_status solve_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows) {
   hipStream_t st = ctx->stream;
   const double t_begin = wall_ms();
   if (n <= 0) return DACP_OK;
@@ -411,12 +411,10 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
   // units), unless the knobs ask for the panel form or for implicit QR.
   if (syev_on_chip(ctx, n) && ctx->dc_min_n > 0 && !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB)))
     return syev_jobs(ctx, {{n, A, ld, w, Zrows}});
-  double *dv = nullptr, *dp = nullptr, *dd = nullptr, *de = nullptr, *db = nullptr;
-  DACP_HIP(ctx, hipMalloc(&dv, sizeof(double) * n));
-  DACP_HIP(ctx, hipMalloc(&dp, sizeof(double) * n));
-  DACP_HIP(ctx, hipMalloc(&dd, sizeof(double) * n));
-  DACP_HIP(ctx, hipMalloc(&de, sizeof(double) * n));
-  DACP_HIP(ctx, hipMalloc(&db, sizeof(double) * n));
+  DevBuf vecs;  // five vectors of the tridiagonalisation
+  const size_t nv = (static_cast<size_t>(n) + 31) / 32 * 32;
+  DACP_HIP(ctx, vecs.alloc(5 * sizeof(double) * nv));
+  double *dv = vecs.as<double>(), *dp = dv + nv, *dd = dp + nv, *de = dd + nv, *db = de + nv;
   DACP_HIP(ctx, hipMemsetAsync(db, 0, sizeof(double) * n, st));
   const int report_every = std::max(1, n / 4);
   const bool blocked = ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB);
@@ -555,13 +553,7 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
     DACP_HIP(ctx, hipMemcpyAsync(qc.p, Zrows, static_cast<size_t>(n) * n * sizeof(double), hipMemcpyDeviceToDevice, st));
     DACP_TRY(to_device(ctx, dd, d.data(), sizeof(double) * n));  // with the last 2 x 2 block's entries
     DACP_TRY(to_device(ctx, de, e.data(), sizeof(double) * n));
-    const dacp_status drc = dc_tridiag_jobs(ctx, {{n, dd, de, zt.as<double>(), work.as<double>(), w}});
-    (void)hipFree(dv);  // the Q-formation kernels, which read db and A, are done
-    (void)hipFree(dp);
-    (void)hipFree(dd);
-    (void)hipFree(de);
-    (void)hipFree(db);
-    if (drc) return drc;
+    DACP_TRY(dc_tridiag_jobs(ctx, {{n, dd, de, zt.as<double>(), work.as<double>(), w}}));
     const double t_dc = wall_ms();
     DACP_HIP(ctx, launch_dgemm(0, 0, n, n, n, 1.0, zt.as<double>(), n, qc.as<double>(), n, 0.0, Zrows, n, 0, st));
     DACP_HIP(ctx, hipStreamSynchronize(st));
@@ -575,13 +567,20 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
   const size_t cap_pairs = flush_pairs + static_cast<size_t>(n);
   std::vector<double> rot;
   std::vector<Sweep> sweeps;
-  double *pinned = nullptr, *drot = nullptr;
+  DevBuf rotbuf;
+  struct Pinned {
+    double *p = nullptr;
+    ~Pinned() {
+      if (p) (void)hipHostFree(p);
+    }
+  } pin;
   dacp_status frc = DACP_OK;
   if (Zrows) {
     rot.reserve(2 * cap_pairs);
-    DACP_HIP(ctx, hipMalloc(&drot, cap_pairs * 2 * sizeof(double)));
-    DACP_HIP(ctx, hipHostMalloc(&pinned, cap_pairs * 2 * sizeof(double), hipHostMallocDefault));
+    DACP_HIP(ctx, rotbuf.alloc(cap_pairs * 2 * sizeof(double)));
+    DACP_HIP(ctx, hipHostMalloc(&pin.p, cap_pairs * 2 * sizeof(double), hipHostMallocDefault));
   }
+  double *const pinned = pin.p, *const drot = rotbuf.as<double>();
   auto flush = [&]() {
     if (sweeps.empty() || frc != DACP_OK) return;
     hipError_t he = hipStreamSynchronize(st);  // the previous batch no longer reads the buffers
@@ -629,13 +628,6 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
   vlog("eigensolver n=%d: QR done", n);
   if (ok && Zrows) flush();
   hipError_t he = hipStreamSynchronize(st);
-  if (drot) (void)hipFree(drot);
-  if (pinned) (void)hipHostFree(pinned);
-  (void)hipFree(dv);
-  (void)hipFree(dp);
-  (void)hipFree(dd);
-  (void)hipFree(de);
-  (void)hipFree(db);
   const double t_replay = wall_ms();
   vlog("eigensolver n=%d timing: tridiagonalise %.0f ms, form Q %.0f ms, QR (host, overlapping replay) %.0f ms, "
        "replay tail %.0f ms", n, t_tri - t_begin, t_q - t_tri, t_qr - t_q, t_replay - t_qr);
@@ -650,21 +642,26 @@ dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, doub
   std::stable_sort(perm.begin(), perm.end(), [&](int i, int j) { return d[i] < d[j]; });
   for (int i = 0; i < n; ++i) w[i] = d[perm[i]];
   if (Zrows) {
-    double *tmp = nullptr;
-    int *dperm = nullptr;
+    DevBuf tmp, dperm;
     const int64_t nn = static_cast<int64_t>(n) * n;
-    DACP_HIP(ctx, hipMalloc(&tmp, sizeof(double) * nn));
-    DACP_HIP(ctx, hipMalloc(&dperm, sizeof(int) * n));
-    DACP_TRY(to_device(ctx, dperm, perm.data(), sizeof(int) * n));
-    DACP_HIP(ctx, hipMemcpyAsync(tmp, Zrows, sizeof(double) * nn, hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_gather_rows, dim3((nn + 255) / 256), dim3(256), 0, st, tmp, (int64_t)n, Zrows, (int64_t)n,
-                       dperm, nullptr, n, n);
+    DACP_HIP(ctx, tmp.alloc(sizeof(double) * nn));
+    DACP_HIP(ctx, dperm.alloc(sizeof(int) * n));
+    DACP_TRY(to_device(ctx, dperm.p, perm.data(), sizeof(int) * n));
+    DACP_HIP(ctx, hipMemcpyAsync(tmp.p, Zrows, sizeof(double) * nn, hipMemcpyDeviceToDevice, st));
+    hipLaunchKernelGGL(k_gather_rows, dim3((nn + 255) / 256), dim3(256), 0, st, tmp.as<double>(), (int64_t)n, Zrows,
+                       (int64_t)n, dperm.as<int>(), nullptr, n, n);
     DACP_HIP(ctx, hipGetLastError());
     DACP_HIP(ctx, hipStreamSynchronize(st));
-    (void)hipFree(tmp);
-    (void)hipFree(dperm);
   }
   return DACP_OK;
+}
+
+dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows) {
+  try {
+    return solve_syev(ctx, n, A, ld, w, Zrows);
+  } catch (...) {  // the host's tables; the callers are C entry points
+    return set_err(ctx, DACP_E_NOMEM, "eigensolver: host allocation failed");
+  }
 }
 
 hipError_t launch_gather_rows(const double *src, int64_t lds, double *dst, int64_t ldd, const int *perm,
