@@ -238,8 +238,9 @@ dacp_status dacp_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, con
  *   P block (p, q) = e_bound (nu_{x+y} + nu_{|x-y|}) / 2,
  * x, y the orders of panels p, q.  psi_e: device [D][b] FP64, 1 <= b <= 128.  S, P: device m x m,
  * row stride ld >= m = b (2n + 1), both triangles written (symmetric parts of the assembled
- * blocks).  m_out (host, may be NULL) gets m.  Memory besides S and P: three D x g FP64 blocks,
- * [psi_E | G psi_E] (D x 2b), up to 256 columns of recorded T_k psi_E (D x 256) and the moments.  Errors as dacp_basis (DACP_E_BOUNDS when |T_{k_m}(G) psi|
+ * blocks).  m_out (host, may be NULL) gets m.  Memory besides S and P: the recurrence's three blocks of
+ * the columns that one launch advances, G psi_E (D x b) and the moments; where there is room also a copy of
+ * psi_E and up to 256 columns of recorded T_k psi_E.  Errors as dacp_basis (DACP_E_BOUNDS when |T_{k_m}(G) psi|
  * exceeds |psi|). */
 dacp_status dacp_basis_moments(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, const double *psi_e, double *S,
                                double *P, int64_t ld, int *m_out);

@@ -1210,6 +1210,23 @@ std::vector<int> moment_slots(const std::vector<int64_t> &orders, int &nslot) {
   return slot_of;
 }
 
+// Columns of a D-row staging block, into z: `want`, or as many as a quarter of the free memory takes past
+// 4 GiB, halved down to `least` until the allocation succeeds; 0 and no block when not even that does.
+int staging_cols(int64_t D, int want, int least, DevBuf &z) {
+  const size_t col = static_cast<size_t>(D) * sizeof(double);
+  if (want > least && col * want > (size_t(4) << 30)) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = 0;
+    want = std::max<int>(least, static_cast<int>(std::min<size_t>(want, free_b / 4 / col)));
+  }
+  while (z.alloc(col * want) != hipSuccess) {
+    (void)hipGetLastError();
+    if (want <= least) return 0;
+    want = std::max(least, want / 2);
+  }
+  return want;
+}
+
 // Moment mode, first pass: filter output psi_e (D x b) -> S and P (device m x m, row stride ld),
 // m = b (2n + 1).  Returns DACP_E_BOUNDS when |T_{k_m}(G) psi_j| exceeds |psi_j| (E_b < ||H||).
 dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, const double *psi_e, double *S,
@@ -1230,22 +1247,56 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
   // The recorded T_k are staged side by side, up to kz columns, and multiplied by [psi_E | G psi_E]^T
   // in one GEMM that gives mu and nu of them all: the left factor is read once for several orders.
   // (One 8-column group and factor at a time, on the vector ALU, a 2^16 x 32 order took 630 us.)
-  const int kz = std::max(256, std::min(b, cg.g * cg.per));
+  // This is the mode for states too long to store a basis, so what it holds gives way to the memory
+  // there is: the staged columns shrink to one launch's, then the products read T_k where it lies, and
+  // psi_E is read from the caller's block.
+  const int nc_max = std::min(b, cg.g * cg.per);
   DevBuf ba, bb, pbuf, left, mu, nu, zb, prod, work, didx, dord;
   DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
-  DACP_HIP(ctx, left.alloc(static_cast<size_t>(D) * 2 * b * sizeof(double)));
   DACP_HIP(ctx, mu.alloc(static_cast<size_t>(nslot) * b * b * sizeof(double)));
   DACP_HIP(ctx, nu.alloc(static_cast<size_t>(nslot) * b * b * sizeof(double)));
-  DACP_HIP(ctx, zb.alloc(static_cast<size_t>(D) * kz * sizeof(double)));
-  DACP_HIP(ctx, prod.alloc(2 * static_cast<size_t>(b) * kz * sizeof(double)));
-  const int sp = dacp::gemm_splits(2 * b, kz, D, 0, ctx->num_cus, 512, 128);
-  if (sp > 1) DACP_HIP(ctx, work.alloc(2 * static_cast<size_t>(sp) * b * kz * sizeof(double)));
-  double *X = left.as<double>();
-  DACP_HIP(ctx, dacp::launch_copy_cols(psi_e, b, X, 2 * b, D, b, ctx->stream));
+  const bool joined = left.alloc(static_cast<size_t>(D) * 2 * b * sizeof(double)) == hipSuccess;
+  if (!joined) {
+    (void)hipGetLastError();
+    DACP_HIP(ctx, left.alloc(static_cast<size_t>(D) * b * sizeof(double)));
+  }
+  const int kz = staging_cols(D, std::max(256, nc_max), nc_max, zb);
+  // rows and columns of one product: both factors or one, the staged columns or a group of T_k
+  const int pm = joined ? 2 * b : b, pn = std::max(kz, cg.g);
+  DACP_HIP(ctx, prod.alloc(static_cast<size_t>(pm) * pn * sizeof(double)));
+  int sp = dacp::gemm_splits(pm, pn, D, 0, ctx->num_cus, 512, 128);
+  if (sp > 1 && work.alloc(static_cast<size_t>(sp) * pm * pn * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    sp = 1;
+  }
+  double *const X = left.as<double>();
+  double *const gpsi = joined ? X + b : X;
+  const int64_t ldg = joined ? 2 * b : b;
+  if (joined) DACP_HIP(ctx, dacp::launch_copy_cols(psi_e, b, X, 2 * b, D, b, ctx->stream));
   for (int c0 = 0; c0 < b; c0 += 64)
-    DACP_TRY(step<double>(ctx, h, std::min(64, b - c0), psi_e + c0, b, X + b + c0, 2 * b, inv_e));
+    DACP_TRY(step<double>(ctx, h, std::min(64, b - c0), psi_e + c0, b, gpsi + c0, ldg, inv_e));
+  // moments of the w columns of Z (row stride ldz), a block of nc for each order of `at`, into columns
+  // c0 .. c0 + nc - 1 of those orders' slots
+  auto products = [&](const double *Z, int64_t ldz, int nc, const std::vector<int64_t> &at, int c0) -> dacp_status {
+    const int w = static_cast<int>(at.size()) * nc;
+    for (int f = 0; f < (joined ? 1 : 2); ++f) {
+      const double *F = joined ? X : f ? gpsi : psi_e;
+      if (sp > 1)
+        DACP_HIP(ctx, dacp::launch_dgemm_splitk(1, 0, pm, w, D, 1.0, F, pm, Z, ldz, 0.0, prod.as<double>(), w, 0, sp,
+                                                work.as<double>(), ctx->stream));
+      else
+        DACP_HIP(ctx, dacp::launch_dgemm(1, 0, pm, w, D, 1.0, F, pm, Z, ldz, 0.0, prod.as<double>(), w, 0, ctx->stream));
+      for (size_t i = 0; i < at.size(); ++i)
+        for (int q = f; q < (joined ? 2 : f + 1); ++q) {
+          const double *src = prod.as<double>() + static_cast<int64_t>(i) * nc + (joined ? q : 0) * static_cast<int64_t>(b) * w;
+          double *dst = (q ? nu : mu).as<double>() + static_cast<int64_t>(slot_of[at[i]]) * b * b + c0;
+          DACP_HIP(ctx, dacp::launch_copy_cols(src, w, dst, b, b, nc, ctx->stream));
+        }
+    }
+    return DACP_OK;
+  };
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
@@ -1257,25 +1308,16 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
     // mu_k[:, g0 .. g0 + nc) = psi_E^T (T_k psi_E)[:, these columns], nu_k likewise with (G psi_E)^T
     std::vector<int64_t> staged;  // orders of the staged blocks of nc columns
     auto flush = [&]() -> dacp_status {
-      const int w = static_cast<int>(staged.size()) * nc;
-      if (w == 0) return DACP_OK;
-      if (sp > 1)
-        DACP_HIP(ctx, dacp::launch_dgemm_splitk(1, 0, 2 * b, w, D, 1.0, X, 2 * b, zb.as<double>(), kz, 0.0,
-                                                prod.as<double>(), w, 0, sp, work.as<double>(), ctx->stream));
-      else
-        DACP_HIP(ctx, dacp::launch_dgemm(1, 0, 2 * b, w, D, 1.0, X, 2 * b, zb.as<double>(), kz, 0.0, prod.as<double>(),
-                                         w, 0, ctx->stream));
-      for (size_t i = 0; i < staged.size(); ++i) {
-        const int64_t off = static_cast<int64_t>(slot_of[staged[i]]) * b * b + g0;
-        const double *src = prod.as<double>() + static_cast<int64_t>(i) * nc;
-        DACP_HIP(ctx, dacp::launch_copy_cols(src, w, mu.as<double>() + off, b, b, nc, ctx->stream));
-        DACP_HIP(ctx, dacp::launch_copy_cols(src + static_cast<int64_t>(b) * w, w, nu.as<double>() + off, b, b, nc,
-                                             ctx->stream));
-      }
+      if (!staged.empty()) DACP_TRY(products(zb.as<double>(), kz, nc, staged, g0));
       staged.clear();
       return DACP_OK;
     };
     auto visit = [&](int64_t k, const double *tk, const double *) -> dacp_status {
+      if (kz == 0) {
+        for (int y = 0; y < groups; ++y)
+          DACP_TRY(products(tk + y * D * gw, gw, std::min(gw, nc - y * gw), {k}, g0 + y * gw));
+        return DACP_OK;
+      }
       DACP_HIP(ctx, dacp::launch_join_cols(tk, D, gw, groups, zb.as<double>() + staged.size() * nc, kz, nc, ctx->stream));
       staged.push_back(k);
       if (static_cast<int>(staged.size() + 1) * nc > kz) return flush();
@@ -1343,13 +1385,14 @@ dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_param
   const int64_t kmax = mp.orders.back();
   const int g = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
   const ColGroups cg = column_groups(ctx, h, b, g, 3, {8});
-  const int kz = 32 * std::min(b, std::max(g, 8));  // staged columns: at least one launch's
   const double inv_e = 1.0 / p->e_bound;
   DevBuf ba, bb, pbuf, zb, wb, dcols;
   DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, pbuf.alloc(cg.elems(D) * sizeof(double)));
-  DACP_HIP(ctx, zb.alloc(static_cast<size_t>(D) * kz * sizeof(double)));
+  // staged columns: 32 groups of the requested width, at least one of the launch's
+  const int kz = staging_cols(D, std::max(32 * g, cg.g), cg.g, zb);
+  if (kz == 0) return set_err(ctx, DACP_E_NOMEM, "moment mode: staging block");
   DACP_HIP(ctx, wb.alloc(static_cast<size_t>(nc) * kz * sizeof(double)));
   DACP_HIP(ctx, dcols.alloc(static_cast<size_t>(kz) * sizeof(int)));
   DACP_HIP(ctx, hipMemsetAsync(Phi, 0, static_cast<size_t>(D) * nc * sizeof(double), ctx->stream));
