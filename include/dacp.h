@@ -289,7 +289,8 @@ dacp_status dacp_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, dou
 /* The same decomposition for `count` matrices together (App. C's two eigen-decompositions for many
  * small subspace problems, the batched-realisation path): Householder tridiagonalisation, divide
  * and conquer, and the reflectors applied to the eigenvectors, each in launches shared by all
- * matrices.  Device memory besides A and Z: about 4 sum n[i]^2 doubles during the call.
+ * matrices.  Device memory besides A and Z: about 4 sum n[i]^2 doubles during the call, or as many
+ * matrices at a time as the device has that much for.
  * n[i] (host): 1 <= n[i] <= 2048.  A[i] (host array of device pointers): symmetric n[i] x n[i],
  * row-major, ld n[i], destroyed.  w[i] (host array of host pointers): n[i] eigenvalues ascending.
  * Z[i] (host array of device pointers, entries may be NULL): n[i] x n[i], row j = eigenvector j.

@@ -502,22 +502,16 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
   return DACP_OK;
 }
 
-static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
+// One round: np matrices together.  A is only read, so a round that fails can be run again.
+static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np) {
   hipStream_t st = ctx->stream;
-  std::vector<SyevJob> jobs;
-  for (const SyevJob &j : all) {
-    if (syev_on_chip(ctx, j.n)) jobs.push_back(j);
-    else DACP_TRY(gpu_syev(ctx, j.n, j.A, j.lda, j.w, j.Z));
-  }
-  const int np = static_cast<int>(jobs.size());
-  if (np == 0) return DACP_OK;
   size_t zs = 0, vs = 0, xs = 0, ds = 0;
-  for (const SyevJob &j : jobs) {
-    const size_t nn = static_cast<size_t>(j.n) * j.n;
-    if (!j.Z) zs += nn;
-    vs += batch_syev_work_doubles(j.n);
-    xs += std::max(dc_work_doubles(j.n), 2 * nn);
-    ds += 3 * static_cast<size_t>(j.n);
+  for (int i = 0; i < np; ++i) {
+    const size_t n = jobs[i].n, nn = n * n;
+    if (!jobs[i].Z) zs += nn;
+    vs += batch_syev_work_doubles(jobs[i].n);
+    xs += std::max(dc_work_doubles(jobs[i].n), 2 * nn);
+    ds += 3 * n;
   }
   DevBuf bz, bv, bx, bd, bp, bi;
   if (zs) DACP_HIP(ctx, bz.alloc(zs * sizeof(double)));
@@ -567,6 +561,31 @@ static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
       if (jobs[i].Z && jobs[i].n > kWyApplyMaxN)
         DACP_TRY(wy_gemm(ctx, jobs[i].n, wy[i].work, jobs[i].Z, probs[i].X));
     DACP_HIP(ctx, hipStreamSynchronize(st));  // the scratch is released on return
+  }
+  return DACP_OK;
+}
+
+static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
+  std::vector<SyevJob> jobs;
+  for (const SyevJob &j : all) {
+    if (syev_on_chip(ctx, j.n)) jobs.push_back(j);
+    else DACP_TRY(gpu_syev(ctx, j.n, j.A, j.lda, j.w, j.Z));
+  }
+  // the whole list, or, where the device has not that much scratch (4 n^2 doubles a matrix, 5 without
+  // Z) left, half as many at a time until it has
+  int per = static_cast<int>(jobs.size());
+  for (int at = 0, np = per; at < np;) {
+    const int take = std::min(per, np - at);
+    const dacp_status st = solve_round(ctx, jobs.data() + at, take);
+    if (st == DACP_E_NOMEM && take > 1) {
+      (void)hipGetLastError();
+      ctx->err.clear();
+      per = (take + 1) / 2;
+    } else if (st != DACP_OK) {
+      return st;
+    } else {
+      at += take;
+    }
   }
   return DACP_OK;
 }
