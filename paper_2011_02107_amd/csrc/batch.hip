@@ -90,10 +90,51 @@ __device__ __forceinline__ T lane_flip(T v) {
   else return dpp<0x128>(v);                             // row_ror 8
 }
 
+// c, negated for an odd count.
+__device__ __forceinline__ double sign_flip(double c, int count) {
+  return __hiloint2double(__double2hiint(c) ^ (count << 31), __double2loint(c));
+}
+__device__ __forceinline__ float sign_flip(float c, int count) {
+  return __int_as_float(__float_as_int(c) ^ (count << 31));
+}
+
+// The flip table's terms of the thread's elements ib .. ib + C - 1.  The source of element tid + 512 i under
+// mask x is (tid ^ x's low 9 bits) + ((512 i) ^ the others): one lane offset a flip and a uniform part an
+// element, and the sign's parity splits the same way.  The next flip's entry is loaded under this one's
+// reads (the table ends with a spare one): a flip's time is the instructions it issues and the latency
+// of one read, not the reads' bandwidth (0.43 us at 2^14 rows in FP64).  With the entry waited for and an
+// index per element it took 0.75 us; now 0.50 (FP32 0.46).
+template <typename T, int C>
+__device__ __forceinline__ void table_flips(T (&s)[C], const T *lds, const OffDiag &od, int ib) {
+  constexpr uint32_t kLane = kBT - 1, kSh = sizeof(T) == 8 ? 3 : 2;
+  const char *ldsb = reinterpret_cast<const char *>(lds);
+  ConstFlipTable next = od.flips;
+  uint32_t xm = next->xmask, zm = next->zmask;
+  double cf = next->coef;
+  auto flip = [&](auto sign) {
+    const uint32_t hi = (xm & ~kLane) << kSh, lo = (tid_off(1u) ^ (xm & kLane)) << kSh, zt = zm << kSh;
+    const T c = sign(static_cast<T>(cf), lo & zt);
+    T g[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+      g[i] = *reinterpret_cast<const T *>(ldsb + (lo + (static_cast<uint32_t>((ib + i) * kBT) << kSh ^ hi)));
+    ++next;
+    xm = next->xmask;
+    zm = next->zmask;
+    cf = next->coef;
+#pragma unroll
+    for (int i = 0; i < C; ++i) s[i] += sign(c, (static_cast<uint32_t>((ib + i) * kBT) << kSh ^ hi) & zt) * g[i];
+  };
+#pragma nounroll
+  for (int t = 0; t < od.nplain; ++t) flip([](T c, uint32_t) { return c; });
+#pragma nounroll
+  for (int t = od.nplain; t < od.nflip; ++t) flip([](T c, uint32_t m) { return sign_flip(c, __popc(m)); });
+}
+
 // s[i] = (H v) of the thread's elements ib .. ib + C - 1; lds holds v (elements past 2^L zero).
 // Elements go in chunks of at most 8, which bounds the loads in flight; a chunk's diagonal entries
 // are loaded first and applied last, so their latency runs under the flips.
-template <typename T, int E, int C>
+template <typename T, int E, int C, bool kSingle>
 __device__ __forceinline__ void chunk_apply(T (&s)[C], const T (&v)[E], const T *lds, const T *diag, const OffDiag &od,
                                             uint32_t D, int ib) {
   T dg[C];
@@ -104,54 +145,39 @@ __device__ __forceinline__ void chunk_apply(T (&s)[C], const T (&v)[E], const T 
   }
 #pragma unroll
   for (int i = 0; i < C; ++i) s[i] = T(0);
+  if constexpr (kSingle) {
 #pragma unroll
-  for (int b = 4; b < 9; ++b) {
-    const T c = static_cast<T>(od.xc[b]);
-    const T *src = lds + (tid_off(1u) ^ (1u << b)) + ib * kBT;
+    for (int b = 4; b < 9; ++b) {
+      const T c = static_cast<T>(od.xc[b]);
+      const T *src = lds + (tid_off(1u) ^ (1u << b)) + ib * kBT;
 #pragma unroll
-    for (int i = 0; i < C; ++i) s[i] += c * src[i * kBT];
-  }
-  const T c0 = static_cast<T>(od.xc[0]), c1 = static_cast<T>(od.xc[1]), c2 = static_cast<T>(od.xc[2]),
-          c3 = static_cast<T>(od.xc[3]);
+      for (int i = 0; i < C; ++i) s[i] += c * src[i * kBT];
+    }
+    const T c0 = static_cast<T>(od.xc[0]), c1 = static_cast<T>(od.xc[1]), c2 = static_cast<T>(od.xc[2]),
+            c3 = static_cast<T>(od.xc[3]);
 #pragma unroll
-  for (int i = 0; i < C; ++i) s[i] += c0 * lane_flip<0>(v[ib + i]);
+    for (int i = 0; i < C; ++i) s[i] += c0 * lane_flip<0>(v[ib + i]);
 #pragma unroll
-  for (int i = 0; i < C; ++i) s[i] += c1 * lane_flip<1>(v[ib + i]);
+    for (int i = 0; i < C; ++i) s[i] += c1 * lane_flip<1>(v[ib + i]);
 #pragma unroll
-  for (int i = 0; i < C; ++i) s[i] += c2 * lane_flip<2>(v[ib + i]);
+    for (int i = 0; i < C; ++i) s[i] += c2 * lane_flip<2>(v[ib + i]);
 #pragma unroll
-  for (int i = 0; i < C; ++i) s[i] += c3 * lane_flip<3>(v[ib + i]);
+    for (int i = 0; i < C; ++i) s[i] += c3 * lane_flip<3>(v[ib + i]);
 #pragma unroll
-  for (int b = 9; (1 << (b - 9)) < E; ++b) {
-    const T c = static_cast<T>(od.xc[b]);
+    for (int b = 9; (1 << (b - 9)) < E; ++b) {
+      const T c = static_cast<T>(od.xc[b]);
 #pragma unroll
-    for (int i = 0; i < C; ++i) s[i] += c * v[(ib + i) ^ (1 << (b - 9))];
-  }
-#pragma nounroll
-  for (int t = 0; t < od.nplain; ++t) {
-    const uint32_t xm = od.flips[t].xmask;
-    const T c = static_cast<T>(od.flips[t].coef);
-#pragma unroll
-    for (int i = 0; i < C; ++i) s[i] += c * lds[(tid_off(1u) + (ib + i) * kBT) ^ xm];
-  }
-#pragma nounroll
-  for (int t = od.nplain; t < od.nflip; ++t) {
-    const uint32_t xm = od.flips[t].xmask;
-    const uint32_t zm = od.flips[t].zmask;
-    const T c = static_cast<T>(od.flips[t].coef);
-#pragma unroll
-    for (int i = 0; i < C; ++i) {
-      const uint32_t src = (tid_off(1u) + (ib + i) * kBT) ^ xm;
-      s[i] += ((__popc(src & zm) & 1) ? -c : c) * lds[src];
+      for (int i = 0; i < C; ++i) s[i] += c * v[(ib + i) ^ (1 << (b - 9))];
     }
   }
+  if (od.nflip > 0) table_flips<T, C>(s, lds, od, ib);
 #pragma unroll
   for (int i = 0; i < C; ++i) s[i] += dg[i] * v[ib + i];
 }
 
 // out(i, (H v)_i) for every element of this thread: v goes to LDS (between barriers: the previous
 // apply's readers are done, then the writers), then chunk by chunk.
-template <typename T, int E, typename Out>
+template <bool kSingle, typename T, int E, typename Out>
 __device__ __forceinline__ void apply(const T (&v)[E], T *lds, const T *diag, const OffDiag &od, uint32_t D, Out out) {
   __syncthreads();
 #pragma unroll
@@ -166,7 +192,7 @@ __device__ __forceinline__ void apply(const T (&v)[E], T *lds, const T *diag, co
   for (int ib = 0; ib < E; ib += C) {
     T s[C];
     asm volatile("" ::: "memory");  // the next chunk's loads stay behind
-    chunk_apply<T, E, C>(s, v, lds, diag, od, D, ib);
+    chunk_apply<T, E, C, kSingle>(s, v, lds, diag, od, D, ib);
 #pragma unroll
     for (int i = 0; i < C; ++i) out(ib + i, s[i]);
   }
@@ -237,34 +263,34 @@ __device__ __forceinline__ void anchor_at(const BatchCol &c, ConstInts ka, int &
 
 // The filter's recurrence from psi in v: on exit v = T^_K and A = T^_(K-1), T^_0 = psi.  Orders run in
 // pairs with the two terms' roles swapped, so that no copies are made.
-template <typename T, int E>
+template <bool kSingle, typename T, int E>
 __device__ __forceinline__ void filter_first(T (&A)[E], T (&B)[E], T *lds, const T *diag, const OffDiag &od, uint32_t D,
                                              T fa, T fb) {
   T w[E];
-  apply<T, E>(A, lds, diag, od, D, [&](int i, T x) { set_now(w[i], x); });
-  apply<T, E>(w, lds, diag, od, D, [&](int i, T x) { set_now(B[i], fa * x + fb * A[i]); });
+  apply<kSingle, T, E>(A, lds, diag, od, D, [&](int i, T x) { set_now(w[i], x); });
+  apply<kSingle, T, E>(w, lds, diag, od, D, [&](int i, T x) { set_now(B[i], fa * x + fb * A[i]); });
 }
 // A <- alpha H (H B) + beta B + gamma A
-template <typename T, int E>
+template <bool kSingle, typename T, int E>
 __device__ __forceinline__ void filter_order(T (&A)[E], const T (&B)[E], T *lds, const T *diag, const OffDiag &od,
                                              uint32_t D, T alpha, T beta, T gamma) {
   T w[E];
-  apply<T, E>(B, lds, diag, od, D, [&](int i, T x) { set_now(w[i], x); });
-  apply<T, E>(w, lds, diag, od, D, [&](int i, T x) { set_now(A[i], alpha * x + beta * B[i] + gamma * A[i]); });
+  apply<kSingle, T, E>(B, lds, diag, od, D, [&](int i, T x) { set_now(w[i], x); });
+  apply<kSingle, T, E>(w, lds, diag, od, D, [&](int i, T x) { set_now(A[i], alpha * x + beta * B[i] + gamma * A[i]); });
 }
 // `count` orders from (A, B) = (T^_(k-1), T^_k); the newest ends in B when count is even, in A when odd.
-template <typename T, int E>
+template <bool kSingle, typename T, int E>
 __device__ __forceinline__ void filter_orders(T (&A)[E], T (&B)[E], T *lds, const T *diag, const OffDiag &od, uint32_t D,
                                               T alpha, T beta, T gamma, int count) {
   int k = 0;
   for (; k + 2 <= count; k += 2) {
-    filter_order<T, E>(A, B, lds, diag, od, D, alpha, beta, gamma);
-    filter_order<T, E>(B, A, lds, diag, od, D, alpha, beta, gamma);
+    filter_order<kSingle, T, E>(A, B, lds, diag, od, D, alpha, beta, gamma);
+    filter_order<kSingle, T, E>(B, A, lds, diag, od, D, alpha, beta, gamma);
   }
-  if (k < count) filter_order<T, E>(A, B, lds, diag, od, D, alpha, beta, gamma);
+  if (k < count) filter_order<kSingle, T, E>(A, B, lds, diag, od, D, alpha, beta, gamma);
 }
 
-template <int E>
+template <int E, bool kSingle>
 __device__ __forceinline__ void run_column(const BatchCol &c, const OffDiag &od, ConstInts ks, ConstInts ka,
                                            unsigned char *smem, double *red) {
   const uint32_t D = 1u << c.L;
@@ -286,9 +312,9 @@ __device__ __forceinline__ void run_column(const BatchCol &c, const OffDiag &od,
       float Af[E], Bf[E];
 #pragma unroll
       for (int i = 0; i < E; ++i) Af[i] = static_cast<float>(v[i]);
-      filter_first<float, E>(Af, Bf, lds32, c.d32, od, D, static_cast<float>(c.f_first_a),
+      filter_first<kSingle, float, E>(Af, Bf, lds32, c.d32, od, D, static_cast<float>(c.f_first_a),
                              static_cast<float>(c.f_first_b));
-      filter_orders<float, E>(Af, Bf, lds32, c.d32, od, D, static_cast<float>(c.f_alpha),
+      filter_orders<kSingle, float, E>(Af, Bf, lds32, c.d32, od, D, static_cast<float>(c.f_alpha),
                               static_cast<float>(c.f_beta), static_cast<float>(c.f_gamma), c.n32 - 1);
       const bool odd = (c.n32 - 1) & 1;
 #pragma unroll
@@ -298,10 +324,10 @@ __device__ __forceinline__ void run_column(const BatchCol &c, const OffDiag &od,
       }
       tail = c.K - c.n32;
     } else if (c.K > 0) {
-      filter_first<double, E>(A, v, lds64, c.d64, od, D, c.f_first_a, c.f_first_b);
+      filter_first<kSingle, double, E>(A, v, lds64, c.d64, od, D, c.f_first_a, c.f_first_b);
       tail = c.K - 1;
     }
-    filter_orders<double, E>(A, v, lds64, c.d64, od, D, c.f_alpha, c.f_beta, c.f_gamma, tail);
+    filter_orders<kSingle, double, E>(A, v, lds64, c.d64, od, D, c.f_alpha, c.f_beta, c.f_gamma, tail);
     if (tail & 1) swap_arrays<E>(A, v);
     if (c.mode == kBatchFilter) {  // not normalised: the caller checks the norms
       store_panel<E>(c.V, c.ldv, 0, v, D);
@@ -320,27 +346,41 @@ __device__ __forceinline__ void run_column(const BatchCol &c, const OffDiag &od,
   anchor_at<E>(c, ka, next_a, 0, v, D);
 #pragma unroll
   for (int i = 0; i < E; ++i) A[i] = v[i];
-  apply<double, E>(A, lds64, c.d64, od, D, [&](int i, double x) { set_now(v[i], c.inv_e * x); });
+  apply<kSingle, double, E>(A, lds64, c.d64, od, D, [&](int i, double x) { set_now(v[i], c.inv_e * x); });
   sample_at<E>(c, ks, next, 1, v, D, norm2, red);
   anchor_at<E>(c, ka, next_a, 1, v, D);
   int64_t kmax = c.n_samples > 0 ? ks[c.n_samples - 1] : 1;
   if (c.n_anchor > 0 && ka[c.n_anchor - 1] > kmax) kmax = ka[c.n_anchor - 1];
   const double two_inv_e = 2.0 * c.inv_e;
   for (int64_t k = 1; k < kmax; k += 2) {
-    apply<double, E>(v, lds64, c.d64, od, D, [&](int i, double x) { set_now(A[i], two_inv_e * x - A[i]); });
+    apply<kSingle, double, E>(v, lds64, c.d64, od, D, [&](int i, double x) { set_now(A[i], two_inv_e * x - A[i]); });
     sample_at<E>(c, ks, next, k + 1, A, D, norm2, red);
     anchor_at<E>(c, ka, next_a, k + 1, A, D);
     if (k + 1 >= kmax) break;
-    apply<double, E>(A, lds64, c.d64, od, D, [&](int i, double x) { set_now(v[i], two_inv_e * x - v[i]); });
+    apply<kSingle, double, E>(A, lds64, c.d64, od, D, [&](int i, double x) { set_now(v[i], two_inv_e * x - v[i]); });
     sample_at<E>(c, ks, next, k + 2, v, D, norm2, red);
     anchor_at<E>(c, ka, next_a, k + 2, v, D);
   }
 }
 
+// Elements per thread: 2^L / 512, at least 1.  Without single-spin terms (kSingle false) their sweeps are
+// not there at all; a branch around them inside the apply costs the others 1 (FP64) to 4 % (FP32).
+template <bool kSingle>
+__device__ __forceinline__ void column_of(const BatchCol &c, const OffDiag &od, ConstInts ks, ConstInts ka,
+                                          unsigned char *smem, double *red) {
+  switch (c.L) {
+    case 14: run_column<32, kSingle>(c, od, ks, ka, smem, red); break;
+    case 13: run_column<16, kSingle>(c, od, ks, ka, smem, red); break;
+    case 12: run_column<8, kSingle>(c, od, ks, ka, smem, red); break;
+    case 11: run_column<4, kSingle>(c, od, ks, ka, smem, red); break;
+    case 10: run_column<2, kSingle>(c, od, ks, ka, smem, red); break;
+    default: run_column<1, kSingle>(c, od, ks, ka, smem, red); break;
+  }
+}
+
 // (two waves per SIMD: 256 registers a lane)
 __global__ __launch_bounds__(kBT, 2) void k_batch_chebyshev(const BatchCol *cols_g) {
-  extern __shared__ unsigned char smem_raw[];
-  __shared__ double red[kBW];
+  extern __shared__ unsigned char smem_raw[];  // the column, then the reductions' scratch
   // field by field through the constant address space (uniform scalar loads)
   const ConstBatchCols cc = (ConstBatchCols)cols_g + blockIdx.x;
   BatchCol c;
@@ -369,16 +409,11 @@ __global__ __launch_bounds__(kBT, 2) void k_batch_chebyshev(const BatchCol *cols
   c.b = cc->b;
   c.n_anchor = cc->n_anchor;
   const OffDiag od{(ConstDoubles)cc->xc, (ConstFlipTable)cc->flips, cc->nplain, cc->nflip};
+  double *red = reinterpret_cast<double *>(smem_raw) + max(1 << c.L, kBT);
   const ConstInts ks = (ConstInts)c.ks;
   const ConstInts ka = (ConstInts)c.ka;
-  switch (c.L) {  // elements per thread: 2^L / 512, at least 1
-    case 14: run_column<32>(c, od, ks, ka, smem_raw, red); break;
-    case 13: run_column<16>(c, od, ks, ka, smem_raw, red); break;
-    case 12: run_column<8>(c, od, ks, ka, smem_raw, red); break;
-    case 11: run_column<4>(c, od, ks, ka, smem_raw, red); break;
-    case 10: run_column<2>(c, od, ks, ka, smem_raw, red); break;
-    default: run_column<1>(c, od, ks, ka, smem_raw, red); break;
-  }
+  if (cc->single) column_of<true>(c, od, ks, ka, smem_raw, red);
+  else column_of<false>(c, od, ks, ka, smem_raw, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -391,7 +426,7 @@ __global__ __launch_bounds__(kBT, 2) void k_batch_chebyshev(const BatchCol *cols
 //   kind 1: out[0] = <r, r>, out[1] = <r, T_1 r>, out[2k] = <T_k r, T_k r>,
 //           out[2k + 1] = <T_(k+1) r, T_k r>  (k >= 1, indices below `steps` = M).
 // ---------------------------------------------------------------------------
-template <int E>
+template <int E, bool kSingle>
 __device__ __forceinline__ void run_spectral(const BatchSpec &c, const OffDiag &od, unsigned char *smem, double *red) {
   const uint32_t D = 1u << c.L;
   double *lds = reinterpret_cast<double *>(smem);
@@ -415,7 +450,7 @@ __device__ __forceinline__ void run_spectral(const BatchSpec &c, const OffDiag &
     int taken = 0;
     // one step: y = v_j on entry; x = v_(j-1) becomes v_(j+1); false at the last
     auto step = [&](int j, double(&x)[E], const double(&y)[E]) -> bool {
-      apply<double, E>(y, lds, c.d64, od, D, [&](int i, double h) { set_now(x[i], h - bprev * x[i]); });
+      apply<kSingle, double, E>(y, lds, c.d64, od, D, [&](int i, double h) { set_now(x[i], h - bprev * x[i]); });
       const double alpha = dot<E>(x, y, red);
 #pragma unroll
       for (int i = 0; i < E; ++i) x[i] -= alpha * y[i];
@@ -447,7 +482,7 @@ __device__ __forceinline__ void run_spectral(const BatchSpec &c, const OffDiag &
   if (c.steps <= 1) return;
 #pragma unroll
   for (int i = 0; i < E; ++i) A[i] = v[i];
-  apply<double, E>(A, lds, c.d64, od, D, [&](int i, double x) { set_now(v[i], c.inv_e * x); });
+  apply<kSingle, double, E>(A, lds, c.d64, od, D, [&](int i, double x) { set_now(v[i], c.inv_e * x); });
   {
     const double m1 = dot<E>(v, A, red);
     if (threadIdx.x == 0) c.out[1] = m1;
@@ -459,7 +494,7 @@ __device__ __forceinline__ void run_spectral(const BatchSpec &c, const OffDiag &
     const double tkk = dot<E>(y, y, red);
     if (threadIdx.x == 0) c.out[2 * k] = tkk;
     if (2 * k + 1 >= c.steps) return false;
-    apply<double, E>(y, lds, c.d64, od, D, [&](int i, double h) { set_now(x[i], two_inv_e * h - x[i]); });
+    apply<kSingle, double, E>(y, lds, c.d64, od, D, [&](int i, double h) { set_now(x[i], two_inv_e * h - x[i]); });
     const double tk1k = dot<E>(x, y, red);
     if (threadIdx.x == 0) c.out[2 * k + 1] = tk1k;
     return true;
@@ -470,11 +505,22 @@ __device__ __forceinline__ void run_spectral(const BatchSpec &c, const OffDiag &
   }
 }
 
+template <bool kSingle>
+__device__ __forceinline__ void spectral_of(const BatchSpec &c, const OffDiag &od, unsigned char *smem, double *red) {
+  switch (c.L) {
+    case 14: run_spectral<32, kSingle>(c, od, smem, red); break;
+    case 13: run_spectral<16, kSingle>(c, od, smem, red); break;
+    case 12: run_spectral<8, kSingle>(c, od, smem, red); break;
+    case 11: run_spectral<4, kSingle>(c, od, smem, red); break;
+    case 10: run_spectral<2, kSingle>(c, od, smem, red); break;
+    default: run_spectral<1, kSingle>(c, od, smem, red); break;
+  }
+}
+
 typedef const __attribute__((address_space(4))) BatchSpec *ConstBatchSpecs;
 
 __global__ __launch_bounds__(kBT, 2) void k_batch_spectral(const BatchSpec *specs_g) {
-  extern __shared__ unsigned char smem_raw[];
-  __shared__ double red[kBW];
+  extern __shared__ unsigned char smem_raw[];  // the column, then the reductions' scratch
   const ConstBatchSpecs cs = (ConstBatchSpecs)specs_g + blockIdx.x;
   BatchSpec c;
   c.d64 = cs->d64;
@@ -485,15 +531,10 @@ __global__ __launch_bounds__(kBT, 2) void k_batch_spectral(const BatchSpec *spec
   c.L = cs->L;
   c.kind = cs->kind;
   c.steps = cs->steps;
+  double *red = reinterpret_cast<double *>(smem_raw) + max(1 << c.L, kBT);
   const OffDiag od{(ConstDoubles)cs->xc, (ConstFlipTable)cs->flips, cs->nplain, cs->nflip};
-  switch (c.L) {
-    case 14: run_spectral<32>(c, od, smem_raw, red); break;
-    case 13: run_spectral<16>(c, od, smem_raw, red); break;
-    case 12: run_spectral<8>(c, od, smem_raw, red); break;
-    case 11: run_spectral<4>(c, od, smem_raw, red); break;
-    case 10: run_spectral<2>(c, od, smem_raw, red); break;
-    default: run_spectral<1>(c, od, smem_raw, red); break;
-  }
+  if (cs->single) spectral_of<true>(c, od, smem_raw, red);
+  else spectral_of<false>(c, od, smem_raw, red);
 }
 
 }  // namespace
@@ -501,7 +542,7 @@ __global__ __launch_bounds__(kBT, 2) void k_batch_spectral(const BatchSpec *spec
 hipError_t launch_batch_chebyshev(const BatchCol *cols, int ncols, int max_L, hipStream_t s) {
   if (ncols <= 0) return hipSuccess;
   if (max_L < 1 || max_L > 14) return hipErrorInvalidValue;
-  const size_t lds = std::max<size_t>(size_t(1) << max_L, kBT) * sizeof(double);
+  const size_t lds = (std::max<size_t>(size_t(1) << max_L, kBT) + kBW) * sizeof(double);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_batch_chebyshev),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
@@ -512,7 +553,7 @@ hipError_t launch_batch_chebyshev(const BatchCol *cols, int ncols, int max_L, hi
 hipError_t launch_batch_spectral(const BatchSpec *specs, int n, int max_L, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (max_L < 1 || max_L > 14) return hipErrorInvalidValue;
-  const size_t lds = std::max<size_t>(size_t(1) << max_L, kBT) * sizeof(double);
+  const size_t lds = (std::max<size_t>(size_t(1) << max_L, kBT) + kBW) * sizeof(double);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_batch_spectral),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;

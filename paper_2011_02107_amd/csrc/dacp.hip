@@ -282,21 +282,24 @@ dacp_status onchip_order(dacp_ctx ctx, dacp_ham h) {
   }
   const auto mid =
       std::stable_partition(rest.begin(), rest.end(), [](const FlipEntry &f) { return f.zmask == 0; });
+  const int nplain = static_cast<int>(mid - rest.begin()), nflip = static_cast<int>(rest.size());
+  rest.push_back(FlipEntry{0, 0, 0.0});  // the kernels load an entry ahead
   // both tables in one allocation
   const size_t bytes = 14 * sizeof(double) + rest.size() * sizeof(FlipEntry);
   double *p = nullptr;
   DACP_HIP(ctx, hipMalloc(&p, bytes));
   FlipEntry *flips = reinterpret_cast<FlipEntry *>(p + 14);
   hipError_t e = hipMemcpy(p, xc.data(), 14 * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !rest.empty())
+  if (e == hipSuccess)
     e = hipMemcpy(flips, rest.data(), rest.size() * sizeof(FlipEntry), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(p);
     return hip_err(ctx, e, "flip tables");
   }
   oc.flips = flips;
-  oc.nplain = static_cast<int>(mid - rest.begin());
-  oc.nflip = static_cast<int>(rest.size());
+  oc.nplain = nplain;
+  oc.nflip = nflip;
+  oc.single = static_cast<int>(h->flips_host.size()) > nflip;
   oc.xc = p;
   return DACP_OK;
 }
@@ -531,6 +534,7 @@ BatchCol onchip_col(dacp_ham h, int mode, double e_b, double a) {
   c.flips = h->onchip.flips;
   c.nflip = h->onchip.nflip;
   c.nplain = h->onchip.nplain;
+  c.single = h->onchip.single;
   c.d64 = h->d64;
   c.d32 = h->d32;
   c.L = h->L;
@@ -1835,6 +1839,7 @@ BatchSpec spectral_spec(dacp_ham h, int kind, int steps, const double *start, in
   c.flips = h->onchip.flips;
   c.nflip = h->onchip.nflip;
   c.nplain = h->onchip.nplain;
+  c.single = h->onchip.single;
   c.d64 = h->d64;
   c.L = h->L;
   c.kind = kind;

@@ -138,6 +138,7 @@ struct BatchCol {
   double f_first_a, f_first_b;      // first order: T^_1 = a H (H psi) + b psi
   double inv_e;                     // 1 / E_b
   int L, nflip, nplain, K, n32, n_samples, b, n_anchor;  // flips[0, nplain) have z-mask 0
+  int single;  // some xc is not 0
   int mode;  // kBatchFilter: the filter alone, T^_K to panel 0 not normalised; kBatchEvolve: the evolution alone
 };
 hipError_t launch_batch_chebyshev(const BatchCol *cols, int ncols, int max_L, hipStream_t s);
@@ -152,7 +153,7 @@ struct BatchSpec {
   double *out;             // kind 0: 2 steps + 2 doubles; kind 1: steps doubles
   int64_t ld;
   double inv_e;            // kind 1: 1 / E_b
-  int L, nflip, nplain, kind, steps;
+  int L, nflip, nplain, single, kind, steps;
 };
 hipError_t launch_batch_spectral(const BatchSpec *specs, int n, int max_L, hipStream_t s);
 
@@ -427,7 +428,7 @@ struct dacp_ham_s {
   struct OnChipOrder {
     double *xc = nullptr;           // 14 coefficients of the single-spin sign-free flips, by spin
     dacp::FlipEntry *flips = nullptr;  // the others, sign-free ones first
-    int nplain = 0, nflip = 0;
+    int nplain = 0, nflip = 0, single = 0;  // single: some xc is not 0
   } onchip;                          // tables of the on-chip column kernels (L <= 14)
 };
 namespace dacp {
