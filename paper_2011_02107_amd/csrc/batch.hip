@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 #include "wave.h"
@@ -90,20 +91,22 @@ __device__ __forceinline__ T lane_flip(T v) {
   else return dpp<0x128>(v);                             // row_ror 8
 }
 
-// c, negated for an odd count.
-__device__ __forceinline__ double sign_flip(double c, int count) {
-  return __hiloint2double(__double2hiint(c) ^ (count << 31), __double2loint(c));
+// v with the sign bit of `bit31` applied.
+__device__ __forceinline__ double sign_xor(double v, uint32_t bit31) {
+  return __hiloint2double(__double2hiint(v) ^ static_cast<int>(bit31), __double2loint(v));
 }
-__device__ __forceinline__ float sign_flip(float c, int count) {
-  return __int_as_float(__float_as_int(c) ^ (count << 31));
+__device__ __forceinline__ float sign_xor(float v, uint32_t bit31) {
+  return __int_as_float(__float_as_int(v) ^ static_cast<int>(bit31));
 }
 
 // The flip table's terms of the thread's elements ib .. ib + C - 1.  The source of element tid + 512 i under
 // mask x is (tid ^ x's low 9 bits) + ((512 i) ^ the others): one lane offset a flip and a uniform part an
-// element, and the sign's parity splits the same way.  The next flip's entry is loaded under this one's
-// reads (the table ends with a spare one): a flip's time is the instructions it issues and the latency
-// of one read, not the reads' bandwidth (0.43 us at 2^14 rows in FP64).  With the entry waited for and an
-// index per element it took 0.75 us; now 0.50 (FP32 0.46).
+// element.  A sign is the parity of the source under the z-mask, which is linear: the lane's part and the
+// mask's go to the coefficient, and what is left for an element is the parity of i's low three bits under
+// bits 9 to 11 of the z-mask.  The next flip's entry is loaded under this one's reads (the table ends
+// with a spare one): a flip's time is the instructions it issues and the latency of one read, not the
+// reads' bandwidth (0.43 us at 2^14 rows in FP64).  With the entry waited for and an index and a sign
+// formed per element it took 0.75 us, 1.3 with a sign; now 0.50 and 0.85.
 template <typename T, int C>
 __device__ __forceinline__ void table_flips(T (&s)[C], const T *lds, const OffDiag &od, int ib) {
   constexpr uint32_t kLane = kBT - 1, kSh = sizeof(T) == 8 ? 3 : 2;
@@ -111,24 +114,33 @@ __device__ __forceinline__ void table_flips(T (&s)[C], const T *lds, const OffDi
   ConstFlipTable next = od.flips;
   uint32_t xm = next->xmask, zm = next->zmask;
   double cf = next->coef;
-  auto flip = [&](auto sign) {
-    const uint32_t hi = (xm & ~kLane) << kSh, lo = (tid_off(1u) ^ (xm & kLane)) << kSh, zt = zm << kSh;
-    const T c = sign(static_cast<T>(cf), lo & zt);
+  auto flip = [&](auto sgn) {
+    constexpr bool kSigned = decltype(sgn)::value;
+    const uint32_t xh = xm & ~kLane, xl = tid_off(1u) ^ (xm & kLane), zt = zm;
+    T c = static_cast<T>(cf);
+    if constexpr (kSigned)
+      c = sign_xor(c, static_cast<uint32_t>(__popc(xl & zt & kLane) + __popc((xh ^ static_cast<uint32_t>(ib * kBT)) & zt & ~kLane))
+                          << 31);
     T g[C];
 #pragma unroll
     for (int i = 0; i < C; ++i)
-      g[i] = *reinterpret_cast<const T *>(ldsb + (lo + (static_cast<uint32_t>((ib + i) * kBT) << kSh ^ hi)));
+      g[i] = *reinterpret_cast<const T *>(ldsb + ((xl << kSh) + (static_cast<uint32_t>((ib + i) * kBT) << kSh ^ xh << kSh)));
     ++next;
     xm = next->xmask;
     zm = next->zmask;
     cf = next->coef;
 #pragma unroll
-    for (int i = 0; i < C; ++i) s[i] += sign(c, (static_cast<uint32_t>((ib + i) * kBT) << kSh ^ hi) & zt) * g[i];
+    for (int i = 0; i < C; ++i) {
+      if constexpr (kSigned)
+        g[i] = sign_xor(g[i], (i & 1 ? zt << 22 & 1u << 31 : 0u) ^ (i & 2 ? zt << 21 & 1u << 31 : 0u) ^
+                                  (i & 4 ? zt << 20 & 1u << 31 : 0u));
+      s[i] += c * g[i];
+    }
   };
 #pragma nounroll
-  for (int t = 0; t < od.nplain; ++t) flip([](T c, uint32_t) { return c; });
+  for (int t = 0; t < od.nplain; ++t) flip(std::false_type());
 #pragma nounroll
-  for (int t = od.nplain; t < od.nflip; ++t) flip([](T c, uint32_t m) { return sign_flip(c, __popc(m)); });
+  for (int t = od.nplain; t < od.nflip; ++t) flip(std::true_type());
 }
 
 // s[i] = (H v) of the thread's elements ib .. ib + C - 1; lds holds v (elements past 2^L zero).

@@ -268,6 +268,9 @@ dacp_status split_order(dacp_ctx ctx, dacp_ham h, int lo_bits) {
   return DACP_OK;
 }
 
+// A flip that the on-chip column kernels take by bit (the others through their flip table).
+bool onchip_single(const FlipEntry &f) { return f.zmask == 0 && (f.xmask & (f.xmask - 1)) == 0; }
+
 // Tables of the on-chip column kernels (L <= 14): one coefficient per spin for the single-spin
 // sign-free flips, the other flips with the sign-free ones first.
 dacp_status onchip_order(dacp_ctx ctx, dacp_ham h) {
@@ -277,7 +280,7 @@ dacp_status onchip_order(dacp_ctx ctx, dacp_ham h) {
   std::vector<double> xc(14, 0.0);
   std::vector<FlipEntry> rest;
   for (const FlipEntry &f : h->flips_host) {
-    if (f.zmask == 0 && (f.xmask & (f.xmask - 1)) == 0) xc[__builtin_ctz(f.xmask)] = f.coef;
+    if (onchip_single(f)) xc[__builtin_ctz(f.xmask)] = f.coef;
     else rest.push_back(f);
   }
   const auto mid =
@@ -517,12 +520,13 @@ struct Timer {
 // ------------------------------------------------------- on-chip columns
 // Up to kOnChipL spins a column fits one compute unit, and a recurrence runs there whole, a
 // workgroup per column (batch.hip): one launch, where a step through memory is one to four
-// launches of about 5 us each whatever the size (an on-chip apply takes 5 us at 2^14 rows, under 2
-// at 2^11).  Orders past kOnChipSteps (seconds in one launch) take the general kernels.
+// launches of about 5 us each whatever the size.  Taken where it is the faster route (rules::onchip_pays:
+// flips of two spins or with a sign cost a sweep of the column each) and the column's 32-bit byte
+// offsets reach, over `applies` applies to each of b columns of a block with row stride ld.
 constexpr int kOnChipL = 14;
-constexpr int64_t kOnChipSteps = int64_t(1) << 20;
-bool onchip_fits(dacp_ham h, int b, int64_t ld, int64_t steps) {
-  return h->L <= kOnChipL && steps <= kOnChipSteps && h->D * std::max<int64_t>(b, ld) * 8 < (int64_t(1) << 32);
+bool onchip_fits(dacp_ctx ctx, dacp_ham h, int b, int64_t ld, double applies, double extra_us = 0.0) {
+  if (h->L > kOnChipL || h->D * std::max<int64_t>(b, ld) * 8 >= (int64_t(1) << 32)) return false;
+  return dacp::rules::onchip_pays(h->L, h->flip_counts, b, ctx->num_cus, applies, extra_us);
 }
 
 // A column's table entry without its buffers: h's tables and the recurrences' coefficients (a > 0:
@@ -822,7 +826,7 @@ dacp_status run_filter(dacp_ctx ctx, dacp_ham h, const dacp_filter_params *p, co
     DACP_HIP(ctx, dacp::launch_philox_gauss(s0.as<double>(), D, b, p->seed, ctx->stream));
     psi = s0.as<double>();
   }
-  if (p->K > 0 && onchip_fits(h, b, b, p->K)) {
+  if (p->K > 0 && onchip_fits(ctx, h, b, b, 2.0 * p->K)) {
     DACP_TRY(onchip_order(ctx, h));
     const int tail = p->precision == DACP_F32 ? std::max(0, std::min(p->fp64_tail, p->K)) : p->K;
     std::vector<BatchCol> cols;
@@ -1070,7 +1074,7 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     panel_of[ks[i]] = 2 * i + 2;
   }
   const int64_t kmax = ks.back();
-  if (onchip_fits(h, b, ldv, kmax)) {
+  if (onchip_fits(ctx, h, b, ldv, static_cast<double>(kmax))) {
     Timer tm(ctx);
     tm.start();
     DACP_TRY(onchip_evolve(ctx, h, p->e_bound, b, psi_e, ks, V, ldv, nullptr, nullptr, 0, "basis"));
@@ -1553,7 +1557,7 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
   const int na = static_cast<int>(anchors.size());
   const int ma = na * b;  // anchor block width
   const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
-  if (onchip_fits(h, b, std::max<int64_t>(ldv, 2 * ma), kn + 1)) {
+  if (onchip_fits(ctx, h, b, std::max<int64_t>(ldv, 2 * ma), static_cast<double>(kn + 1))) {
     std::vector<int64_t> ks;
     for (int j = 1; j <= n; ++j) ks.push_back(mp.orders[2 * j]);
     DevBuf abuf;
@@ -1856,7 +1860,7 @@ dacp_status run_bound(dacp_ctx ctx, dacp_ham h, int steps, const double *v0, uin
   if (steps < 1) return set_err(ctx, DACP_E_INVALID, "bound: steps >= 1");
   steps = static_cast<int>(std::min<int64_t>(steps, D));
   hipStream_t s = ctx->stream;
-  const bool onchip = h->L <= kOnChipL;
+  const bool onchip = onchip_fits(ctx, h, 1, 1, steps, 8.0);  // two more launches a step
   DevBuf bv, bp, bw, bs, dspec;
   const double *start = v0;
   if (!v0 || !onchip) {
@@ -1924,7 +1928,7 @@ dacp_status moment_dots(dacp_ctx ctx, dacp_ham h, double e_bound, int M, int nve
   hipStream_t s = ctx->stream;
   const int kmax = M / 2;
   d.assign(2 * kmax + 2, 0.0);
-  if (onchip_fits(h, nvec, nvec, M)) {
+  if (onchip_fits(ctx, h, nvec, nvec, 0.5 * M, 4.0)) {  // a launch of dot products an order
     DACP_TRY(onchip_order(ctx, h));
     DevBuf dout, dspec;
     DACP_HIP(ctx, dout.alloc(static_cast<size_t>(M) * nvec * sizeof(double)));
@@ -2255,6 +2259,12 @@ dacp_status dacp_build_hamiltonian(dacp_ctx ctx, int L, int n_terms, const dacp_
   if (h->flips_host.size() > static_cast<size_t>(dacp::kMaxFlips)) {
     delete h;
     return set_err(ctx, DACP_E_INVALID, "too many distinct off-diagonal Pauli strings");
+  }
+  for (size_t i = 0; i < h->flips_host.size(); ++i) {
+    const FlipEntry &f = h->flips_host[i];
+    ++h->flip_counts.flips;
+    h->flip_counts.masks += i == 0 || f.xmask != h->flips_host[i - 1].xmask;
+    if (!onchip_single(f)) ++(f.zmask == 0 ? h->flip_counts.table_plain : h->flip_counts.table_signed);
   }
   auto fail = [&](hipError_t e, const char *what) {
     dacp_free_hamiltonian(h);

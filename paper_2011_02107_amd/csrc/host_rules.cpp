@@ -293,6 +293,23 @@ DcPlacement dc_place(std::vector<DcEntry> ents, int k) {
   return out;
 }
 
+double onchip_apply_us(int L, const FlipCounts &f) {
+  const double rows = std::max<double>(std::ldexp(1.0, L), 512.0);  // at least one element a thread
+  const bool single = f.flips > f.table_plain + f.table_signed;
+  return 0.45 + rows / 16384.0 * (1.9 + (single ? 3.3 : 0.0) + 0.49 * f.table_plain + 0.84 * f.table_signed);
+}
+
+double memory_apply_us(int L, const FlipCounts &f, int b) {
+  const double launch = std::max(5.8 + 0.22 * f.table_signed, 0.23 * f.flips);
+  const double stream = std::ldexp(8.0, L) * b * (f.masks + 12.0) / 16e6;
+  return std::pow(launch * std::sqrt(launch) + stream * std::sqrt(stream), 2.0 / 3.0);
+}
+
+bool onchip_pays(int L, const FlipCounts &f, int b, int cus, double applies, double extra_us) {
+  const double us = onchip_apply_us(L, f) * ((b + cus - 1) / std::max(1, cus));
+  return us <= memory_apply_us(L, f, b) + extra_us && us * applies <= kOnChipSeconds * 1e6;
+}
+
 }  // namespace rules
 }  // namespace dacp
 

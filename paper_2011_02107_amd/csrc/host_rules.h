@@ -121,5 +121,29 @@ struct MomentChain {
 };
 MomentChain moment_chain(const std::vector<int64_t> &orders, const std::vector<int64_t> &anchors);
 
+// Route of a recurrence up to 14 spins: a workgroup per column on chip (batch.hip), or the kernels that
+// step through memory, spread over the GPU.  Microseconds of one apply, fitted to what both took on
+// MI355X for 8 to 14 spins and 1 to 256 columns of a chain (single-spin flips), the paper's
+// nearest-neighbour model (L - 1 pair flips) and its spin glass (L (L - 1) / 2), and both with X_i X_j +
+// Y_i Y_j (twice as many flips, half of them with a sign):
+//   on chip  0.45 + rows / 2^14 (1.9 + 3.3 with single-spin flips + 0.49 a flip of the table, 0.84 with a
+//            sign), for every compute unit's worth of columns: a table flip is a sweep of the column through
+//            one unit's LDS (at 14 spins 5.7; 8.8 and 46.7; 20 and 124);
+//   memory   launches of 5.8 and 0.22 a flip with a sign, or 0.23 a flip where those are many, and the
+//            reads of each flip mask and 12 streams at 16 TB/s of the caches, half hidden under one
+//            another (the 2/3 power of their 3/2 powers' sum; for one column 6.0; 6.3 and 21; 8.9 and
+//            40; for 64 13; 13 and 51; 18.5 and 92).
+struct FlipCounts {
+  int flips = 0, masks = 0;              // all, and their distinct x-masks
+  int table_plain = 0, table_signed = 0;  // those that are not a single spin's without a sign
+};
+double onchip_apply_us(int L, const FlipCounts &f);
+double memory_apply_us(int L, const FlipCounts &f, int b);
+// Whether `applies` applies to each of b columns are faster on chip; extra_us: what the other route spends
+// besides an apply (scalars kept between launches).  Never past kOnChipSeconds in one launch, which
+// holds its compute units until it ends.
+constexpr double kOnChipSeconds = 2.0;
+bool onchip_pays(int L, const FlipCounts &f, int b, int cus, double applies, double extra_us);
+
 }  // namespace rules
 }  // namespace dacp

@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/dacp.h"
+#include "host_rules.h"
 
 namespace dacp {
 
@@ -407,6 +408,7 @@ struct dacp_ham_s {
   // coupling statistics of the merged Pauli strings (features of the learned window)
   double w_diag = 0.0, w_zz = 0.0, w_flip1 = 0.0, max_abs = 0.0;
   int n_strings = 0;
+  dacp::rules::FlipCounts flip_counts;
   bool flip_sym = false;  // H commutes with the global spin flip prod_i sigma^x_i
   double *d64 = nullptr;  // diagonal of H, FP64
   float *d32 = nullptr;   // same in FP32

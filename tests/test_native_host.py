@@ -16,10 +16,18 @@ pytestmark = pytest.mark.skipif(
     reason="no host C++ compiler or HIP headers")
 
 
-def test_worker_contexts_describe_the_callers_device(tmp_path):
-    exe = str(tmp_path / "worker_context")
-    cmd = [CXX, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-isystem", os.path.join(ROCM, "include"),
-           os.path.join(NATIVE, "worker_context_harness.cpp"), "-o", exe, "-lpthread"]
-    subprocess.run(cmd, check=True, capture_output=True, text=True)
+def run(tmp_path, name, *args):
+    exe = str(tmp_path / name)
+    subprocess.run([CXX, "-std=c++17", "-O1", "-I", CSRC, *args, "-o", exe, "-lpthread"], check=True,
+                   capture_output=True, text=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "0 failures" in r.stdout, r.stderr
+
+
+def test_worker_contexts_describe_the_callers_device(tmp_path):
+    run(tmp_path, "worker_context", "-D__HIP_PLATFORM_AMD__", "-isystem", os.path.join(ROCM, "include"),
+        os.path.join(NATIVE, "worker_context_harness.cpp"))
+
+
+def test_onchip_route_is_the_faster_one(tmp_path):
+    run(tmp_path, "onchip_route", os.path.join(NATIVE, "onchip_route_harness.cpp"), os.path.join(CSRC, "host_rules.cpp"))
