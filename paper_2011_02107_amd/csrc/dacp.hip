@@ -370,39 +370,32 @@ bool fused_plan(dacp_ctx ctx, dacp_ham h, int g, int &lo_bits, int &W, int esize
   return false;
 }
 
-// Column groups of a recurrence over b columns, `g` columns wanted per group and `blocks` live
-// [D][g] blocks of up to `esize` bytes an element: the fused kernels take power-of-two widths, so a
-// ragged width is rounded up and the columns past b are zero (they cost no launch, where the
-// general kernels take twice as long per step), and `per` groups advance in one launch.  One group
-// of 8 columns is 2 to 32 MB a block below 2^19 rows, whose launches are bound by their own start
-// and end (6-8 us each at 2^16 rows, the streams' rate would take 2.5); together they stream at the
-// rate of a large copy.  A launch's groups stay within the 256 MB Infinity Cache: past it every step
-// would go to HBM (two groups at once at 2^20 rows: 50-60 us a group, alone 43); half of it costs
-// the FP64 filter at 2^17 to 2^19 rows 5-8 %.
-// A shape without a fused plan keeps its width and runs one group at a time.
-constexpr int64_t kRecCacheBytes = int64_t(256) << 20;
-struct ColGroups {
-  int g, per;
-  bool fused;
-  // columns of the launch that starts at column c0 of b, its group width and group count
-  int cols(int c0, int b) const { return std::min(g * per, b - c0); }
-  int width(int nc) const { return fused ? g : nc; }
-  int groups(int nc) const { return fused ? (nc + g - 1) / g : 1; }
+// Column groups of a recurrence over b columns, `g` columns wanted per group (rules::column_plan): what the
+// launch that starts at column c0 advances.  A shape without a fused plan keeps its width and runs one
+// group at a time.
+struct ColGroups : dacp::rules::ColumnPlan {
+  int b;
+  int cols(int c0) const { return c0 < b - tail ? std::min(g * per, b - tail - c0) : tail; }
+  int width(int c0) const { return c0 >= b - tail ? tail_w : fused ? g : cols(c0); }
+  int groups(int c0) const { return c0 < b - tail && fused ? (cols(c0) + g - 1) / g : 1; }
   size_t elems(int64_t D) const { return static_cast<size_t>(D) * g * per; }
 };
-ColGroups column_groups(dacp_ctx ctx, dacp_ham h, int b, int g, int blocks, std::initializer_list<int> esizes) {
-  int w = 1;
-  while (w < g) w *= 2;
-  int emax = 0;
-  for (int e : esizes) {
-    int lo_bits = 0, hw = 1;
-    if (!fused_plan(ctx, h, w, lo_bits, hw, e)) return {g, 1, false};
-    emax = std::max(emax, e);
-  }
-  const int64_t all = (b + w - 1) / w;
-  const int64_t fit = std::max<int64_t>(1, kRecCacheBytes / (h->D * w * emax * blocks));
-  const int64_t launches = (all + fit - 1) / fit;  // of about equal size
-  return {w, static_cast<int>((all + launches - 1) / launches), true};
+// `blocks` live [D][g] blocks of up to the largest of `esizes` bytes an element; filter: its launches do
+// two applies.
+ColGroups column_groups(dacp_ctx ctx, dacp_ham h, int b, int g, int blocks, std::initializer_list<int> esizes,
+                        bool filter = false) {
+  auto fused = [&](int w) {
+    for (int e : esizes) {
+      int lo_bits = 0, hw = 1;
+      if (!fused_plan(ctx, h, w, lo_bits, hw, e)) return false;
+    }
+    return true;
+  };
+  ColGroups cg;
+  static_cast<dacp::rules::ColumnPlan &>(cg) = dacp::rules::column_plan(
+      h->D, b, g, static_cast<int64_t>(blocks) * *std::max_element(esizes.begin(), esizes.end()), esizes.size() > 1, filter, fused);
+  cg.b = b;
+  return cg;
 }
 
 // y = alpha H x + beta u + gamma z (+ FP64 copy into st), columns split in chunks of <= 2048.
@@ -852,13 +845,13 @@ dacp_status run_filter(dacp_ctx ctx, dacp_ham h, const dacp_filter_params *p, co
   const int gf = p->precision == DACP_F32 ? ctx->filter_group_f32 : ctx->filter_group_f64;
   // four live blocks: T_(k-1), T_k, w and the partial
   const int gt = (h->L >= 15 && b > gf) ? gf : b;
-  const ColGroups cg = p->precision == DACP_F32 ? column_groups(ctx, h, b, gt, 4, {4, 8})
-                                                : column_groups(ctx, h, b, gt, 4, {8});
+  const ColGroups cg = p->precision == DACP_F32 ? column_groups(ctx, h, b, gt, 4, {4, 8}, true)
+                                                : column_groups(ctx, h, b, gt, 4, {8}, true);
   DevBuf gin, gout;
   DACP_HIP(ctx, gin.alloc(cg.elems(D) * sizeof(double)));
   DACP_HIP(ctx, gout.alloc(cg.elems(D) * sizeof(double)));
-  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
-    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
+  for (int g0 = 0; g0 < b; g0 += cg.cols(g0)) {
+    const int nc = cg.cols(g0), gw = cg.width(g0), groups = cg.groups(g0);
     DACP_HIP(ctx, dacp::launch_split_cols(psi + g0, b, nc, gin.as<double>(), D, gw, groups, ctx->stream));
     dacp_status st = filter_group(ctx, h, gw, groups, fc, p->K, p->fp64_tail, p->precision, gin.as<double>(),
                                   gout.as<double>());
@@ -1093,8 +1086,8 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
-  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
-    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
+  for (int g0 = 0; g0 < b; g0 += cg.cols(g0)) {
+    const int nc = cg.cols(g0), gw = cg.width(g0), groups = cg.groups(g0);
     double *A = ba.as<double>(), *B = bb.as<double>();
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, V + g0, ldv, D, nc, ctx->stream));
@@ -1308,8 +1301,8 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
-  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
-    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
+  for (int g0 = 0; g0 < b; g0 += cg.cols(g0)) {
+    const int nc = cg.cols(g0), gw = cg.width(g0), groups = cg.groups(g0);
     double *A = ba.as<double>(), *B = bb.as<double>();
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return k <= kmax && slot_of[k] >= 0; };
@@ -1418,8 +1411,8 @@ dacp_status moment_ritz_vectors(dacp_ctx ctx, dacp_ham h, const dacp_basis_param
     cols.clear();  // the next copies into Z and dcols are queued behind this GEMM on the same stream
     return DACP_OK;
   };
-  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
-    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
+  for (int g0 = 0; g0 < b; g0 += cg.cols(g0)) {
+    const int nc = cg.cols(g0), gw = cg.width(g0), groups = cg.groups(g0);
     double *A = ba.as<double>(), *B = bb.as<double>();
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, ctx->stream));
     auto want = [&](int64_t k) { return panel_of.count(k) > 0; };
@@ -1583,8 +1576,8 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
   Timer tm(ctx);
   tm.start();
   int64_t launches = 0;
-  for (int g0 = 0; g0 < b; g0 += cg.g * cg.per) {
-    const int nc = cg.cols(g0, b), gw = cg.width(nc), groups = cg.groups(nc);
+  for (int g0 = 0; g0 < b; g0 += cg.cols(g0)) {
+    const int nc = cg.cols(g0), gw = cg.width(g0), groups = cg.groups(g0);
     double *A = ba.as<double>(), *B = bb.as<double>();
     DACP_HIP(ctx, dacp::launch_split_cols(psi_e + g0, b, nc, A, D, gw, groups, s));
     DACP_HIP(ctx, dacp::launch_copy_cols(psi_e + g0, b, V + g0, ldv, D, nc, s));
@@ -1955,8 +1948,8 @@ dacp_status moment_dots(dacp_ctx ctx, dacp_ham h, double e_bound, int M, int nve
   DACP_HIP(ctx, sums.alloc(2 * static_cast<size_t>(kmax + 1) * sizeof(double)));
   std::vector<double> got(2 * kmax + 2);
   int64_t launches = 0;
-  for (int g0 = 0; g0 < nvec; g0 += cg.g * cg.per) {
-    const int nc = cg.cols(g0, nvec), gw = cg.width(nc), groups = cg.groups(nc);
+  for (int g0 = 0; g0 < nvec; g0 += cg.cols(g0)) {
+    const int nc = cg.cols(g0), gw = cg.width(g0), groups = cg.groups(g0);
     const int64_t n = D * gw * groups;  // zero columns add nothing
     const int nb = dacp::scalar_blocks(n);
     DACP_HIP(ctx, dacp::launch_split_cols(r + g0, nvec, nc, ba.as<double>(), D, gw, groups, s));
@@ -3787,7 +3780,8 @@ dacp_status dacp_autotune(dacp_ctx ctx, dacp_ham h, int b, int steps, int *best_
   // unit start columns; E_b = sum |c| >= ||H||; a_r = pi / steps puts the first sample pair at k = steps
   DevBuf psi, V;
   const int gmax = std::min(b, 16);
-  const int bmax = static_cast<int>(std::max<int64_t>(gmax, std::min<int64_t>(b, kRecCacheBytes / (D * 24))));
+  const int bmax =
+      static_cast<int>(std::max<int64_t>(gmax, std::min<int64_t>(b, dacp::rules::kRecCacheBytes / (D * 24))));
   DACP_HIP(ctx, psi.alloc(static_cast<size_t>(D) * bmax * sizeof(double)));
   DACP_HIP(ctx, V.alloc(static_cast<size_t>(D) * 3 * bmax * sizeof(double)));
   double best = INFINITY;

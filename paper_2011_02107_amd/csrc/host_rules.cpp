@@ -293,6 +293,33 @@ DcPlacement dc_place(std::vector<DcEntry> ents, int k) {
   return out;
 }
 
+ColumnPlan column_plan(int64_t D, int b, int g, int64_t col_bytes, bool mixed, bool filter,
+                       const std::function<bool(int)> &fused) {
+  auto pow2 = [](int n) {
+    int w = 1;
+    while (w < n) w *= 2;
+    return w;
+  };
+  const int w = pow2(g);
+  if (!fused(w) || (mixed && w > b && D * w * 4 < (int64_t(4) << 20))) return {g, 1, false, 0, 0};
+  const int64_t fit = std::max<int64_t>(1, kRecCacheBytes / (D * w * col_bytes));
+  auto launches = [&](int64_t groups) { return (groups + fit - 1) / fit; };  // of about equal size
+  int64_t groups = (b + w - 1) / w;
+  int tail = b % w, tail_w = 0;
+  if (tail > 0 && b > w) {
+    tail_w = std::max(2, pow2(tail));
+    const bool own = tail_w < w && (launches(b / w) < launches(groups) ||
+                                    (!mixed && (w - tail_w) * D >= (filter ? kPadRowsFilter : kPadRows)));
+    if (own) --groups;
+    if (!own) tail = tail_w = 0;
+    else if (!fused(tail_w)) tail_w = tail;
+  } else {
+    tail = 0;
+  }
+  const int64_t n = launches(groups);
+  return {w, static_cast<int>((groups + n - 1) / n), true, tail, tail_w};
+}
+
 double onchip_apply_us(int L, const FlipCounts &f) {
   const double rows = std::max<double>(std::ldexp(1.0, L), 512.0);  // at least one element a thread
   const bool single = f.flips > f.table_plain + f.table_signed;

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cstdint>
+#include <functional>
 #include <vector>
 
 #include "../../include/dacp.h"
@@ -120,6 +121,34 @@ struct MomentChain {
   int64_t missing = -1;             // an order the assembly needs that the anchors do not reach
 };
 MomentChain moment_chain(const std::vector<int64_t> &orders, const std::vector<int64_t> &anchors);
+
+// Column groups of a recurrence over b columns of D rows, `g` wanted per group.  The fused kernels take
+// power-of-two widths (fused(w)), so a ragged width is rounded up to w and the columns past b are zero
+// (they cost no launch, where the general kernels take twice as long per step), and `per` groups advance
+// in one launch.  One group of 8 columns is 2 to 32 MB a block below 2^19 rows, whose launches are bound by
+// their own start and end (6-8 us each at 2^16 rows, the streams' rate would take 2.5); together they
+// stream at the rate of a large copy.  A launch's groups stay within the 256 MB Infinity Cache (col_bytes
+// a row and column over the live blocks): past it every step would go to HBM (two groups at once at 2^20
+// rows: 50-60 us a group, alone 43); half of it costs the FP64 filter at 2^17 to 2^19 rows 5-8 %.
+//
+// The columns left over by whole groups go along with them as one more padded group, or, where that moves
+// more than a launch costs, in a launch of their own of the next power of two (tail columns of width
+// tail_w; without a fused plan for it the general kernels at their own number).  A launch of their own is
+// always right when the padded group would need one too; else from kPadRows padded rows on: 9 columns of 2^20
+// rows took 10.8 ms padded to 16 and 8.4 as 8 and 1; 9 of 2^17 rows 1.7 and 2.2 (evolution); the filter's
+// four launches an order put the line higher (9 of 2^18: 6.4 and 7.2), and in mixed precision, where widths
+// below 4 have no fused plan, sharing a launch is right at any size (9 of 2^19: 10.0 and 12.3).
+// Mixed precision: a padded group alone of less than 4 MB in FP32 is slower than the general kernels at the
+// ragged width (5 columns of 2^16 rows: 2.2 against 1.9 ms).
+constexpr int64_t kRecCacheBytes = int64_t(256) << 20;
+constexpr int64_t kPadRows = int64_t(5) << 18, kPadRowsFilter = int64_t(2) << 20;
+struct ColumnPlan {
+  int g, per;
+  bool fused;
+  int tail, tail_w;
+};
+ColumnPlan column_plan(int64_t D, int b, int g, int64_t col_bytes, bool mixed, bool filter,
+                       const std::function<bool(int)> &fused);
 
 // Route of a recurrence up to 14 spins: a workgroup per column on chip (batch.hip), or the kernels that
 // step through memory, spread over the GPU.  Microseconds of one apply, fitted to what both took on

@@ -31,3 +31,7 @@ def test_worker_contexts_describe_the_callers_device(tmp_path):
 
 def test_onchip_route_is_the_faster_one(tmp_path):
     run(tmp_path, "onchip_route", os.path.join(NATIVE, "onchip_route_harness.cpp"), os.path.join(CSRC, "host_rules.cpp"))
+
+
+def test_column_groups_pad_only_where_it_pays(tmp_path):
+    run(tmp_path, "column_plan", os.path.join(NATIVE, "column_plan_harness.cpp"), os.path.join(CSRC, "host_rules.cpp"))
