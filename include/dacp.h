@@ -479,7 +479,9 @@ dacp_status dacp_spacing_ratios(const double *eigs, int n, double *r_out, double
  * rows) and high-tile row count
  * (automatic, 1, 2), at the real state length, and keeps the fastest in ctx (the "group",
  * "rec_threads", "rec_tile", "rec_hi_w" knobs).  best_group and best_us_per_column_step (host,
- * may be NULL) get the winner's group width and its time per column and step. */
+ * may be NULL) get the winner's group width and its time per column and step.  It times the recurrence
+ * through memory, also up to 14 spins, where most calls run a column whole on a compute unit, which
+ * none of these knobs steers. */
 dacp_status dacp_autotune(dacp_ctx ctx, dacp_ham h, int b, int steps, int *best_group, double *best_us_per_column_step);
 
 /* Autotuner of the batched schedule: runs dacp_central_eigs_batched on a sample of the realisations

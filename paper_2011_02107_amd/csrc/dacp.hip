@@ -1052,7 +1052,7 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
 }
 
 dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, const double *psi_e, double *V,
-                      int64_t ldv, int *m_out, EvolStats *stats) {
+                      int64_t ldv, int *m_out, EvolStats *stats, bool onchip = true) {
   const int64_t D = h->D;
   const int b = p->b, n = p->n;
   if (b < 1 || n < 1 || !(p->e_bound > 0.0) || !(p->a > 0.0) || p->a >= p->e_bound || !psi_e || !V)
@@ -1067,7 +1067,7 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     panel_of[ks[i]] = 2 * i + 2;
   }
   const int64_t kmax = ks.back();
-  if (onchip_fits(ctx, h, b, ldv, static_cast<double>(kmax))) {
+  if (onchip && onchip_fits(ctx, h, b, ldv, static_cast<double>(kmax))) {
     Timer tm(ctx);
     tm.start();
     DACP_TRY(onchip_evolve(ctx, h, p->e_bound, b, psi_e, ks, V, ldv, nullptr, nullptr, 0, "basis"));
@@ -3819,8 +3819,9 @@ dacp_status dacp_autotune(dacp_ctx ctx, dacp_ham h, int b, int steps, int *best_
     EvolStats es;
     int m = 0;
     // first call loads the kernels and the flip tables, the second is timed
-    dacp_status st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * ncol, &m, &es);
-    if (st == DACP_OK) st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * ncol, &m, &es);
+    // (the kernels that the knobs are for, also where a call would take the on-chip one)
+    dacp_status st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * ncol, &m, &es, false);
+    if (st == DACP_OK) st = run_basis(ctx, h, &bp, psi.as<double>(), V.as<double>(), 3 * ncol, &m, &es, false);
     if (st != DACP_OK || es.steps < 1) {
       ctx->err.clear();
       continue;
