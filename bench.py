@@ -634,9 +634,9 @@ def main():
     rep = reps[-1]
     D = 1 << L
     g = rep["evol_group"]
-    # one evolution step of a column group reads T_k and T_{k-1} and writes T_{k+1}:
-    # 3 D g 8 algorithmic bytes per step (one step = the low-bit and the high-bit pass at L >= 15)
-    bytes_per_launch = 3.0 * D * g * 8
+    # one evolution step of a column reads T_k and T_{k-1} and writes T_{k+1}: 3 D 8 algorithmic bytes
+    # (one step = the low-bit and the high-bit pass at L >= 15), over the launches that took them
+    bytes_per_launch = 3.0 * D * 8 * rep["b"] * rep["evol_steps"] / max(1, rep["evol_launches"])
     evol_launch_ms = rep["evol_kernel_ms"] / max(1, rep["evol_launches"])
     achieved = bytes_per_launch / (evol_launch_ms * 1e-3) / 1e9
     # filter: per order 5 D b s algorithmic bytes (w round trip included); s = 4 for the FP32 orders

@@ -368,7 +368,7 @@ typedef struct {
   double t_bound_ms, t_filter_ms, t_evol_ms, t_project_ms, t_gep_ms, t_accept_ms, t_total_ms;
   double evol_kernel_ms;    /* HIP-event time of the evolution launches only        */
   double max_err_est;       /* largest accepted error estimate                      */
-  int evol_group;           /* columns one evolution launch advances                */
+  int evol_group;           /* column-group width the evolution ran with            */
   int n_ghost;              /* candidates whose residual reaches the window edge   */
   int model_used;           /* dacp_central_eigs_learned: 1 = bound and window from the network */
   int model_fallback;       /* 1 = the network's window failed and Lanczos / KPM redid the call */

@@ -1067,15 +1067,15 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     panel_of[ks[i]] = 2 * i + 2;
   }
   const int64_t kmax = ks.back();
+  const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
   if (onchip && onchip_fits(ctx, h, b, ldv, static_cast<double>(kmax))) {
     Timer tm(ctx);
     tm.start();
     DACP_TRY(onchip_evolve(ctx, h, p->e_bound, b, psi_e, ks, V, ldv, nullptr, nullptr, 0, "basis"));
     if (m_out) *m_out = m;
-    if (stats) *stats = {kmax, 1, tm.stop_ms(), b};
+    if (stats) *stats = {kmax, 1, tm.stop_ms(), gt};
     return DACP_OK;
   }
-  const int gt = (p->group > 0 && p->group < b) ? p->group : recurrence_group(ctx, h, b);
   const ColGroups cg = column_groups(ctx, h, b, gt, 3, {8});
   DevBuf ba, bb, nrm, pbuf;
   DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
@@ -1129,7 +1129,7 @@ dacp_status run_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *p, cons
     stats->steps = kmax;
     stats->launches = launches;
     stats->kernel_ms = evol_ms;
-    stats->group = std::min(b, cg.g * cg.per);
+    stats->group = gt;
   }
   return DACP_OK;
 }
@@ -1366,7 +1366,7 @@ dacp_status run_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_params *
     stats->steps = kmax;
     stats->launches = launches;
     stats->kernel_ms = evol_ms;
-    stats->group = std::min(b, cg.g * cg.per);
+    stats->group = g;
   }
   return DACP_OK;
 }
@@ -1562,7 +1562,7 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
     const double evol_ms = tm.stop_ms();
     DACP_TRY(anchor_projection(ctx, h, mp.orders, anchors, abuf.as<double>(), V, ldv, b, p->e_bound, S, P, ld, gram_ms));
     if (m_out) *m_out = m;
-    if (stats) *stats = {kn + 1, 1, evol_ms, b};
+    if (stats) *stats = {kn + 1, 1, evol_ms, gt};
     return DACP_OK;
   }
   const ColGroups cg = column_groups(ctx, h, b, gt, 3, {8});
@@ -1623,7 +1623,7 @@ dacp_status run_stored_moment_basis(dacp_ctx ctx, dacp_ham h, const dacp_basis_p
     stats->steps = kn + 1;
     stats->launches = launches;
     stats->kernel_ms = evol_ms;
-    stats->group = std::min(b, cg.g * cg.per);
+    stats->group = gt;
   }
   return DACP_OK;
 }
