@@ -294,7 +294,8 @@ dacp_status dacp_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, dou
  * n[i] (host): 1 <= n[i] <= 2048.  A[i] (host array of device pointers): symmetric n[i] x n[i],
  * row-major, ld n[i], destroyed.  w[i] (host array of host pointers): n[i] eigenvalues ascending.
  * Z[i] (host array of device pointers, entries may be NULL): n[i] x n[i], row j = eigenvector j.
- * Errors: DACP_E_INVALID (sizes, null pointers), DACP_E_CONVERGENCE (QR did not converge). */
+ * Errors: DACP_E_INVALID (sizes, null pointers), DACP_E_CONVERGENCE (no convergence; also a matrix that is
+ * not finite). */
 dacp_status dacp_syev_batched(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
                               double *const *Z);
 

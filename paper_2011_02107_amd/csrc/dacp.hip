@@ -2408,7 +2408,9 @@ dacp_status dacp_syev_batched(dacp_ctx ctx, int count, const int *n, double *con
   try {
     std::vector<dacp::SyevJob> jobs;
     for (int i = 0; i < count; ++i) jobs.push_back({n[i], A[i], n[i], w[i], Z[i]});
-    return dacp::syev_jobs(ctx, jobs);
+    const dacp_status st = dacp::syev_jobs(ctx, jobs);
+    if (st == DACP_E_NUMERIC) return set_err(ctx, DACP_E_CONVERGENCE, "syev_batched: no convergence, " + ctx->err);
+    return st;
   } catch (...) {
     return set_err(ctx, DACP_E_NOMEM, "syev_batched: host allocation failed");
   }

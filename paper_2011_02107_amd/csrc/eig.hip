@@ -410,7 +410,13 @@ static dacp_status solve_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double
   // While the registers of the GPU hold the matrix it stays there (tridiag.hip; 3072 rows on 256 compute
   // units), unless the knobs ask for the panel form or for implicit QR.
   if (syev_on_chip(ctx, n) && ctx->dc_min_n > 0 && !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB)))
-    return syev_jobs(ctx, {{n, A, ld, w, Zrows}});
+  {
+    const dacp_status s = syev_jobs(ctx, {{n, A, ld, w, Zrows}});
+    // where QR iteration would have run, a matrix that is not finite is one on which it does not end
+    if (s == DACP_E_NUMERIC && (!Zrows || n < ctx->dc_min_n))
+      return set_err(ctx, DACP_E_CONVERGENCE, "eigensolver: no convergence, " + ctx->err);
+    return s;
+  }
   DevBuf vecs;  // five vectors of the tridiagonalisation
   const size_t nv = (static_cast<size_t>(n) + 31) / 32 * 32;
   DACP_HIP(ctx, vecs.alloc(5 * sizeof(double) * nv));
