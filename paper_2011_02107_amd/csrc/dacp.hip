@@ -2107,6 +2107,11 @@ dacp_status dacp_tune(dacp_ctx ctx, const char *key, int value) {
     ctx->blocked_min_n = value;
     return DACP_OK;
   }
+  if (k == "tri_spins") {
+    if (value < 0 || value > (1 << 26)) return set_err(ctx, DACP_E_INVALID, "tri_spins: 0..2^26");
+    ctx->tri_spins = value;
+    return DACP_OK;
+  }
   if (k == "project_whole") {
     if (value != 0 && value != 1) return set_err(ctx, DACP_E_INVALID, "project_whole: 0 or 1");
     ctx->project_whole = value;
@@ -2153,6 +2158,7 @@ dacp_status dacp_tune_get(dacp_ctx ctx, const char *key, int *value) {
   else if (k == "two_pass_L") *value = ctx->two_pass_min_L;
   else if (k == "fused") *value = ctx->fused_rec;
   else if (k == "dc") *value = ctx->dc_min_n;
+  else if (k == "tri_spins") *value = ctx->tri_spins;
   else if (k == "group") *value = ctx->group_default;
   else if (k == "filter_group_f64") *value = ctx->filter_group_f64;
   else if (k == "filter_group_f32") *value = ctx->filter_group_f32;

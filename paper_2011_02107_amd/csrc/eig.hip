@@ -393,7 +393,7 @@ static double wall_ms() {
   return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
-static dacp_status solve_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows) {
+static dacp_status solve_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows, bool registers) {
   hipStream_t st = ctx->stream;
   const double t_begin = wall_ms();
   if (n <= 0) return DACP_OK;
@@ -409,8 +409,8 @@ static dacp_status solve_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double
   }
   // While the registers of the GPU hold the matrix it stays there (tridiag.hip; 3072 rows on 256 compute
   // units), unless the knobs ask for the panel form or for implicit QR.
-  if (syev_on_chip(ctx, n) && ctx->dc_min_n > 0 && !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB)))
-  {
+  if (registers && syev_on_chip(ctx, n) && ctx->dc_min_n > 0 &&
+      !(ctx->blocked_min_n > 0 && n >= std::max(ctx->blocked_min_n, 8 * kTB))) {
     const dacp_status s = syev_jobs(ctx, {{n, A, ld, w, Zrows}});
     // where QR iteration would have run, a matrix that is not finite is one on which it does not end
     if (s == DACP_E_NUMERIC && (!Zrows || n < ctx->dc_min_n))
@@ -662,9 +662,9 @@ static dacp_status solve_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double
   return DACP_OK;
 }
 
-dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows) {
+dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows, bool registers) {
   try {
-    return solve_syev(ctx, n, A, ld, w, Zrows);
+    return solve_syev(ctx, n, A, ld, w, Zrows, registers);
   } catch (...) {  // the host's tables; the callers are C entry points
     return set_err(ctx, DACP_E_NOMEM, "eigensolver: host allocation failed");
   }

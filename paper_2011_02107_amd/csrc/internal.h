@@ -387,6 +387,10 @@ struct dacp_ctx_s {
   int dc_min_n = 96;           // eigenvectors by divide and conquer from this size on (0 = never)
   int blocked_min_n = 3500;    // blocked tridiagonalisation and compact-WY Q from this size on (0 = never);
                                // below it the unblocked form issues fewer launches and is faster
+  // register tridiagonalisation: polls of one exchanged value before it gives up, tens of seconds where a
+  // step takes microseconds, since other streams' kernels may hold the compute units that the launch's last
+  // workgroups wait for
+  int tri_spins = 1 << 24;
   // A worker thread's context for o's device: what the device is (num_cus bounds the cooperative launches
   // and not only the tuning) and the knobs of the stages that workers run.
   void worker_of(const dacp_ctx_s &o) {
@@ -397,6 +401,7 @@ struct dacp_ctx_s {
     two_pass_min_L = o.two_pass_min_L;
     dc_min_n = o.dc_min_n;
     blocked_min_n = o.blocked_min_n;
+    tri_spins = o.tri_spins;
   }
 };
 
@@ -465,8 +470,8 @@ dacp_status hip_err(dacp_ctx ctx, hipError_t e, const char *what);
 // Progress lines on stderr when the environment variable DACP_VERBOSE is set.
 bool verbose();
 void vlog(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
-// Dense symmetric eigensolver (eig.hip).
-dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows);
+// Dense symmetric eigensolver (eig.hip); registers = false: the matrix stays in memory at every size.
+dacp_status gpu_syev(dacp_ctx ctx, int n, double *A, int64_t ld, double *w, double *Zrows, bool registers = true);
 // The allocation-free form (dacp_syev_batched_noalloc): every device buffer besides A and Zrows comes
 // from one fixed device array of kNoAllocScratchBytes per device (beig.hip).  noalloc_scratch_init
 // resolves that device's address once (call it with the device current); batch_syev_noalloc_bytes

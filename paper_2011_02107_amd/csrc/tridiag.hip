@@ -15,9 +15,6 @@ namespace dacp {
 
 namespace {
 
-// polls of one value before a workgroup gives up: tens of seconds, where a step takes microseconds, since
-// other streams' kernels may hold the compute units that the launch's last workgroups wait for
-constexpr int kSpinLimit = 1 << 24;
 constexpr unsigned long long kEmpty = ~0ull;  // exchange slot not written yet
 
 // One matrix of a launch: workgroups wg0 .. wg0 + G - 1 hold its rows.
@@ -79,10 +76,11 @@ __device__ __forceinline__ void publish(double *slot, double v) {
 //   - a published double is its own flag: slots start out as a NaN pattern that no result has
 //     (another one is written for it), every step has slots of its own, and readers poll them
 //     with relaxed agent-scope loads, so no fence or counter is involved.
-// The launch is cooperative: all workgroups are resident, and a poll that outlasts kSpinLimit ends
+// The launch is cooperative: all workgroups are resident, and a poll that outlasts `spins` ends
 // its workgroup with *fail set, which ends the others the same way.
 template <int NWV, int NE, int R>
-__global__ __launch_bounds__(64 * NWV, NWV / 4) void k_tridiag(const TriProb *probs, const int *wg_prob, int *fail) {
+__global__ __launch_bounds__(64 * NWV, NWV / 4) void k_tridiag(const TriProb *probs, const int *wg_prob, int *fail,
+                                                                   int spins) {
   constexpr int NT = 64 * NWV;
   __shared__ double lv[2][NT * NE];  // v of the last two steps (a row's own element)
   __shared__ double part[NWV][R];    // per wave: the rows' parts of A v
@@ -242,7 +240,7 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_tridiag(const TriProb *pr
             todo &= ~(2u << (2 * e));
           }
         }
-        if (spin >= kSpinLimit) {
+        if (spin >= spins) {
           failed = 1;
           break;
         }
@@ -434,8 +432,9 @@ bool syev_on_chip(dacp_ctx ctx, int n) {
 }
 
 // The tridiagonalisations: matrices of similar size go together, largest first, each launch taking
-// as many as the compute units hold (one workgroup each).
-static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, TriProb *dprobs) {
+// as many as the compute units hold (one workgroup each).  timed_out: an exchange waited too long (other
+// processes' kernels hold compute units); the results are not there.
+static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, TriProb *dprobs, bool &timed_out) {
   hipStream_t st = ctx->stream;
   const int np = static_cast<int>(probs.size());
   std::vector<int> order(np);
@@ -493,17 +492,19 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
   for (const Launch &ln : launches) {
     const TriProb *ap = dprobs;
     const int *aw = dwg.as<int>() + ln.wg0;
-    void *args[] = {&ap, &aw, &fail};
+    int spins = ctx->tri_spins;
+    void *args[] = {&ap, &aw, &fail, &spins};
     DACP_HIP(ctx, hipLaunchCooperativeKernel(ln.fn, dim3(ln.wgs), dim3(ln.threads), args, 0, st));
   }
   int failed = 0;
   DACP_TRY(to_host(ctx, &failed, fail, sizeof(int)));
-  if (failed) return set_err(ctx, DACP_E_HIP, "eigensolver: tridiagonalisation's exchange timed out");
+  timed_out = failed != 0;
   return DACP_OK;
 }
 
-// One round: np matrices together.  A is only read, so a round that fails can be run again.
-static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np) {
+// One round: np matrices together.  A is only read, so a round that fails can be run again, and one whose
+// exchange timed out is left to the caller.
+static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np, bool &timed_out) {
   hipStream_t st = ctx->stream;
   size_t zs = 0, vs = 0, xs = 0, ds = 0;
   for (int i = 0; i < np; ++i) {
@@ -542,7 +543,9 @@ static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np) {
         for (int r0 = 0; r0 < j.n; r0 += kWyRows) apply.push_back({i, r0});
     }
   }
-  DACP_TRY(tridiagonalise(ctx, probs, bp.as<TriProb>()));
+  timed_out = false;
+  DACP_TRY(tridiagonalise(ctx, probs, bp.as<TriProb>(), timed_out));
+  if (timed_out) return DACP_OK;
   DACP_TRY(dc_tridiag_jobs(ctx, dc));
   if (!prep.empty()) {
     DevBuf bw;
@@ -576,7 +579,13 @@ static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
   int per = static_cast<int>(jobs.size());
   for (int at = 0, np = per; at < np;) {
     const int take = std::min(per, np - at);
-    const dacp_status st = solve_round(ctx, jobs.data() + at, take);
+    bool timed_out = false;
+    dacp_status st = solve_round(ctx, jobs.data() + at, take, timed_out);
+    if (st == DACP_OK && timed_out) {
+      vlog("eigensolver: register tridiagonalisation timed out, %d matrices column by column", take);
+      for (int i = at; st == DACP_OK && i < at + take; ++i)
+        st = gpu_syev(ctx, jobs[i].n, jobs[i].A, jobs[i].lda, jobs[i].w, jobs[i].Z, false);
+    }
     if (st == DACP_E_NOMEM && take > 1) {
       (void)hipGetLastError();
       ctx->err.clear();
