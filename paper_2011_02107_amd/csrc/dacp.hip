@@ -3067,6 +3067,9 @@ class EigRendezvous {
     } catch (...) {
       st = set_err(ctx, DACP_E_NOMEM, "batched eigensolver: host allocation failed");
     }
+    // a round that failed half way may still be writing the waiting threads' buffers, which they release
+    // to their own streams on return
+    if (st != DACP_OK) (void)hipStreamSynchronize(stream_);
     for (Arrival *a : arrived_) {
       a->st = st;
       if (st != DACP_OK && a->ctx != ctx) a->ctx->err = ctx->err;
