@@ -1483,9 +1483,12 @@ dacp_status anchor_projection(dacp_ctx ctx, dacp_ham h, const std::vector<int64_
   DACP_HIP(ctx, gd.alloc(static_cast<size_t>(mg) * m * sizeof(double)));
   {
     DevBuf work;
-    const int sp = dacp::gemm_splits(mg, m, D, 0, ctx->num_cus, 1024, 64);
+    int sp = dacp::gemm_splits(mg, m, D, 0, ctx->num_cus, 1024, 64);
+    if (sp > 1 && work.alloc(static_cast<size_t>(sp) * mg * m * sizeof(double)) != hipSuccess) {
+      (void)hipGetLastError();
+      sp = 1;
+    }
     if (sp > 1) {
-      DACP_HIP(ctx, work.alloc(static_cast<size_t>(sp) * mg * m * sizeof(double)));
       DACP_HIP(ctx, dacp::launch_dgemm_splitk(1, 0, mg, m, D, 1.0, abuf, mg, V, ldv, 0.0, gd.as<double>(), m, 0, sp,
                                               work.as<double>(), s));
     } else {
@@ -1687,13 +1690,15 @@ dacp_status run_project(dacp_ctx ctx, dacp_ham h, int m, const double *V, int64_
     }
     (void)hipGetLastError();  // a failed allocation here only selects the chunked form
   }
+  split_work.release();  // S is queued, and the chunks' buffers come first
   const int cw = std::min(m, 512);
   DevBuf wbuf;
   DACP_HIP(ctx, wbuf.alloc(static_cast<size_t>(D) * cw * sizeof(double)));
   double *W = wbuf.as<double>();
-  // The early chunks have few output tiles against a K of 2^L: split K to fill the GPU.
+  // The early chunks have few output tiles against a K of 2^L: split K to fill the GPU, if there is room.
+  int max_splits = 64;
   auto splits_for = [&](int rows, int cols) {
-    return dacp::gemm_splits(rows, cols, D, 0, ctx->num_cus, 1024, 64);
+    return dacp::gemm_splits(rows, cols, D, 0, ctx->num_cus, 1024, max_splits);
   };
   size_t work_elems = 0;
   for (int c0 = 0; c0 < m; c0 += cw) {
@@ -1702,7 +1707,10 @@ dacp_status run_project(dacp_ctx ctx, dacp_ham h, int m, const double *V, int64_
     if (sp > 1) work_elems = std::max(work_elems, static_cast<size_t>(sp) * c1 * (c1 - c0));
   }
   DevBuf work;
-  if (work_elems) DACP_HIP(ctx, work.alloc(work_elems * sizeof(double)));
+  if (work_elems && work.alloc(work_elems * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    max_splits = 1;
+  }
   for (int c0 = 0; c0 < m; c0 += cw) {
     const int c1 = std::min(m, c0 + cw);
     const int w = c1 - c0;
