@@ -35,3 +35,7 @@ def test_onchip_route_is_the_faster_one(tmp_path):
 
 def test_column_groups_pad_only_where_it_pays(tmp_path):
     run(tmp_path, "column_plan", os.path.join(NATIVE, "column_plan_harness.cpp"), os.path.join(CSRC, "host_rules.cpp"))
+
+
+def test_secular_roots_against_long_double(tmp_path):
+    run(tmp_path, "secular", os.path.join(NATIVE, "secular_harness.cpp"))
