@@ -439,8 +439,9 @@ size_t align8(size_t x) { return (x + 7) / 8 * 8; }
 
 size_t dc_work_doubles(int n) { return 3 * static_cast<size_t>(n) * n; }
 
-dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
+dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs_in) {
   hipStream_t st = ctx->stream;
+  std::vector<DcJob> jobs(jobs_in);
   std::vector<std::vector<Node>> inner, leaf;
   std::vector<size_t> woff(jobs.size() + 1, 0);
   for (size_t i = 0; i < jobs.size(); ++i) {
@@ -475,21 +476,6 @@ dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
       DACP_HIP(ctx, hipMemcpyAsync(eh.data() + woff[i], jobs[i].e, (jobs[i].n - 1) * sizeof(double),
                                    hipMemcpyDeviceToHost, st));
   }
-  {
-    std::vector<DcLeaf> ls;
-    for (size_t t = 0; t < leaf.size(); ++t)
-      for (const Node &nd : leaf[t])
-        ls.push_back({jobs[nd.job].d, jobs[nd.job].e, buffer(nd.job, t), wdev + woff[nd.job], jobs[nd.job].n, nd.lo, nd.hi});
-    const int zero = 0;
-    DACP_HIP(ctx, hipMemcpyAsync(bad, &zero, sizeof(int), hipMemcpyHostToDevice, st));
-    DACP_TRY(to_device(ctx, dleaf.p, ls.data(), ls.size() * sizeof(DcLeaf)));
-    for (size_t i = 0; i < wtot; ++i)
-      if (!std::isfinite(dh[i]) || !std::isfinite(eh[i]))
-        return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite tridiagonal entry");
-    hipLaunchKernelGGL(k_dc_leaf, dim3(static_cast<unsigned>(ls.size())), dim3(64), 0, st, dleaf.as<DcLeaf>(), bad);
-    DACP_HIP(ctx, hipGetLastError());
-  }
-
   // the merges' blocks and buffers, every depth in one upload (the update vectors' kernel reads them)
   std::vector<DcMerge> geo;
   std::vector<size_t> geo_at(inner.size());
@@ -518,6 +504,45 @@ dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
   DevBuf dgeo;
   DACP_HIP(ctx, dgeo.alloc(geo.size() * sizeof(DcMerge)));
   DACP_TRY(to_device(ctx, dgeo.p, geo.data(), geo.size() * sizeof(DcMerge)));
+  if (geo.empty()) DACP_HIP(ctx, hipStreamSynchronize(st));  // else the upload has waited for the diagonals
+  for (size_t i = 0; i < wtot; ++i)
+    if (!std::isfinite(dh[i]) || !std::isfinite(eh[i]))
+      return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite tridiagonal entry");
+  // A matrix of a scale far from 1 is solved as its multiple by a power of two (which is exact): the secular
+  // equation squares the poles' distances and their reciprocals.
+  std::vector<int> scale(jobs.size(), 0);
+  DevBuf scaled;
+  {
+    size_t at = 0;
+    for (size_t i = 0; i < jobs.size(); ++i) {
+      double top = 0.0;
+      for (size_t q = woff[i]; q < woff[i + 1]; ++q) top = std::max({top, std::fabs(dh[q]), std::fabs(eh[q])});
+      if (top > 0.0 && (top < 1e-60 || top > 1e60)) scale[i] = std::ilogb(top), at += 2 * static_cast<size_t>(jobs[i].n);
+    }
+    if (at > 0) {
+      std::vector<double> host;
+      DACP_HIP(ctx, scaled.alloc(at * sizeof(double)));
+      for (size_t i = 0; i < jobs.size(); ++i) {
+        if (scale[i] == 0) continue;
+        for (std::vector<double> *v : {&dh, &eh}) {
+          (v == &dh ? jobs[i].d : jobs[i].e) = scaled.as<double>() + host.size();
+          for (size_t q = woff[i]; q < woff[i + 1]; ++q) host.push_back((*v)[q] = std::scalbn((*v)[q], -scale[i]));
+        }
+      }
+      DACP_TRY(to_device(ctx, scaled.p, host.data(), at * sizeof(double)));
+    }
+  }
+  {
+    std::vector<DcLeaf> ls;
+    for (size_t t = 0; t < leaf.size(); ++t)
+      for (const Node &nd : leaf[t])
+        ls.push_back({jobs[nd.job].d, jobs[nd.job].e, buffer(nd.job, t), wdev + woff[nd.job], jobs[nd.job].n, nd.lo, nd.hi});
+    const int zero = 0;
+    DACP_HIP(ctx, hipMemcpyAsync(bad, &zero, sizeof(int), hipMemcpyHostToDevice, st));
+    DACP_TRY(to_device(ctx, dleaf.p, ls.data(), ls.size() * sizeof(DcLeaf)));
+    hipLaunchKernelGGL(k_dc_leaf, dim3(static_cast<unsigned>(ls.size())), dim3(64), 0, st, dleaf.as<DcLeaf>(), bad);
+    DACP_HIP(ctx, hipGetLastError());
+  }
 
   std::vector<double> host_wz(2 * wtot + 1);
   std::vector<unsigned char> blob(table_bytes);
@@ -673,7 +698,7 @@ dacp_status dc_tridiag_jobs(dacp_ctx ctx, const std::vector<DcJob> &jobs) {
   for (size_t i = 0; i < wtot; ++i)
     if (!std::isfinite(host_wz[i])) return set_err(ctx, DACP_E_NUMERIC, "divide and conquer: non-finite root");
   for (size_t i = 0; i < jobs.size(); ++i)
-    if (jobs[i].n > 0) std::copy_n(host_wz.begin() + woff[i], jobs[i].n, jobs[i].w);
+    for (int q = 0; q < jobs[i].n; ++q) jobs[i].w[q] = std::scalbn(host_wz[woff[i] + q], scale[i]);
   return DACP_OK;
 }
 

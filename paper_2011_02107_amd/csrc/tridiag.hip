@@ -246,10 +246,12 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_tridiag(const TriProb *pr
         }
       }
     }
-    // w = p - (beta p^T v / 2) v with p = beta A v; then row k + 1 as this step leaves it
+    // w = p - (beta p^T v / 2) v with p = beta A v (beta first: A v is of the matrix' scale squared, and its
+    // product with v would leave the range past 1e+-103); then row k + 1 as this step leaves it
     double pv = 0.0;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
+      p[e] *= beta;
       pv += p[e] * x[e];
       if (tid + NT * e == k + 1) sc[2] = p[e];
     }
@@ -260,14 +262,14 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_tridiag(const TriProb *pr
       if (tid == 0) *fail = 1;
       return;
     }
-    hprev = 0.5 * beta * (beta * total(red2));
+    hprev = 0.5 * beta * total(red2);
     bprev = beta;
-    const double wk1 = beta * sc[2] - hprev * v0;
+    const double wk1 = sc[2] - hprev * v0;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
       const int j = tid + NT * e;
       v[e] = x[e];
-      w[e] = beta * p[e] - hprev * x[e];
+      w[e] = p[e] - hprev * x[e];
       x[e] = (j > k && j < n) ? raw[e] - (v0 * w[e] + wk1 * v[e]) : 0.0;
     }
   }
