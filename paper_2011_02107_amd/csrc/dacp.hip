@@ -939,7 +939,7 @@ dacp_status evolve_group(dacp_ctx ctx, dacp_ham h, double inv_e, int64_t kmax, i
   if (want(1)) DACP_TRY(visit(1, B, A));
   const int64_t report_every = std::max<int64_t>(1, kmax / 8);
   int lo_bits = 0, hw = 1;
-  if (kmax > 1 && fused_plan(ctx, h, gw, lo_bits, hw, 8)) {
+  if (kmax > 1 && Pp && fused_plan(ctx, h, gw, lo_bits, hw, 8)) {
     // P_2 = (2/E)(D + Lo) T_1 - T_0 by the low-bit pass, then alternate high / low fused kernels.
     st = split_order(ctx, h, lo_bits);
     if (st) return st;
@@ -1947,11 +1947,25 @@ dacp_status moment_dots(dacp_ctx ctx, dacp_ham h, double e_bound, int M, int nve
       for (int i = 0; i < M; ++i) d[(i & 1) ? i + 2 : i] += out[static_cast<size_t>(q) * M + i];
     return DACP_OK;
   }
-  const ColGroups cg = column_groups(ctx, h, nvec, recurrence_group(ctx, h, nvec), 3, {8});
+  ColGroups cg = column_groups(ctx, h, nvec, recurrence_group(ctx, h, nvec), 3, {8});
   DevBuf ba, bb, bp, part, sums;
-  DACP_HIP(ctx, ba.alloc(cg.elems(D) * sizeof(double)));
-  DACP_HIP(ctx, bb.alloc(cg.elems(D) * sizeof(double)));
-  DACP_HIP(ctx, bp.alloc(cg.elems(D) * sizeof(double)));
+  auto blocks = [&]() -> hipError_t {
+    for (DevBuf *b : {&ba, &bb, &bp}) {
+      const hipError_t e = (b != &bp || cg.fused) ? b->alloc(cg.elems(D) * sizeof(double)) : hipSuccess;
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
+  hipError_t got_blocks = blocks();
+  if (got_blocks == hipErrorOutOfMemory && cg.fused) {  // single applies do with two blocks, of one group's columns
+    for (DevBuf *b : {&ba, &bb, &bp}) b->release();
+    cg.fused = false;
+    cg.g = std::min(cg.g, nvec);
+    cg.per = 1;
+    cg.tail = 0;
+    got_blocks = blocks();
+  }
+  DACP_HIP(ctx, got_blocks);
   DACP_HIP(ctx, part.alloc(2 * static_cast<size_t>(kmax + 1) * 256 * sizeof(double)));
   DACP_HIP(ctx, sums.alloc(2 * static_cast<size_t>(kmax + 1) * sizeof(double)));
   std::vector<double> got(2 * kmax + 2);
