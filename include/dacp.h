@@ -130,8 +130,10 @@ dacp_status dacp_set_tile(dacp_ctx ctx, int tile_elems);
  *                 (default 96; matrices below the "blocked" value of up to 3072 rows always take it,
  *                 unless it is 0 = always implicit QR with replayed rotations)
  *   "tri_spins"   dense eigensolver: polls of an exchanged value (0..2^26, default 2^24: tens of seconds)
- *                 after which a tridiagonalisation in registers gives up and the matrices go column by
- *                 column, as when other processes' kernels hold compute units; 0 = at once
+ *                 after which a tridiagonalisation in registers gives up and the matrices are solved in
+ *                 memory, as when other processes' kernels hold compute units; 0 = at once.  (A process
+ *                 beside one that has solved in registers is refused that form by the runtime and solves
+ *                 in memory from the start.)
  * Results agree for every setting up to the rounding order of each element's sum ("moment_explicit":
  * within the values' certified error estimates, since S and P are formed differently).
  * Returns DACP_E_INVALID for an unknown key or a value out of range. */

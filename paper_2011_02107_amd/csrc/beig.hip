@@ -990,19 +990,9 @@ size_t batch_syev_noalloc_bytes(int count, const int *n) {
          round256(sizeof(WyItem) * batch_syev_items(count, n)) + round256(sizeof(int) * max_n);
 }
 
-dacp_status batch_syev_noalloc(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
-                               double *const *Zrows) {
-  if (count <= 0) return DACP_OK;
-  for (int i = 0; i < count; ++i)
-    if (n[i] < 1 || n[i] > kBatchEigMaxN) return set_err(ctx, DACP_E_INVALID, "batch_syev: 1 <= n <= 2048");
-  const size_t need = batch_syev_noalloc_bytes(count, n);
-  if (need > kNoAllocScratchBytes)
-    return set_err(ctx, DACP_E_INVALID,
-                   "syev_batched_noalloc: the matrices need " + std::to_string(need) +
-                       " bytes of workspace; the fixed workspace holds " + std::to_string(kNoAllocScratchBytes));
-  const hipError_t e = noalloc_scratch_init(ctx->device);
-  if (e != hipSuccess) return hip_err(ctx, e, "syev_batched_noalloc: hipGetSymbolAddress(scratch)");
-  unsigned char *base = static_cast<unsigned char *>(g_scratch_ptr[ctx->device]);
+// The solve on a workspace of batch_syev_noalloc_bytes.
+static dacp_status batch_syev_at(dacp_ctx ctx, unsigned char *base, int count, const int *n, double *const *A,
+                                 double *const *w, double *const *Zrows) {
   size_t wb = 0, z = 0;
   int max_n = 0;
   for (int i = 0; i < count; ++i) {
@@ -1041,6 +1031,28 @@ dacp_status batch_syev_noalloc(dacp_ctx ctx, int count, const int *n, double *co
   DACP_TRY(batch_syev_raw_on(ctx, count, n, A, zr.data(), work.data(), wr.data(), wk));
   for (int i = 0; i < count; ++i) DACP_TRY(batch_syev_finish_on(ctx, n[i], wr[i], zr[i], w[i], Zrows[i], dperm));
   return DACP_OK;
+}
+
+dacp_status batch_syev_noalloc(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
+                               double *const *Zrows) {
+  if (count <= 0) return DACP_OK;
+  for (int i = 0; i < count; ++i)
+    if (n[i] < 1 || n[i] > kBatchEigMaxN) return set_err(ctx, DACP_E_INVALID, "batch_syev: 1 <= n <= 2048");
+  const size_t need = batch_syev_noalloc_bytes(count, n);
+  if (need > kNoAllocScratchBytes)
+    return set_err(ctx, DACP_E_INVALID,
+                   "syev_batched_noalloc: the matrices need " + std::to_string(need) +
+                       " bytes of workspace; the fixed workspace holds " + std::to_string(kNoAllocScratchBytes));
+  const hipError_t e = noalloc_scratch_init(ctx->device);
+  if (e != hipSuccess) return hip_err(ctx, e, "syev_batched_noalloc: hipGetSymbolAddress(scratch)");
+  return batch_syev_at(ctx, static_cast<unsigned char *>(g_scratch_ptr[ctx->device]), count, n, A, w, Zrows);
+}
+
+dacp_status batch_syev_each(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
+                            double *const *Zrows) {
+  DevBuf work;
+  DACP_HIP(ctx, work.alloc(batch_syev_noalloc_bytes(count, n)));
+  return batch_syev_at(ctx, work.as<unsigned char>(), count, n, A, w, Zrows);
 }
 
 }  // namespace dacp

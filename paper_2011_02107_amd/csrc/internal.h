@@ -481,6 +481,9 @@ hipError_t noalloc_scratch_init(int device);
 size_t batch_syev_noalloc_bytes(int count, const int *n);
 dacp_status batch_syev_noalloc(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
                                double *const *Zrows);
+// The same solver, a workgroup a matrix, on a workspace of its own for the call.
+dacp_status batch_syev_each(dacp_ctx ctx, int count, const int *n, double *const *A, double *const *w,
+                            double *const *Zrows);
 bool host_tridiag_eig(const double *diag, const double *off, int n, double *w, double *Z);
 // Divide and conquer (dc.hip) of several symmetric tridiagonal matrices at once: d, e device (e[i]
 // couples i and i + 1), w host ascending, Z device n x n with row j = eigenvector j, work device

@@ -434,9 +434,10 @@ bool syev_on_chip(dacp_ctx ctx, int n) {
 }
 
 // The tridiagonalisations: matrices of similar size go together, largest first, each launch taking
-// as many as the compute units hold (one workgroup each).  timed_out: an exchange waited too long (other
-// processes' kernels hold compute units); the results are not there.
-static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, TriProb *dprobs, bool &timed_out) {
+// as many as the compute units hold (one workgroup each).  no_exchange: the runtime refused a cooperative launch
+// (it gives them to one process at a time on a device), or an exchange waited too long (other processes'
+// kernels hold compute units); the results are not there.
+static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, TriProb *dprobs, bool &no_exchange) {
   hipStream_t st = ctx->stream;
   const int np = static_cast<int>(probs.size());
   std::vector<int> order(np);
@@ -493,6 +494,7 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
                          reinterpret_cast<unsigned long long *>(p.X), nx);
     }
   DACP_HIP(ctx, hipGetLastError());
+  bool refused = false;
   for (const Launch &ln : launches) {
     const TriProb *ap = dprobs;
     const int *aw = dwg.as<int>() + ln.wg0;
@@ -500,18 +502,26 @@ static dacp_status tridiagonalise(dacp_ctx ctx, std::vector<TriProb> &probs, Tri
     void *args[] = {&ap, &aw, &fail, &spins};
     // matrices of one workgroup exchange nothing: an ordinary launch (eigenvalues of 5 rows: 135 us, as a
     // cooperative one 153, and a process without one waits about 1 us less at each synchronisation)
-    if (ln.shared) DACP_HIP(ctx, hipLaunchCooperativeKernel(ln.fn, dim3(ln.wgs), dim3(ln.threads), args, 0, st));
-    else DACP_HIP(ctx, hipLaunchKernel(ln.fn, dim3(ln.wgs), dim3(ln.threads), args, 0, st));
+    if (ln.shared) {
+      if (hipLaunchCooperativeKernel(ln.fn, dim3(ln.wgs), dim3(ln.threads), args, 0, st) != hipSuccess) {
+        const hipError_t e = hipGetLastError();
+        vlog("eigensolver: cooperative launch refused: %s", hipGetErrorString(e));
+        refused = true;
+        break;
+      }
+    } else {
+      DACP_HIP(ctx, hipLaunchKernel(ln.fn, dim3(ln.wgs), dim3(ln.threads), args, 0, st));
+    }
   }
   int failed = 0;
   DACP_TRY(to_host(ctx, &failed, fail, sizeof(int)));
-  timed_out = failed != 0;
+  no_exchange = refused || failed != 0;
   return DACP_OK;
 }
 
-// One round: np matrices together.  A is only read, so a round that fails can be run again, and one whose
-// exchange timed out is left to the caller.
-static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np, bool &timed_out) {
+// One round: np matrices together.  A is only read, so a round that fails can be run again, and one without an
+// exchange is left to the caller.
+static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np, bool &no_exchange) {
   hipStream_t st = ctx->stream;
   size_t zs = 0, vs = 0, xs = 0, ds = 0;
   for (int i = 0; i < np; ++i) {
@@ -550,9 +560,9 @@ static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np, bool &
         for (int r0 = 0; r0 < j.n; r0 += kWyRows) apply.push_back({i, r0});
     }
   }
-  timed_out = false;
-  DACP_TRY(tridiagonalise(ctx, probs, bp.as<TriProb>(), timed_out));
-  if (timed_out) return DACP_OK;
+  no_exchange = false;
+  DACP_TRY(tridiagonalise(ctx, probs, bp.as<TriProb>(), no_exchange));
+  if (no_exchange) return DACP_OK;
   DACP_TRY(dc_tridiag_jobs(ctx, dc));
   if (!prep.empty()) {
     DevBuf bw;
@@ -575,6 +585,29 @@ static dacp_status solve_round(dacp_ctx ctx, const SyevJob *jobs, int np, bool &
   return DACP_OK;
 }
 
+// The matrices of a round without an exchange, in memory: one after the other column by column (about 20 us a row:
+// 4.0 ms at 200 rows, 13.9 at 664), or, where that takes longer, together with a workgroup each (about 0.3 us times
+// the square of the largest's rows: 32 of 200 rows 14 ms, 8 of 664 rows 127).
+static dacp_status solve_apart(dacp_ctx ctx, const SyevJob *jobs, int np) {
+  std::vector<int> n;
+  std::vector<double *> A, w, Z;
+  int64_t rows = 0, max_n = 0;
+  bool whole = true;
+  for (int i = 0; i < np; ++i) {
+    n.push_back(jobs[i].n);
+    A.push_back(jobs[i].A);
+    w.push_back(jobs[i].w);
+    Z.push_back(jobs[i].Z);
+    rows += jobs[i].n;
+    max_n = std::max<int64_t>(max_n, jobs[i].n);
+    whole = whole && jobs[i].lda == jobs[i].n;
+  }
+  if (whole && np > 1 && max_n <= kBatchEigMaxN && 60 * rows > max_n * max_n)
+    return batch_syev_each(ctx, np, n.data(), A.data(), w.data(), Z.data());
+  for (int i = 0; i < np; ++i) DACP_TRY(gpu_syev(ctx, jobs[i].n, jobs[i].A, jobs[i].lda, jobs[i].w, jobs[i].Z, false));
+  return DACP_OK;
+}
+
 static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
   std::vector<SyevJob> jobs;
   for (const SyevJob &j : all) {
@@ -586,12 +619,11 @@ static dacp_status solve_jobs(dacp_ctx ctx, const std::vector<SyevJob> &all) {
   int per = static_cast<int>(jobs.size());
   for (int at = 0, np = per; at < np;) {
     const int take = std::min(per, np - at);
-    bool timed_out = false;
-    dacp_status st = solve_round(ctx, jobs.data() + at, take, timed_out);
-    if (st == DACP_OK && timed_out) {
-      vlog("eigensolver: register tridiagonalisation timed out, %d matrices column by column", take);
-      for (int i = at; st == DACP_OK && i < at + take; ++i)
-        st = gpu_syev(ctx, jobs[i].n, jobs[i].A, jobs[i].lda, jobs[i].w, jobs[i].Z, false);
+    bool no_exchange = false;
+    dacp_status st = solve_round(ctx, jobs.data() + at, take, no_exchange);
+    if (st == DACP_OK && no_exchange) {
+      vlog("eigensolver: no exchange between compute units, %d matrices in memory", take);
+      DACP_TRY(solve_apart(ctx, jobs.data() + at, take));  // destroys A: a failure is not tried again
     }
     if (st == DACP_E_NOMEM && take > 1) {
       (void)hipGetLastError();
