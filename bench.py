@@ -332,9 +332,9 @@ def batch96(args):
     hams = [B.dacp_build_hamiltonian(ctx, L, t) for (L, _, t) in sets]
     N = 200
     # b = 16 start columns: with 8, close pairs of levels are left unresolved more often and more
-    # realisations need the retry round (autotuned schedule: 0.63 s per call against 0.76 s).
-    # S and P from the anchor panels' moments (moment_mode 2): 0.50 s per call against 0.63 s with
-    # the explicit products
+    # realisations need the retry round (autotuned schedule: 0.277 s per call against 0.287 s with 2
+    # redone).  S and P from the anchor panels' moments (moment_mode 2): 0.277 s per call against
+    # 0.289 s with the explicit products
     opts = B.default_opts(b=16, precision=B.DACP_F32, fp64_tail_frac=0.3, moment_mode=2)
     if args.moment_mode is not None:
         opts.moment_mode = args.moment_mode

@@ -3322,9 +3322,8 @@ dacp_status central_eigs_batched(dacp_ctx ctx, int count, const dacp_ham *hams, 
   }
   EigRendezvous rendezvous(nw, ctx->device);
   std::vector<char> has_left(nw, 0);  // the worker has left the rendezvous
-  // The batched eigensolver runs one matrix per workgroup with a serial QR chase: it pays for many
-  // matrices at once, but a handful of them (a retry round) finish sooner through the per-problem
-  // solver on the workers' own streams (n = 1000: 58 ms each, against 318 ms for the batched launch).
+  // The matrices of a round share every launch of the eigensolver, so that even a few of them (a retry
+  // round) finish sooner together: one of n = 1000 takes 6 ms alone, 4 and 8 take 9.4 and 11.3 ms together.
   const bool batch_eig = ctx->batch_eig == 2 || (ctx->batch_eig == 1 && count > dacp::kBatchEigMinCount);
   // Each thread finishes its realisations r = w, w + nw, ...: with the batched eigensolver, stage by
   // stage (projection; eig(S) for all of them in the shared launch; U and H~; eig(H~) likewise;
